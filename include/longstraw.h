@@ -44,9 +44,9 @@
  *   undefined behaviour.
  *
  * Supported shapes: dtype LS_F32 with head_dim, head_dim_v <= 256 (any GQA
- * group; the forward of head_dim = head_dim_v in {64, 128} with a power-of-two
- * group runs on the matrix cores, the other shapes on a scalar kernel, both
- * with fp32 products and sums, so results differ in rounding order only);
+ * group; head dimensions that are multiples of 4 up to 128 run on the matrix
+ * cores, the other shapes on scalar kernels, both with fp32 products and sums,
+ * so results differ in rounding order only);
  * dtype LS_BF16 with head_dim = head_dim_v = 256, n_q_heads /
  * n_kv_heads dividing 32, n_q * n_q_heads * 512 < 2^31 bytes of queries,
  * pool rows n_kv_heads * 512 < 2^24 bytes, fewer than 2^29 logical pages and
@@ -198,7 +198,8 @@ size_t ls_prefix_attn_bwd_workspace_size(const ls_attn_params* p);
  * LS_FLAG_ACCUMULATE_DQ / LS_FLAG_ACCUMULATE_DKV select += over =.
  * workspace: device memory of ls_prefix_attn_bwd_workspace_size(p) bytes for
  *   the same p (it grows with the response length q_pos0 + n_q - prefix_len:
- *   the bf16 path keeps per-row-chunk dK/dV partial sums there).  Every call
+ *   it holds the partial dK/dV sums of row chunks and the partial dq sums of
+ *   key chunks, and a workspace made for p serves any smaller n_q and q_pos0).  Every call
  *   first writes Delta_i = d_out_i . out_i and lse_i * log2(e) ([n_q_heads,
  *   n_q] fp32 each) at the start of the workspace.  LS_FLAG_PREP_READY skips
  *   that step: the caller asserts that an earlier call on the same stream, with

@@ -345,22 +345,31 @@ LS_API ls_status ls_lse_merge(const float* out_part, const float* lse_part, int3
 }
 
 namespace {
-// Backward workspace: Delta and lse * log2(e), both [Hq, n_q] fp32 and padded
-// to 256 bytes, then (bf16 path) the dk/dv partials of the row chunks,
-// [chunks, 2, Hkv, kv_len - prefix_len, D] fp32.
+// Backward workspace: Delta and lse * log2(e), both [Hq, n_q] fp32, then (bf16
+// path and the fp32 matrix-core path) the dk/dv partials of the row chunks and
+// the dq partials of the key chunks; each padded to 256 bytes.  Every part
+// grows with n_q and q_pos0, so a workspace serves any call with smaller ones.
 struct BwdWorkspace {
-  size_t stat_bytes, part_bytes;
-  size_t total() const { return 2 * stat_bytes + part_bytes; }
+  size_t stat_bytes, part_bytes, dq_bytes;
+  size_t total() const { return 2 * stat_bytes + part_bytes + dq_bytes; }
 };
 
 BwdWorkspace bwd_workspace_layout(const ls_attn_params* p) {
-  BwdWorkspace w{0, 0};
+  BwdWorkspace w{0, 0, 0};
   if (!p || p->n_q <= 0 || p->n_q_heads <= 0 || p->n_kv_heads <= 0) return w;
-  w.stat_bytes = ((size_t)p->n_q * p->n_q_heads * 4 + 255) / 256 * 256;
+  auto pad = [](size_t x) { return (x + 255) / 256 * 256; };
+  w.stat_bytes = pad((size_t)p->n_q * p->n_q_heads * 4);
   const int64_t n_resp = p->q_pos0 + p->n_q - p->prefix_len;
-  if (p->dtype == LS_BF16 && n_resp > 0 && p->n_q_heads % p->n_kv_heads == 0)
-    w.part_bytes = (size_t)ls::dkdv_row_chunks(p->n_q, p->n_q_heads / p->n_kv_heads) * 2 *
-                   p->n_kv_heads * (size_t)n_resp * p->head_dim * 4;
+  if (n_resp <= 0 || p->n_q_heads % p->n_kv_heads != 0) return w;
+  const int group = p->n_q_heads / p->n_kv_heads;
+  if (p->dtype == LS_BF16) {
+    w.part_bytes = (size_t)ls::dkdv_row_chunks(p->n_q, group) * 2 * p->n_kv_heads *
+                   (size_t)n_resp * p->head_dim * 4;
+  } else if (ls::f32_mfma_fits(p->head_dim, p->head_dim_v, p->n_kv_heads)) {
+    w.part_bytes = pad((size_t)ls::f32_dkdv_chunks(p->n_q, group) * p->n_kv_heads *
+                       (size_t)n_resp * (p->head_dim + p->head_dim_v) * 4);
+    w.dq_bytes = (size_t)ls::dq_part_rows(p->n_q, group) * p->head_dim * 4;
+  }
   return w;
 }
 }  // namespace
@@ -436,6 +445,7 @@ LS_API ls_status ls_prefix_attn_bwd(const ls_attn_params* p, int64_t kv_begin, i
   a.dk_resp = dk_resp;
   a.dv_resp = dv_resp;
   a.dkdv_part = wl.part_bytes ? (float*)((char*)workspace + 2 * wl.stat_bytes) : nullptr;
+  a.dq_part = wl.dq_bytes ? (float*)((char*)workspace + 2 * wl.stat_bytes + wl.part_bytes) : nullptr;
   a.q_pos0 = p->q_pos0;
   a.prefix_len = p->prefix_len;
   a.kv_begin = kv_begin;

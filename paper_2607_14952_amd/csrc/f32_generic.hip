@@ -1,10 +1,9 @@
-// fp32 replay kernels for any head_dim <= 256 and any GQA group (the forward
-// for head_dim = head_dim_v in {64, 128} runs on the matrix cores instead,
-// fwd_f32_mfma.hip).  One wave
-// owns one (query row, head) -- or, for the response-key gradients, one
-// (key, KV head) -- and walks its keys one at a time with an online softmax;
-// lane l holds channels l, l+64, l+128, l+192.  These serve the fp32
-// configuration, where exactness rather than speed is the point.
+// fp32 replay kernels for any head_dim <= 256 and any GQA group; head dimensions
+// that are multiples of 4 up to 128 run on the matrix cores instead
+// (fwd_f32_mfma.hip, bwd_f32_mfma.hip).  One wave owns one (query row, head) --
+// or, for the response-key gradients, one (key, KV head) -- and walks its keys
+// one at a time with an online softmax; lane l holds channels l, l+64, l+128,
+// l+192.
 #include <math.h>
 
 #include "ls_internal.h"
@@ -197,27 +196,26 @@ __global__ __launch_bounds__(256) void bwd_dkdv_f32_kernel(BwdArgs a, int64_t ke
 }  // namespace
 
 hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t stream) {
-  if (fwd_f32_mfma_fits(a)) return launch_fwd_f32_mfma(a, stream);
+  if (f32_mfma_fits(a.head_dim, a.head_dim_v, a.n_kv_heads)) return launch_fwd_f32_mfma(a, stream);
   const unsigned blocks = (unsigned)(((int64_t)a.n_q * a.n_q_heads + 3) / 4);
   hipLaunchKernelGGL(fwd_f32_kernel, dim3(blocks, 1, a.n_splits), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_f32(const BwdArgs& a, bool need_dq, bool need_dkv, hipStream_t stream) {
+  const int64_t key0 = need_dkv ? (a.kv_begin > a.prefix_len ? a.kv_begin : a.prefix_len) : a.kv_end;
+  if (f32_mfma_fits(a.head_dim, a.head_dim_v, a.n_kv_heads)) return launch_bwd_f32_mfma(a, need_dq, key0, stream);
   if (need_dq) {
     const unsigned blocks = (unsigned)(((int64_t)a.n_q * a.n_q_heads + 3) / 4);
     hipLaunchKernelGGL(bwd_dq_f32_kernel, dim3(blocks), dim3(256), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (need_dkv) {
-    const int64_t key0 = a.kv_begin > a.prefix_len ? a.kv_begin : a.prefix_len;
-    const int64_t n_keys = a.kv_end - key0;
-    if (n_keys > 0) {
-      const unsigned blocks = (unsigned)((n_keys * a.n_kv_heads + 3) / 4);
-      hipLaunchKernelGGL(bwd_dkdv_f32_kernel, dim3(blocks), dim3(256), 0, stream, a, key0, n_keys);
-      return hipGetLastError();
-    }
+  const int64_t n_keys = a.kv_end - key0;
+  if (n_keys > 0) {
+    const unsigned blocks = (unsigned)((n_keys * a.n_kv_heads + 3) / 4);
+    hipLaunchKernelGGL(bwd_dkdv_f32_kernel, dim3(blocks), dim3(256), 0, stream, a, key0, n_keys);
+    return hipGetLastError();
   }
   return hipSuccess;
 }

@@ -1,129 +1,88 @@
-// fp32 split-KV forward on the matrix cores (v_mfma_f32_32x32x2_f32) for
-// head_dim = head_dim_v in {64, 128} and a power-of-two GQA group (Eq.
-// qwen-local-attn): the fp32 configuration's forward, with products and sums
-// in fp32 as the generic kernel forms them, but a 32-key x 32-row score tile
-// per MFMA chain.
+// fp32 split-KV forward on the matrix cores (f32_mfma.h) for head dimensions
+// that are multiples of 4 up to 128, any GQA group (Eq. qwen-local-attn): products
+// and sums in fp32 as the generic kernel forms them, but a 32-key x 32-row score
+// tile per MFMA chain.
 //
-// Workgroup = 4 waves x 32 packed query rows of one KV head (packed row r is
-// token r / G, head g*G + r % G, as in the bf16 kernel).  Each 32-key tile of
-// K and V is staged in LDS by the whole workgroup, then every wave forms
-//   S^T (32 keys x its 32 rows) = K Q^T        D/2 MFMAs of K = 2,
-//   O^T (D x 32 rows) += V^T P^T               16 * D/32 MFMAs of K = 2.
-// Operand layout of the 32x32x2 instruction: lane l gives A[l % 32][l / 32]
-// and B[l / 32][l % 32]; D register r of lane l is row 8(r/4) + 4(l/32) + r%4,
-// column l % 32.  For the scores, lane half h = l / 32 takes head dimensions
-// h*D/2 .. h*D/2 + D/2 - 1 (step t pairs dimensions t and D/2 + t), so a lane's
-// K and Q values are contiguous.  For the PV product, step r pairs the keys
-// held by register r of the two lane halves (8(r/4) + r%4 and that + 4): each
-// lane's P value is then its own score register, with no exchange.
-// LDS rows are padded: K rows by 4 floats (the 16-byte reads of 16 lanes on 16
-// rows fall in 16 distinct bank groups), V rows by 8 (the two key rows of one
-// read, 4 rows apart, lie 128 bytes apart modulo 256: disjoint banks).
-#include <math.h>
-
-#include "ls_internal.h"
-#include "mfma_common.h"
+// A workgroup is 4 waves = kRW groups of 32 packed query rows of one KV head
+// (packed row r is token r / G, head g*G + r % G) x 4 / kRW key slots: per
+// iteration the whole workgroup stages 4 / kRW consecutive 32-key tiles of K
+// and V in LDS, and each wave forms, for its rows and its slot's tile,
+//   S^T (32 keys x its 32 rows) = K Q^T        kDP/2 MFMAs of K = 2,
+//   O^T (kDP x 32 rows) += V^T P^T             16 * kDP/32 MFMAs of K = 2.
+// With kRW = 1 the waves' partial softmaxes are merged through LDS at the end.
+//
+// The MFMA bounds it (64 cycles each; one 16-byte LDS read per 4 of them), so
+// what matters is that every SIMD has a wave: calls whose 128-row workgroups
+// would not give each CU one take kRW = 1, four times as many workgroups with a
+// quarter of the keys per wave (128 rows x 2 heads, 3 splits: 198 -> 58 us; at
+// 288 workgroups of 128 rows kRW = 1 measured 536 us against 422).
+#include "f32_mfma.h"
 
 namespace ls {
 namespace {
+using namespace f32m;
 
-__device__ __forceinline__ int64_t phys_pos(const int32_t* __restrict__ table, int64_t j,
-                                            int log2_page) {
-  const int64_t S = int64_t(1) << log2_page;
-  return (int64_t)table[j >> log2_page] * S + (j & (S - 1));
-}
-
-__device__ __forceinline__ f32x16 mfma32x2(float a, float b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
-
-template <int kD>
+template <int kDP, int kRW>
 __global__ __launch_bounds__(256) void fwd_f32_mfma_kernel(FwdArgs a) {
-  constexpr int kKS = kD + 4, kVS = kD + 8;   // LDS row strides (floats)
-  constexpr int kHalf = kD / 2;
-  constexpr int kDB = kD / 32;                // output dimension blocks
-  __shared__ __attribute__((aligned(16))) float ks[32 * kKS];
-  __shared__ __attribute__((aligned(16))) float vs[32 * kVS];
+  constexpr int kKW = 4 / kRW;                // key slots
+  constexpr int kKS = kRowS<kDP>, kVS = kColS<kDP>;
+  constexpr int kDB = kDP / 32;               // output dimension blocks
+  __shared__ __attribute__((aligned(16))) float smem[kKW * 32 * (kKS + kVS)];
+  float* const ks = smem;
+  float* const vs = smem + kKW * 32 * kKS;
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int rw = w % kRW, kw = w / kRW;
   const int j = lane & 31, h = lane >> 5;
   const int g = blockIdx.y, sp = blockIdx.z;
-  const int lg = a.log2_group;
-  const int rows_total = a.n_q << lg;
-  const int row0 = blockIdx.x * 128;
-  const int prow = row0 + w * 32 + j;
+  const int G = a.group, D = a.head_dim, Dv = a.head_dim_v;
+  const int64_t rows_total = (int64_t)a.n_q * G;
+  const int64_t row0 = (int64_t)blockIdx.x * (32 * kRW);
+  const int64_t prow = row0 + rw * 32 + j;
   const bool row_ok = prow < rows_total;
-  const int tok = prow >> lg;
-  const int head = (g << lg) + (prow & ((1 << lg) - 1));
+  const int tok = (int)(prow / G);
+  const int head = g * G + (int)(prow - (int64_t)tok * G);
   const int64_t kb = a.split_begin[sp], ke = a.split_end[sp];
-  const int tok_last = min(a.n_q - 1, (row0 + 127) >> lg);
+  const int tok_last = (int)(min(rows_total, row0 + 32 * kRW) - 1) / G;
   const int64_t k_hi = min(ke, a.q_pos0 + tok_last + 1);            // keys of the workgroup
   const int64_t my_lim = row_ok ? min(ke, a.q_pos0 + tok + 1) : kb;  // this row: [kb, my_lim)
+  // below: visible to every row (of a whole row group)
+  const int64_t k_all =
+      row0 + 32 * kRW <= rows_total ? min(ke, a.q_pos0 + (int)(row0 / G) + 1) : kb;
   const int64_t k_lo = kb & ~int64_t(31);
   const int n_tiles = k_hi > kb ? (int)((k_hi - k_lo + 31) / 32) : 0;
 
-  float* out = a.out_part + (((int64_t)sp * a.n_q + tok) * a.n_q_heads + head) * kD;
-  float* lse_out = a.lse_part + (int64_t)sp * a.n_q * a.n_q_heads + (int64_t)head * a.n_q + tok;
-
-  float qv[kHalf];
-  if (row_ok) {
-    const float* qr = static_cast<const float*>(a.q) + ((int64_t)tok * a.n_q_heads + head) * kD +
-                      h * kHalf;
-#pragma unroll
-    for (int t = 0; t < kHalf; t += 4) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(qr + t);
-      qv[t] = v[0];
-      qv[t + 1] = v[1];
-      qv[t + 2] = v[2];
-      qv[t + 3] = v[3];
-    }
-  } else {
-#pragma unroll
-    for (int t = 0; t < kHalf; ++t) qv[t] = 0.f;
-  }
+  float qv[kDP / 2];
+  const int64_t rh = row_ok ? (int64_t)tok * a.n_q_heads + head : 0;   // (rows past the end: row 0)
+  load_half_row<kDP>(qv, static_cast<const float*>(a.q) + rh * D, D, h);
   f32x16 oacc[kDB];
 #pragma unroll
   for (int b = 0; b < kDB; ++b) oacc[b] = zero16();
   float m_run = -INFINITY, l_run = 0.f;
 
-  const float* kp = static_cast<const float*>(a.k_pool) + (int64_t)g * kD;
-  const float* vp = static_cast<const float*>(a.v_pool) + (int64_t)g * kD;
-  for (int t = 0; t < n_tiles; ++t) {
+  KvStage<kDP, kKW> stage;
+  if (n_tiles > 0) {
+    stage.load_pages(a, k_lo, kb, k_hi, tid);
+    stage.load(a, g, k_lo, kb, k_hi, tid);
+  }
+  for (int t = 0; t < n_tiles; t += kKW) {
     const int64_t t0 = k_lo + (int64_t)t * 32;
-    __syncthreads();   // every wave is done with the previous tile
-    // Keys outside [kb, k_hi) are staged as zeros (their page-table entry may
-    // not exist) and masked below.
-    for (int idx = tid; idx < 32 * (kD / 4); idx += 256) {
-      const int key = idx / (kD / 4), c = 4 * (idx % (kD / 4));
-      const int64_t pos = t0 + key;
-      f32x4 kv = {0.f, 0.f, 0.f, 0.f}, vv = {0.f, 0.f, 0.f, 0.f};
-      if (pos >= kb && pos < k_hi) {
-        const int64_t pr = phys_pos(a.page_table, pos, a.log2_page);
-        kv = *reinterpret_cast<const f32x4*>(kp + pr * a.k_pos_stride + c);
-        vv = *reinterpret_cast<const f32x4*>(vp + pr * a.v_pos_stride + c);
-      }
-      *reinterpret_cast<f32x4*>(ks + key * kKS + c) = kv;
-      *reinterpret_cast<f32x4*>(vs + key * kVS + c) = vv;
-    }
+    __syncthreads();   // every wave is done with the previous tiles
+    stage.template store<kKS, kVS>(a, ks, vs, tid);
     __syncthreads();
+    if (t + kKW < n_tiles) stage.load(a, g, t0 + 32 * kKW, kb, k_hi, tid);
+    if (t + kw >= n_tiles) continue;   // (uniform per wave; the barriers above are not skipped)
 
-    f32x16 s = zero16();
+    const int64_t tw = t0 + 32 * kw;
+    f32x16 s = row_product<kDP, kKS>(ks + kw * 32 * kKS, qv, j, h);
+    if (tw < kb || tw + 32 > k_all) {
 #pragma unroll
-    for (int d = 0; d < kHalf; d += 4) {
-      const f32x4 kk = *reinterpret_cast<const f32x4*>(ks + j * kKS + h * kHalf + d);
-      s = mfma32x2(kk[0], qv[d], s);
-      s = mfma32x2(kk[1], qv[d + 1], s);
-      s = mfma32x2(kk[2], qv[d + 2], s);
-      s = mfma32x2(kk[3], qv[d + 3], s);
+      for (int r = 0; r < 16; ++r)
+        if (!in_rows(r, h, kb - tw, my_lim - tw)) s[r] = -INFINITY;
     }
-    // register r holds key t0 + 8(r/4) + 4h + r%4 of row prow
-    float mx = -INFINITY;
+    float mx = s[0];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int64_t pos = t0 + 8 * (r >> 2) + 4 * h + (r & 3);
-      if (pos < kb || pos >= my_lim) s[r] = -INFINITY;
-      mx = fmaxf(mx, s[r]);
-    }
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
     mx = half_max(mx) * a.scale_log2;
     const float m_new = fmaxf(m_run, mx);
     const float m_use = m_new == -INFINITY ? 0.f : m_new;
@@ -138,49 +97,84 @@ __global__ __launch_bounds__(256) void fwd_f32_mfma_kernel(FwdArgs a) {
     m_run = m_new;
 #pragma unroll
     for (int b = 0; b < kDB; ++b) oacc[b] *= alpha;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float* vrow = vs + (8 * (r >> 2) + 4 * h + (r & 3)) * kVS + j;
-#pragma unroll
-      for (int b = 0; b < kDB; ++b) oacc[b] = mfma32x2(vrow[32 * b], s[r], oacc[b]);
-    }
+    col_product<kDP, kVS>(vs + kw * 32 * kVS, s, oacc, j, h);
   }
 
-  const float l_tot = half_sum(l_run);
+  float l_tot = half_sum(l_run);
+  if constexpr (kKW > 1) {
+    // merge the key slots: slot 0's wave adds the others' accumulators, each
+    // rescaled to the common maximum, in slot order
+    constexpr int kAcc = kDB * 16 * 64;
+    static_assert((kKW - 1) * kAcc + 2 * kKW * 64 <= kKW * 32 * (kKS + kVS), "merge area");
+    __syncthreads();
+    float* stat = smem + (kKW - 1) * kAcc;
+    stat[(2 * kw) * 64 + lane] = m_run;
+    stat[(2 * kw + 1) * 64 + lane] = l_tot;
+    if (kw > 0) acc_to_lds<kDB>(smem + (kw - 1) * kAcc, oacc, lane);
+    __syncthreads();
+    if (kw > 0) return;
+    float m = m_run;
+#pragma unroll
+    for (int k = 1; k < kKW; ++k) m = fmaxf(m, stat[2 * k * 64 + lane]);
+    const float m_use = m == -INFINITY ? 0.f : m;
+    const float w0 = __builtin_amdgcn_exp2f(m_run - m_use);
+    l_tot *= w0;
+#pragma unroll
+    for (int b = 0; b < kDB; ++b) oacc[b] *= w0;
+#pragma unroll
+    for (int k = 1; k < kKW; ++k) {
+      const float wk = __builtin_amdgcn_exp2f(stat[2 * k * 64 + lane] - m_use);
+      l_tot = fmaf(wk, stat[(2 * k + 1) * 64 + lane], l_tot);
+      acc_add_lds<kDB>(oacc, smem + (k - 1) * kAcc, wk, lane);
+    }
+    m_run = m;
+  }
   if (row_ok) {
+    float* out = a.out_part + (((int64_t)sp * a.n_q + tok) * a.n_q_heads + head) * Dv;
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
 #pragma unroll
     for (int b = 0; b < kDB; ++b) {
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
+        const int d = 32 * b + 8 * q4 + 4 * h;
         f32x4 v;
-        v[0] = oacc[b][4 * q4 + 0] * inv;
-        v[1] = oacc[b][4 * q4 + 1] * inv;
-        v[2] = oacc[b][4 * q4 + 2] * inv;
-        v[3] = oacc[b][4 * q4 + 3] * inv;
-        *reinterpret_cast<f32x4*>(out + 32 * b + 8 * q4 + 4 * h) = v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = oacc[b][4 * q4 + e] * inv;
+        if (d < Dv) *reinterpret_cast<f32x4*>(out + d) = v;
       }
     }
     if (h == 0)
-      *lse_out = l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
+      a.lse_part[((int64_t)sp * a.n_q_heads + head) * a.n_q + tok] =
+          l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
+  }
+}
+
+template <int kDP>
+void launch(const FwdArgs& a, hipStream_t stream) {
+  const int64_t rows = (int64_t)a.n_q * a.group;
+  const int64_t wide = (rows + 127) / 128 * a.n_kv_heads * a.n_splits;
+  // a 128-row workgroup for each CU, or quarter-size ones
+  if (wide >= 256) {
+    const dim3 grid((unsigned)((rows + 127) / 128), a.n_kv_heads, a.n_splits);
+    hipLaunchKernelGGL((fwd_f32_mfma_kernel<kDP, 4>), grid, dim3(256), 0, stream, a);
+  } else {
+    const dim3 grid((unsigned)((rows + 31) / 32), a.n_kv_heads, a.n_splits);
+    hipLaunchKernelGGL((fwd_f32_mfma_kernel<kDP, 1>), grid, dim3(256), 0, stream, a);
   }
 }
 
 }  // namespace
 
-// (packed rows need a power-of-two group)
-bool fwd_f32_mfma_fits(const FwdArgs& a) {
-  return a.head_dim == a.head_dim_v && (a.head_dim == 64 || a.head_dim == 128) &&
-         a.group == (1 << a.log2_group);
+bool f32_mfma_fits(int head_dim, int head_dim_v, int n_kv_heads) {
+  return head_dim <= kMaxWidth && head_dim_v <= kMaxWidth && head_dim % 4 == 0 &&
+         head_dim_v % 4 == 0 && n_kv_heads <= 65535;   // (a grid dimension)
 }
 
 hipError_t launch_fwd_f32_mfma(const FwdArgs& a, hipStream_t stream) {
-  const unsigned row_tiles = (unsigned)(((int64_t)a.n_q * a.group + 127) / 128);
-  const dim3 grid(row_tiles, a.n_kv_heads, a.n_splits);
-  if (a.head_dim == 64)
-    hipLaunchKernelGGL(fwd_f32_mfma_kernel<64>, grid, dim3(256), 0, stream, a);
-  else
-    hipLaunchKernelGGL(fwd_f32_mfma_kernel<128>, grid, dim3(256), 0, stream, a);
+  const int d = a.head_dim > a.head_dim_v ? a.head_dim : a.head_dim_v;
+  if (d <= 64) launch<64>(a, stream);
+  else if (d <= 96) launch<96>(a, stream);
+  else launch<128>(a, stream);
   return hipGetLastError();
 }
 

@@ -23,6 +23,25 @@ inline int dkdv_row_chunks(int n_q, int group) {
   return (int)((rows + kDkdvRowChunk - 1) / kDkdvRowChunk);
 }
 
+// Row chunks of the fp32 matrix-core dk/dv kernel: 128 packed rows (one 32-row
+// tile per wave of its workgroups), at most 16 chunks.
+inline int f32_dkdv_chunks(int n_q, int group) {
+  const int64_t c = ((int64_t)n_q * group + 127) / 128;
+  return (int)(c < 16 ? c : 16);
+}
+
+// Rows (of head_dim floats) that the backward workspace has for dq partial sums
+// of key chunks: 512 workgroups, two per CU, of up to 128 packed rows.  It
+// grows with n_q, so that a workspace made for more rows serves fewer.
+inline int64_t dq_part_rows(int n_q, int group) {
+  const int64_t rows = (int64_t)n_q * group;
+  return 512 * (rows < 128 ? rows : 128);
+}
+
+// Whether the fp32 matrix-core kernels take these shapes (the generic kernels
+// take the others).
+bool f32_mfma_fits(int head_dim, int head_dim_v, int n_kv_heads);
+
 // Everything a forward-split kernel needs; passed by value as a kernel argument.
 struct FwdArgs {
   const void* q;
@@ -55,7 +74,10 @@ struct BwdArgs {
   float* dq;                // [n_q, Hq, D]
   float* dk_resp;           // [kv_len - prefix_len, Hkv, D]
   float* dv_resp;           // [kv_len - prefix_len, Hkv, Dv]
-  float* dkdv_part;         // bf16 path: [row chunks, 2, Hkv, kv_end - prefix_len, D] partials
+  float* dkdv_part;         // partial dk/dv sums of row chunks (bf16: [row chunks, 2, Hkv,
+                            // kv_end - prefix_len, D]; fp32: [row chunks, keys, Hkv, D + Dv])
+  float* dq_part;           // partial dq sums of key chunks [chunks, n_q, Hq, D], unscaled
+                            // (dq_part_rows rows in all)
   int64_t q_pos0;
   int64_t prefix_len;
   int64_t kv_begin, kv_end;
@@ -125,10 +147,13 @@ hipError_t launch_merge(const float* out_part, const float* lse_part, int n_spli
                         int n_heads, int dv, bool out_bf16, bool bf16_numerator, void* out,
                         float* lse, hipStream_t stream);
 hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t stream);
-// fp32 forward on the matrix cores, for the shapes fwd_f32_mfma_fits accepts
-// (launch_fwd_f32 takes it for them and the generic kernel for the others)
-bool fwd_f32_mfma_fits(const FwdArgs& a);
+// fp32 on the matrix cores, for the shapes f32_mfma_fits accepts (launch_fwd_f32
+// and launch_bwd_f32 take them for those and the generic kernels for the others)
 hipError_t launch_fwd_f32_mfma(const FwdArgs& a, hipStream_t stream);
+// dq over the range and dk/dv of its keys from key0 on (none when key0 >= kv_end)
+hipError_t launch_bwd_f32_mfma(const BwdArgs& a, bool need_dq, int64_t key0, hipStream_t stream);
+// dq (+)= scale * the sum of a.dq_part's n_chunks partials, in order
+hipError_t launch_dq_reduce(const BwdArgs& a, int n_chunks, hipStream_t stream);
 hipError_t launch_hbm_read(const void* buf, int64_t n16, uint32_t* out, hipStream_t stream);
 hipError_t launch_dsa_scores(const DsaArgs& a, hipStream_t stream);
 hipError_t launch_topk(const TopkArgs& a, hipStream_t stream);

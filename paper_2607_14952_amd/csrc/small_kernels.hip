@@ -203,6 +203,29 @@ __global__ __launch_bounds__(256) void prep_vec_kernel(const TD* __restrict__ d_
   }
 }
 
+// ---------------------------------------------------------------- dq chunks
+// dq (+)= scale * the sum of the key chunks' partials [n_chunks, rows, D], in
+// chunk order.  One thread per 4 values; four chunks' loads in flight.
+__global__ __launch_bounds__(256) void dq_reduce_kernel(const f32x4* __restrict__ part,
+                                                        int64_t n4, int n_chunks, float scale,
+                                                        int accumulate, f32x4* __restrict__ dq) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n4) return;
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  int c = 0;
+  for (; c + 4 <= n_chunks; c += 4) {
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = part[(int64_t)(c + u) * n4 + i];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) sum += v[u];
+  }
+  for (; c < n_chunks; ++c) sum += part[(int64_t)c * n4 + i];
+  sum *= scale;
+  if (accumulate) sum += dq[i];
+  dq[i] = sum;
+}
+
 // ---------------------------------------------------------------- HBM read probe
 // Reads n16 16-byte units once and XORs their 32-bit words: a read-only
 // streaming pass with no arithmetic to speak of, the measured read ceiling the
@@ -305,6 +328,14 @@ hipError_t launch_bwd_prep(const void* d_out, const void* out, bool dout_bf16, b
     LS_PREP(float, float);
   }
 #undef LS_PREP
+  return hipGetLastError();
+}
+
+hipError_t launch_dq_reduce(const BwdArgs& a, int n_chunks, hipStream_t stream) {
+  const int64_t n4 = (int64_t)a.n_q * a.n_q_heads * a.head_dim / 4;
+  hipLaunchKernelGGL(dq_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream,
+                     (const f32x4*)a.dq_part, n4, n_chunks, a.scale, a.accumulate_dq,
+                     (f32x4*)a.dq);
   return hipGetLastError();
 }
 
