@@ -365,6 +365,7 @@ BwdWorkspace bwd_workspace_layout(const ls_attn_params* p) {
   if (p->dtype == LS_BF16) {
     w.part_bytes = (size_t)ls::dkdv_row_chunks(p->n_q, group) * 2 * p->n_kv_heads *
                    (size_t)n_resp * p->head_dim * 4;
+    w.dq_bytes = (size_t)ls::dq_part_rows(p->n_q, group) * p->head_dim * 4;
   } else if (ls::f32_mfma_fits(p->head_dim, p->head_dim_v, p->n_kv_heads)) {
     w.part_bytes = pad((size_t)ls::f32_dkdv_chunks(p->n_q, group) * p->n_kv_heads *
                        (size_t)n_resp * (p->head_dim + p->head_dim_v) * 4);
@@ -464,6 +465,8 @@ LS_API ls_status ls_prefix_attn_bwd(const ls_attn_params* p, int64_t kv_begin, i
   a.scale_log2 = p->softmax_scale * ls::kLog2e;
   a.accumulate_dq = (p->flags & LS_FLAG_ACCUMULATE_DQ) ? 1 : 0;
   a.accumulate_dkv = (p->flags & LS_FLAG_ACCUMULATE_DKV) ? 1 : 0;
+  const int64_t packed = (int64_t)p->n_q * a.group, chunks = ls::dkdv_row_chunks(p->n_q, a.group);
+  a.dkdv_rows = (int32_t)(((packed + chunks - 1) / chunks + 31) / 32 * 32);
   e = p->dtype == LS_BF16 ? ls::launch_bwd_bf16_d256(a, true, has_resp, s)
                           : ls::launch_bwd_f32(a, true, has_resp, s);
   return e == hipSuccess ? LS_OK : hip_fail(e, "backward launch");

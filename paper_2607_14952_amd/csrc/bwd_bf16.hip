@@ -21,6 +21,8 @@
 // gradient.
 #include <math.h>
 
+#include <algorithm>
+
 #include "ls_internal.h"
 #include "mfma_common.h"
 
@@ -227,8 +229,12 @@ __device__ __forceinline__ void dq_step(const BwdArgs& a, char* __restrict__ nex
                                       &tail);
 }
 
+// Workgroup z works on key tiles z * tiles_per_chunk .. + tiles_per_chunk - 1 of
+// the range.  With several chunks (part not null) each writes its unscaled sums
+// to part[z] and dq_reduce_kernel adds them in order; dq_chunks chooses.
 template <bool kPerKey>
-__global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a) {
+__global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a, int tiles_per_chunk,
+                                                                  float* __restrict__ part) {
   __shared__ __attribute__((aligned(1024))) char smem[kQSlots * kQStage];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -249,16 +255,20 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a) {
   const int head = (g << lg) + (prow & ((1 << lg) - 1));
   const int tok_first = row0 >> lg;
   const int tok_last = min(a.n_q - 1, (row0 + kQBM - 1) >> lg);
-  const int64_t kb = a.kv_begin;
-  const int64_t k_hi = min(a.kv_end, a.q_pos0 + tok_last + 1);
-  const int64_t k_all = min(a.kv_end, a.q_pos0 + tok_first + 1);
-  const int64_t my_lim = min(a.kv_end, a.q_pos0 + tok + 1);
+  const int64_t c_lo = (a.kv_begin & ~int64_t(kQBN - 1)) + (int64_t)wi.z * tiles_per_chunk * kQBN;
+  const int64_t kb = max(a.kv_begin, c_lo);
+  const int64_t ke = min(a.kv_end, c_lo + (int64_t)tiles_per_chunk * kQBN);
+  const int64_t k_hi = min(ke, a.q_pos0 + tok_last + 1);
+  const int64_t k_all = min(ke, a.q_pos0 + tok_first + 1);
+  const int64_t my_lim = min(ke, a.q_pos0 + tok + 1);
   const int64_t k_lo = kb & ~int64_t(kQBN - 1);
   const int n_tiles = k_hi > kb ? (int)((k_hi - k_lo + kQBN - 1) / kQBN) : 0;
 
-  float* dq = a.dq + ((int64_t)tok * a.n_q_heads + head) * kD;
+  const bool add = !part && a.accumulate_dq;
+  float* dq = part ? part + (((int64_t)wi.z * a.n_q + tok) * a.n_q_heads + head) * kD
+                   : a.dq + ((int64_t)tok * a.n_q_heads + head) * kD;
   if (n_tiles == 0) {
-    if (row_ok && !a.accumulate_dq) {
+    if (row_ok && !add) {
       const f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int c = 0; c < 32; ++c) *reinterpret_cast<f32x4*>(dq + c * 8 + hh * 4) = z;
@@ -370,17 +380,18 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a) {
   wait_fetch();   // no direct load is left in flight when the waves end
 
   if (row_ok) {
+    const float c = part ? 1.f : a.scale;
 #pragma unroll
     for (int db = 0; db < 8; ++db) {
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         f32x4* dst = reinterpret_cast<f32x4*>(dq + 32 * db + 8 * q4 + 4 * hh);
         f32x4 v;
-        v[0] = acc[db][4 * q4 + 0] * a.scale;
-        v[1] = acc[db][4 * q4 + 1] * a.scale;
-        v[2] = acc[db][4 * q4 + 2] * a.scale;
-        v[3] = acc[db][4 * q4 + 3] * a.scale;
-        if (a.accumulate_dq) v += *dst;
+        v[0] = acc[db][4 * q4 + 0] * c;
+        v[1] = acc[db][4 * q4 + 1] * c;
+        v[2] = acc[db][4 * q4 + 2] * c;
+        v[3] = acc[db][4 * q4 + 3] * c;
+        if (add) v += *dst;
         *dst = v;
       }
     }
@@ -390,7 +401,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a) {
 // ============================================================== dk/dv kernel
 // Workgroup = 4 waves = kKeysPerWG response keys of one KV head (wave w owns
 // keys j0 + 32w .. +31; lane l owns key l % 32 and keeps its K and V rows in
-// registers) x one chunk of kRowChunk packed query rows.  The chunk's 32-row
+// registers) x one chunk of a.dkdv_rows packed query rows (dkdv_row_chunks).  The chunk's 32-row
 // tiles of Q and dO stream into a four-slot LDS ring by direct loads, two
 // tiles ahead, each with the rows' lse * log2(e) and Delta.  Per tile:
 //   S = Q K^T, dP = dO V^T (lane = key, result registers = rows),
@@ -400,7 +411,6 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a) {
 // The chunk's partial sums go to the workspace; dkdv_reduce_kernel adds the
 // active chunks in order (deterministic), scales dk and writes or accumulates.
 constexpr int kKeysPerWG = 128;
-constexpr int kRowChunk = kDkdvRowChunk;                   // packed query rows per workgroup
 constexpr int kRStat = 256;                                // per wave: 32 lse2 + 32 Delta floats
 constexpr int kRStage = 2 * kTileBytes + 4 * kRStat;       // Q tile, dO tile, stats
 constexpr int kRAhead = 2;
@@ -414,10 +424,10 @@ __device__ __forceinline__ int dkdv_row_lo(const BwdArgs& a, int64_t j0, int chu
   if (first_tok < 0) first_tok = 0;
   const int64_t rows_total = (int64_t)a.n_q << a.log2_group;
   const int64_t vis = min(rows_total, first_tok << a.log2_group) & ~int64_t(31);
-  return (int)max((int64_t)chunk * kRowChunk, vis);
+  return (int)max((int64_t)chunk * a.dkdv_rows, vis);
 }
 __device__ __forceinline__ int dkdv_row_hi(const BwdArgs& a, int chunk) {
-  return min(a.n_q << a.log2_group, (chunk + 1) * kRowChunk);
+  return (int)min((int64_t)a.n_q << a.log2_group, (int64_t)(chunk + 1) * a.dkdv_rows);
 }
 
 // Direct loads of 32 packed query rows (token, head of KV group g) of Q or dO
@@ -616,17 +626,53 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(BwdArgs a, int64_t key
 
 }  // namespace
 
+namespace {
+
+// Key chunks of a dq launch.  One workgroup (128 KiB of LDS) runs per CU, so
+// `items` workgroups of `tiles` key tiles take ceil(items / 256) rounds of
+// (tiles + 6) tile times: 6 for the first loads, the Q and dO rows and the
+// result.  c chunks cut the rounds to whole shares of fewer tiles (10 items
+// leave 246 CUs idle, 140 leave 116) and add the partial sums' way through
+// memory, about 4.7e-4 tile times per row and chunk (1 KiB out and back in
+// against 32 KiB of K and V per 0.95 us) and a launch.  The chunk count with
+// the least sum is taken; one when items fill the rounds (512 items: 2 rounds
+// either way).  Measured: 77 rows x 16 heads over 32,768 keys 836 -> 76 us
+// (25 chunks), 1,111 rows over 12,500 keys 396 -> 345 us (3 chunks), 952 rows
+// over 32,768 keys 952 -> 568 us (2 chunks), the reduce included.
+int dq_chunks(const BwdArgs& a, int64_t items, int64_t tiles) {
+  const int64_t rows = (int64_t)a.n_q * a.n_q_heads;
+  const int64_t most = std::min(dq_part_rows(a.n_q, a.group) / rows, std::min<int64_t>(256, tiles / 4));
+  int best = 1;
+  double least = 0;
+  for (int c = 1; c == 1 || c <= most; ++c) {
+    double cost = (double)((items * c + 255) / 256) * (double)((tiles + c - 1) / c + 6);
+    if (c > 1) cost += 5 + 4.7e-4 * (double)rows * c;
+    if (c == 1 || cost < least) {
+      best = c;
+      least = cost;
+    }
+  }
+  return best;
+}
+
+}  // namespace
+
 hipError_t launch_bwd_bf16_d256(const BwdArgs& a, bool need_dq, bool need_dkv,
                                 hipStream_t stream) {
   if (need_dq) {
     const unsigned row_tiles = (unsigned)(((int64_t)a.n_q * a.group + kQBM - 1) / kQBM);
+    const int64_t tiles = (a.kv_end - (a.kv_begin & ~int64_t(kQBN - 1)) + kQBN - 1) / kQBN;
+    const int want = dq_chunks(a, (int64_t)row_tiles * a.n_kv_heads, tiles);
+    const int per = (int)((tiles + want - 1) / want);
+    const int n_chunks = (int)((tiles + per - 1) / per);
+    float* part = n_chunks > 1 ? a.dq_part : nullptr;
+    const dim3 grid(row_tiles, a.n_kv_heads, n_chunks);
     if (a.log2_page < 5)
-      hipLaunchKernelGGL(bwd_dq_bf16_d256_kernel<true>, dim3(row_tiles, a.n_kv_heads), dim3(256),
-                         0, stream, a);
+      hipLaunchKernelGGL(bwd_dq_bf16_d256_kernel<true>, grid, dim3(256), 0, stream, a, per, part);
     else
-      hipLaunchKernelGGL(bwd_dq_bf16_d256_kernel<false>, dim3(row_tiles, a.n_kv_heads), dim3(256),
-                         0, stream, a);
+      hipLaunchKernelGGL(bwd_dq_bf16_d256_kernel<false>, grid, dim3(256), 0, stream, a, per, part);
     hipError_t e = hipGetLastError();
+    if (e == hipSuccess && part) e = launch_dq_reduce(a, n_chunks, stream);
     if (e != hipSuccess) return e;
   }
   if (need_dkv) {

@@ -43,3 +43,30 @@ def _f32(name, hq, hkv, d, dv, prefix, resp, page=64, shards=1, splits=2):
 ], ids=lambda c: c.name)
 def test_f32_shapes(cfg):
     full_case(cfg)
+
+
+def _bf16(name, prefix, resp, hq=16, hkv=2, page=256, shards=1, splits=2, **kw):
+    # No planted keys: with all of them aimed at one row, dq is what is left of
+    # large terms that cancel, and the bf16 rounding of out inside Delta alone
+    # moves it by 9.2e-3 (10,017 keys, 100 planted, the rest in 64 bits; 8e-5
+    # without planted keys).
+    kw.setdefault("plant_frac", 0.0)
+    return configs.C3.scaled(name=f"bf16_{name}", n_q_heads=hq, n_kv_heads=hkv, prefix_len=prefix,
+                             resp_len=resp, page_size=page, n_shards=shards,
+                             splits_per_shard=splits, **kw)
+
+
+@pytest.mark.parametrize("cfg", [
+    # dq over key chunks (few row tiles): one row, the last chunk one tile;
+    # 16-position pages; two row tiles per KV head, the second ragged
+    _bf16("dq_chunks_r1", 10_017, 1),
+    _bf16("dq_chunks_p16", 5_003, 17, page=16),
+    _bf16("dq_chunks_r20", 8_192, 20, shards=3),
+    # enough row tiles that a few chunks only even out the last round
+    _bf16("dq_rounds", 2_100, 1_120),
+    # dk/dv row chunks of 128 rows up to 16 of them, the last one ragged
+    _bf16("dkdv_r17", 300, 17),
+    _bf16("dkdv_g4", 64, 519, hq=4, hkv=1),
+], ids=lambda c: c.name)
+def test_bf16_shapes(cfg):
+    full_case(cfg)
