@@ -178,6 +178,21 @@ ls_status ls_lse_merge(const float* out_part, const float* lse_part, int32_t n_s
                        int32_t n_q, int32_t n_heads, int32_t dv, int32_t out_dtype,
                        void* out, float* lse, uint32_t flags, void* stream);
 
+/*
+ * ls_lse_merge_groups: both levels of the composition in one launch.  Group k
+ * holds parts group_begin[k] .. group_end[k] - 1 (host arrays; non-empty
+ * ranges in [0, n_parts), a part may be in several groups or in none), its fp32
+ * result goes to group_out[k] [n_q, n_heads, dv] and group_lse[k] [n_heads,
+ * n_q], and the groups' results, in group order, compose out and lse, as
+ * ls_lse_merge of each group and then of group_out / group_lse with these
+ * flags does.  At most 64 groups (LS_ERR_UNSUPPORTED beyond).
+ */
+ls_status ls_lse_merge_groups(const float* out_part, const float* lse_part, int32_t n_parts,
+                              const int32_t* group_begin, const int32_t* group_end,
+                              int32_t n_groups, int32_t n_q, int32_t n_heads, int32_t dv,
+                              int32_t out_dtype, float* group_out, float* group_lse, void* out,
+                              float* lse, uint32_t flags, void* stream);
+
 /* Bytes of device workspace ls_prefix_attn_bwd needs for these params. */
 size_t ls_prefix_attn_bwd_workspace_size(const ls_attn_params* p);
 

@@ -23,10 +23,10 @@ FLAG_PREP_READY = 32
 STATUS = {0: "LS_OK", -1: "LS_ERR_INVALID_ARG", -2: "LS_ERR_UNSUPPORTED", -3: "LS_ERR_WORKSPACE",
           -4: "LS_ERR_ALIAS", -5: "LS_ERR_STALE", -6: "LS_ERR_PAGE_OOB", -7: "LS_ERR_HIP"}
 EXPORTS = ["ls_abi_version", "ls_status_string", "ls_last_error", "ls_gather_kv", "ls_scatter_kv",
-           "ls_prefix_attn_fwd", "ls_lse_merge", "ls_prefix_attn_bwd_workspace_size",
-           "ls_prefix_attn_bwd", "ls_sparse_attn_workspace_size", "ls_sparse_attn_fwd",
-           "ls_sparse_attn_bwd", "ls_dsa_index_scores", "ls_topk_select", "ls_hbm_read_probe",
-           "ls_sparse_attn_fwd_noalloc"]
+           "ls_prefix_attn_fwd", "ls_lse_merge", "ls_lse_merge_groups",
+           "ls_prefix_attn_bwd_workspace_size", "ls_prefix_attn_bwd", "ls_sparse_attn_workspace_size",
+           "ls_sparse_attn_fwd", "ls_sparse_attn_bwd", "ls_dsa_index_scores", "ls_topk_select",
+           "ls_hbm_read_probe", "ls_sparse_attn_fwd_noalloc"]
 
 
 class AttnParams(ctypes.Structure):
@@ -83,6 +83,11 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.ls_lse_merge.restype = c_int32
     lib.ls_lse_merge.argtypes = [c_void_p, c_void_p, c_int32, c_int32, c_int32, c_int32, c_int32,
                                  c_void_p, c_void_p, c_uint32, c_void_p]
+    lib.ls_lse_merge_groups.restype = c_int32
+    lib.ls_lse_merge_groups.argtypes = [c_void_p, c_void_p, c_int32, POINTER(c_int32),
+                                        POINTER(c_int32), c_int32, c_int32, c_int32, c_int32,
+                                        c_int32, c_void_p, c_void_p, c_void_p, c_void_p, c_uint32,
+                                        c_void_p]
     lib.ls_prefix_attn_bwd_workspace_size.restype = c_size_t
     lib.ls_prefix_attn_bwd_workspace_size.argtypes = [P]
     lib.ls_prefix_attn_bwd.restype = c_int32
@@ -268,6 +273,32 @@ def lse_merge(out_part, lse_part, *, out_dtype=None, out=None, lse=None, flags: 
                                       _ptr(lse_part, torch.float32, "lse_part"), n, R, H, Dv,
                                       _dtype_code(out), _ptr(out, None, "out"),
                                       _ptr(lse, torch.float32, "lse"), flags, _stream(stream)))
+    return out, lse
+
+
+MAX_MERGE_GROUPS = 64
+
+
+def lse_merge_groups(out_part, lse_part, groups, *, group_out, group_lse, out, lse, flags: int = 0,
+                     stream=None):
+    """ls_lse_merge_groups: parts [b, e) of each group -> group_out / group_lse (fp32),
+    and the groups, in order -> out / lse."""
+    torch = _torch()
+    n, R, H, Dv = out_part.shape
+    k = len(groups)
+    for t, shape, name in ((lse_part, (n, H, R), "lse_part"), (group_out, (k, R, H, Dv), "group_out"),
+                           (group_lse, (k, H, R), "group_lse"), (out, (R, H, Dv), "out"),
+                           (lse, (H, R), "lse")):
+        if tuple(t.shape) != shape:
+            raise ValueError(f"lse_merge_groups: {name} must have shape {shape} "
+                             f"(got {tuple(t.shape)})")
+    begin = (c_int32 * k)(*[b for b, _ in groups])
+    end = (c_int32 * k)(*[e for _, e in groups])
+    f32 = torch.float32
+    check(load_library().ls_lse_merge_groups(
+        _ptr(out_part, f32, "out_part"), _ptr(lse_part, f32, "lse_part"), n, begin, end, k, R, H,
+        Dv, _dtype_code(out), _ptr(group_out, f32, "group_out"), _ptr(group_lse, f32, "group_lse"),
+        _ptr(out, None, "out"), _ptr(lse, f32, "lse"), flags, _stream(stream)))
     return out, lse
 
 

@@ -301,15 +301,26 @@ LS_API ls_status ls_prefix_attn_fwd(const ls_attn_params* p, const ls_split* spl
 
   ls::FwdArgs a;
   fill_common(p, a);
-  for (int i0 = 0; i0 < n_splits; i0 += ls::kMaxSplitsPerLaunch) {
-    int n = n_splits - i0 < ls::kMaxSplitsPerLaunch ? n_splits - i0 : ls::kMaxSplitsPerLaunch;
+  for (int i0 = 0; i0 < n_splits; i0 += a.n_splits) {
+    // as many splits as the arguments hold and 32-bit offsets reach; a longer
+    // split goes alone
+    a.split_base = splits[i0].kv_begin;
+    int n = 0;
+    while (n < ls::kMaxSplitsPerLaunch && i0 + n < n_splits &&
+           splits[i0 + n].kv_end - a.split_base <= (int64_t)UINT32_MAX) {
+      a.split_lo[n] = (uint32_t)(splits[i0 + n].kv_begin - a.split_base);
+      a.split_hi[n] = (uint32_t)(splits[i0 + n].kv_end - a.split_base);
+      ++n;
+    }
+    a.split_more = 0;
+    if (n == 0) {
+      n = 1;
+      a.split_lo[0] = a.split_hi[0] = 0;
+      a.split_more = splits[i0].kv_end - a.split_base;
+    }
     a.n_splits = n;
     a.out_part = out_part + part_out * i0;
     a.lse_part = lse_part + part_lse * i0;
-    for (int i = 0; i < n; ++i) {
-      a.split_begin[i] = splits[i0 + i].kv_begin;
-      a.split_end[i] = splits[i0 + i].kv_end;
-    }
     hipError_t e = p->dtype == LS_BF16 ? ls::launch_fwd_bf16_d256(a, s) : ls::launch_fwd_f32(a, s);
     if (e != hipSuccess) return hip_fail(e, "forward launch");
   }
@@ -338,9 +349,64 @@ LS_API ls_status ls_lse_merge(const float* out_part, const float* lse_part, int3
                           rng("lse", lse, (size_t)n_q * n_heads * 4)};
   ls_status st = check_alias(outs, ins);
   if (st != LS_OK) return st;
-  hipError_t e = ls::launch_merge(out_part, lse_part, n_splits, n_q, n_heads, dv,
+  const int32_t begin = 0;
+  hipError_t e = ls::launch_merge(out_part, lse_part, &begin, &n_splits, 1, n_q, n_heads, dv,
                                   out_dtype == LS_BF16, (flags & LS_FLAG_BF16_NUMERATOR) != 0,
-                                  out, lse, (hipStream_t)stream);
+                                  nullptr, nullptr, out, lse, (hipStream_t)stream);
+  return e == hipSuccess ? LS_OK : hip_fail(e, "merge launch");
+}
+
+LS_API ls_status ls_lse_merge_groups(const float* out_part, const float* lse_part,
+                                     int32_t n_parts, const int32_t* group_begin,
+                                     const int32_t* group_end, int32_t n_groups, int32_t n_q,
+                                     int32_t n_heads, int32_t dv, int32_t out_dtype,
+                                     float* group_out, float* group_lse, void* out, float* lse,
+                                     uint32_t flags, void* stream) {
+  if (n_parts <= 0 || n_q < 0 || n_heads <= 0 || dv <= 0)
+    return fail(LS_ERR_INVALID_ARG, "bad merge shape (parts %d, n_q %d, heads %d, dv %d)", n_parts,
+                n_q, n_heads, dv);
+  if (!group_begin || !group_end || n_groups <= 0)
+    return fail(LS_ERR_INVALID_ARG, "need at least one group");
+  if (n_groups > ls::kMaxMergeGroups)
+    return fail(LS_ERR_UNSUPPORTED, "%d groups in one merge (at most %d)", n_groups,
+                ls::kMaxMergeGroups);
+  for (int32_t k = 0; k < n_groups; ++k)
+    if (group_begin[k] < 0 || group_end[k] <= group_begin[k] || group_end[k] > n_parts)
+      return fail(LS_ERR_INVALID_ARG, "group %d [%d, %d) not a non-empty range in [0, %d)", k,
+                  group_begin[k], group_end[k], n_parts);
+  if (out_dtype != LS_BF16 && out_dtype != LS_F32)
+    return fail(LS_ERR_UNSUPPORTED, "out_dtype %d", out_dtype);
+  if (flags & ~LS_FLAG_BF16_NUMERATOR) return fail(LS_ERR_UNSUPPORTED, "merge flags 0x%x", flags);
+  if (dv % 4 != 0) return fail(LS_ERR_UNSUPPORTED, "merge needs dv %% 4 == 0 (got %d)", dv);
+  if (n_q == 0) return LS_OK;
+  for (const void* ptr : {(const void*)out_part, (const void*)lse_part, (const void*)group_out,
+                          (const void*)group_lse, (const void*)out, (const void*)lse}) {
+    if (!ptr) return fail(LS_ERR_INVALID_ARG, "NULL device pointer");
+    if (!aligned16(ptr))
+      return fail(LS_ERR_INVALID_ARG, "device pointers must be 16-byte aligned");
+  }
+  const size_t rows = (size_t)n_q * n_heads, elems = rows * dv;
+  std::vector<Range> ins{rng("out_part", out_part, elems * n_parts * 4),
+                         rng("lse_part", lse_part, rows * n_parts * 4)};
+  std::vector<Range> outs{rng("group_out", group_out, elems * n_groups * 4),
+                          rng("group_lse", group_lse, rows * n_groups * 4),
+                          rng("out", out, elems * (out_dtype == LS_BF16 ? 2 : 4)),
+                          rng("lse", lse, rows * 4)};
+  ls_status st = check_alias(outs, ins);
+  if (st != LS_OK) return st;
+  hipStream_t s = (hipStream_t)stream;
+  if (n_groups == 1) {
+    // the groups' results are outputs too: compose the group, then its one result
+    hipError_t e = ls::launch_merge(out_part, lse_part, group_begin, group_end, 1, n_q, n_heads,
+                                    dv, false, false, nullptr, nullptr, group_out, group_lse, s);
+    if (e != hipSuccess) return hip_fail(e, "merge launch");
+    return ls_lse_merge(group_out, group_lse, 1, n_q, n_heads, dv, out_dtype, out, lse, flags,
+                        stream);
+  }
+  hipError_t e = ls::launch_merge(out_part, lse_part, group_begin, group_end, n_groups, n_q,
+                                  n_heads, dv, out_dtype == LS_BF16,
+                                  (flags & LS_FLAG_BF16_NUMERATOR) != 0, group_out, group_lse, out,
+                                  lse, s);
   return e == hipSuccess ? LS_OK : hip_fail(e, "merge launch");
 }
 

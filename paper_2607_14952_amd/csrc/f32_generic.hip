@@ -33,8 +33,8 @@ __global__ __launch_bounds__(256) void fwd_f32_kernel(FwdArgs a) {
   const int row = (int)(pair / a.n_q_heads), head = (int)(pair - (int64_t)row * a.n_q_heads);
   const int g = head / a.group;   // any group size, not only powers of two
   const int sp = blockIdx.z;
-  const int64_t kb = a.split_begin[sp];
-  const int64_t ke = min(a.split_end[sp], a.q_pos0 + row + 1);
+  const int64_t kb = a.split_begin(sp);
+  const int64_t ke = min(a.split_end(sp), a.q_pos0 + row + 1);
   const float* q = static_cast<const float*>(a.q) + pair * a.head_dim;
   const float* kp = static_cast<const float*>(a.k_pool);
   const float* vp = static_cast<const float*>(a.v_pool);

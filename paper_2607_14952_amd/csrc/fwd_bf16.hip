@@ -308,7 +308,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void fwd_bf16_d256_kernel(FwdArgs a
   const bool row_ok = prow < rows_total;
   const int tok = prow >> lg;
   const int head = (g << lg) + (prow & ((1 << lg) - 1));
-  const int64_t kb = a.split_begin[sp], ke = a.split_end[sp];
+  const int64_t kb = a.split_begin(sp), ke = a.split_end(sp);
   const int tok_first = row0 >> lg;
   const int tok_last = min(a.n_q - 1, (row0 + kBM - 1) >> lg);
   const int64_t k_hi = min(ke, a.q_pos0 + tok_last + 1);   // keys of the WG: [kb, k_hi)

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) void fwd_f32_mfma_kernel(FwdArgs a) {
   const bool row_ok = prow < rows_total;
   const int tok = (int)(prow / G);
   const int head = g * G + (int)(prow - (int64_t)tok * G);
-  const int64_t kb = a.split_begin[sp], ke = a.split_end[sp];
+  const int64_t kb = a.split_begin(sp), ke = a.split_end(sp);
   const int tok_last = (int)(min(rows_total, row0 + 32 * kRW) - 1) / G;
   const int64_t k_hi = min(ke, a.q_pos0 + tok_last + 1);            // keys of the workgroup
   const int64_t my_lim = row_ok ? min(ke, a.q_pos0 + tok + 1) : kb;  // this row: [kb, my_lim)

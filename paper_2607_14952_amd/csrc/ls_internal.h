@@ -14,7 +14,10 @@ namespace ls {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr int kMaxSplitsPerLaunch = 128;   // split bounds travel in the kernel arguments (< 4 KiB)
+constexpr int kMaxMergeGroups = 64;        // groups of one merge call (kernel arguments)
+// Split bounds travel in the kernel arguments (< 4 KiB), as 32-bit offsets from
+// the launch's first key (64-bit bounds took a second launch from 129 splits on).
+constexpr int kMaxSplitsPerLaunch = 448;
 
 // Row chunks of the bf16 dk/dv kernel (partials in the backward workspace): up
 // to 16 chunks of at least 128 packed rows, so that the few key blocks of a
@@ -63,9 +66,12 @@ struct FwdArgs {
   int32_t log2_page;
   float scale_log2;         // softmax_scale * log2(e)
   int32_t n_splits;
-  int64_t split_begin[kMaxSplitsPerLaunch];
-  int64_t split_end[kMaxSplitsPerLaunch];
+  int64_t split_base, split_more;   // split_more: added to every end (a split past 32 bits)
+  uint32_t split_lo[kMaxSplitsPerLaunch], split_hi[kMaxSplitsPerLaunch];
+  __host__ __device__ int64_t split_begin(int i) const { return split_base + split_lo[i]; }
+  __host__ __device__ int64_t split_end(int i) const { return split_base + split_hi[i] + split_more; }
 };
+static_assert(sizeof(FwdArgs) <= 4096, "kernel arguments");
 
 // Backward over one key range [kv_begin, kv_end).
 struct BwdArgs {
@@ -149,9 +155,13 @@ hipError_t launch_scatter(void* k_pool, void* v_pool, const int32_t* page_table,
                           int64_t pos_begin, int64_t pos_end, int log2_page, int64_t k_row_elems,
                           int64_t v_row_elems, int esize, const void* k_src, const void* v_src,
                           hipStream_t stream);
-hipError_t launch_merge(const float* out_part, const float* lse_part, int n_splits, int n_q,
-                        int n_heads, int dv, bool out_bf16, bool bf16_numerator, void* out,
-                        float* lse, hipStream_t stream);
+// Parts begin[k] .. end[k] - 1 (host arrays, non-empty) compose group k; with
+// several groups their results go to group_out / group_lse and the groups
+// compose out / lse, in order.
+hipError_t launch_merge(const float* out_part, const float* lse_part, const int32_t* begin,
+                        const int32_t* end, int n_groups, int n_q, int n_heads, int dv,
+                        bool out_bf16, bool bf16_numerator, float* group_out, float* group_lse,
+                        void* out, float* lse, hipStream_t stream);
 hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t stream);
 // fp32 on the matrix cores, for the shapes f32_mfma_fits accepts (launch_fwd_f32
 // and launch_bwd_f32 take them for those and the generic kernels for the others)

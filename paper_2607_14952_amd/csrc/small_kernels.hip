@@ -3,6 +3,8 @@
 // read-only streaming probe that measures the HBM read ceiling.
 #include <math.h>
 
+#include <algorithm>
+
 #include "ls_internal.h"
 
 namespace ls {
@@ -67,78 +69,255 @@ __global__ __launch_bounds__(256) void scatter_kernel(char* __restrict__ k_pool,
 }
 
 // ---------------------------------------------------------------- merge
-// One thread per 4 output values of one (row, head).  Eq. qwen-lse-parts:
-// m = max l_r, a = sum e^(l_r - m), n = sum e^(l_r - m) o_r; o = n / a,
-// l = m + log a (computed with exp2/log2 and converted to natural log).
-// BF16_NUM: the production composition described after Eq. qwen-global-attn,
-// n reduced in bf16: each term e^(l_r - m) o_r is rounded to bf16 and added
-// in part order with the running sum rounded to bf16 after every addition
-// (m, a and l stay fp32).
+// Eq. qwen-lse-parts: m = max l_r, a = sum e^(l_r - m), n = sum e^(l_r - m) o_r;
+// o = n / a, l = m + log a (computed with exp2/log2 and converted to natural
+// log), over each group of parts and, with several groups, once more over the
+// groups' results in group order.
+// BF16_NUM (the last level only): the production composition described after
+// Eq. qwen-global-attn, n reduced in bf16: each term e^(l_r - m) o_r is rounded
+// to bf16 and added in part order with the running sum rounded to bf16 after
+// every addition (m, a and l stay fp32).
+//
+// An item is 4 output values of one (row, head).  Two kernels, both bound by
+// reading the parts once: the wide one gives an item one thread, the narrow one
+// sixteen waves of a workgroup that share its parts, for calls too small to
+// fill the chip with threads (launch_merge).
 __device__ __forceinline__ float round_bf16(float x) { return (float)(__bf16)x; }
 
-template <bool OUT_BF16, bool BF16_NUM>
-__global__ __launch_bounds__(256) void merge_kernel(const float* __restrict__ out_part,
-                                                    const float* __restrict__ lse_part,
-                                                    int n_splits, int n_q, int n_heads, int dv4,
-                                                    void* __restrict__ out,
-                                                    float* __restrict__ lse) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t rows = (int64_t)n_q * n_heads;
-  if (t >= rows * dv4) return;
-  const int64_t rh = t / dv4;               // row-major (row, head)
-  const int d4 = (int)(t - rh * dv4);
-  const int row = (int)(rh / n_heads), head = (int)(rh - (int64_t)row * n_heads);
-  const int64_t lse_off = (int64_t)head * n_q + row;
-  const int64_t part_lse = rows, part_out = rows * dv4 * 4;
+constexpr int kMU = 8;   // parts read at a time, so that their loads are in flight together
 
-  // parts are read kU at a time so that their loads are in flight together
-  constexpr int kU = 8;
-  float m = -INFINITY;
-  for (int s0 = 0; s0 < n_splits; s0 += kU) {
-    float l[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u)
-      l[u] = s0 + u < n_splits ? lse_part[(int64_t)(s0 + u) * part_lse + lse_off] : -INFINITY;
-#pragma unroll
-    for (int u = 0; u < kU; ++u) m = fmaxf(m, l[u]);
+struct MergeArgs {
+  const float* out_part;
+  const float* lse_part;
+  float* group_out;         // [n_groups, rows, dv] and [n_groups, heads, n_q]; null with one group
+  float* group_lse;
+  void* out;
+  float* lse;
+  int32_t n_q, n_heads, dv4, n_groups;
+  int32_t begin[kMaxMergeGroups], end[kMaxMergeGroups];   // parts of each group
+  int32_t per;              // narrow kernel: parts per unit
+};
+
+struct MergeItem {
+  int64_t t, rows, lse_off;   // item index, rows * heads, offset into an lse array
+  int d4;
+  __device__ __forceinline__ MergeItem(const MergeArgs& a, int64_t item) : t(item) {
+    rows = (int64_t)a.n_q * a.n_heads;
+    const int64_t rh = t / a.dv4;               // row-major (row, head)
+    d4 = (int)(t - rh * a.dv4);
+    const int row = (int)(rh / a.n_heads), head = (int)(rh - (int64_t)row * a.n_heads);
+    lse_off = (int64_t)head * a.n_q + row;
   }
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  float a = 0.f;
-  if (m != -INFINITY) {
-    const float m2 = m * kLog2e;
-    const f32x4* src = reinterpret_cast<const f32x4*>(out_part) + rh * dv4 + d4;
-    for (int s0 = 0; s0 < n_splits; s0 += kU) {
-      float l[kU];
-      f32x4 o[kU];
+};
+
+__device__ __forceinline__ float merged_lse(float m, float a) {
+  return m == -INFINITY ? -INFINITY : m + __builtin_amdgcn_logf(a) * kLn2;
+}
+
+template <bool BF16_NUM>
+__device__ __forceinline__ void add_part(float l, const f32x4& o, float m2, float& a, f32x4& acc) {
+  const float w = __builtin_amdgcn_exp2f(fmaf(l, kLog2e, -m2));   // 0 for l = -inf
+  a += w;
+  if (BF16_NUM) {
 #pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const bool in = s0 + u < n_splits;
-        l[u] = in ? lse_part[(int64_t)(s0 + u) * part_lse + lse_off] : -INFINITY;
-        o[u] = in ? src[(int64_t)(s0 + u) * (part_out / 4)] : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < 4; ++e) acc[e] = round_bf16(acc[e] + round_bf16(w * o[e]));
+  } else {
+    acc += w * o;
+  }
+}
+
+// Weighted sum over parts [p0, p1) of arrays out [., rows * dv] and lse
+// [., rows]: m, a and acc as above (acc = a = 0 where every part is empty).
+template <bool BF16_NUM>
+__device__ __forceinline__ void merge_parts(const float* out, const float* lse, int p0, int p1,
+                                            int dv4, const MergeItem& it, float& m, float& a,
+                                            f32x4& acc) {
+  const f32x4* src = reinterpret_cast<const f32x4*>(out) + it.t;
+  m = -INFINITY;
+  acc = f32x4{0.f, 0.f, 0.f, 0.f};
+  a = 0.f;
+  if (p1 - p0 <= kMU) {   // one batch: log-normalizers and values load together
+    float l[kMU];
+    f32x4 o[kMU];
+#pragma unroll
+    for (int u = 0; u < kMU; ++u) {
+      const int p = min(p0 + u, p1 - 1);
+      l[u] = lse[(int64_t)p * it.rows + it.lse_off];
+      o[u] = src[(int64_t)p * it.rows * dv4];
+    }
+#pragma unroll
+    for (int u = 0; u < kMU; ++u)
+      if (p0 + u < p1) m = fmaxf(m, l[u]);
+    if (m == -INFINITY) return;
+#pragma unroll
+    for (int u = 0; u < kMU; ++u) {
+      if (p0 + u < p1) add_part<BF16_NUM>(l[u], o[u], m * kLog2e, a, acc);
+    }
+    return;
+  }
+  for (int s0 = p0; s0 < p1; s0 += kMU) {
+    float l[kMU];
+#pragma unroll
+    for (int u = 0; u < kMU; ++u)
+      l[u] = s0 + u < p1 ? lse[(int64_t)(s0 + u) * it.rows + it.lse_off] : -INFINITY;
+#pragma unroll
+    for (int u = 0; u < kMU; ++u) m = fmaxf(m, l[u]);
+  }
+  if (m == -INFINITY) return;
+  const float m2 = m * kLog2e;
+  for (int s0 = p0; s0 < p1; s0 += kMU) {
+    float l[kMU];
+    f32x4 o[kMU];
+#pragma unroll
+    for (int u = 0; u < kMU; ++u) {
+      const bool in = s0 + u < p1;
+      l[u] = in ? lse[(int64_t)(s0 + u) * it.rows + it.lse_off] : -INFINITY;
+      o[u] = in ? src[(int64_t)(s0 + u) * it.rows * dv4] : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int u = 0; u < kMU; ++u) {
+      if (s0 + u >= p1) break;
+      add_part<BF16_NUM>(l[u], o[u], m2, a, acc);
+    }
+  }
+}
+
+template <bool OUT_BF16>
+__device__ __forceinline__ void store_item(void* out, int64_t t, const f32x4& v) {
+  if (OUT_BF16) {
+    bf16x4 r;
+    r[0] = (__bf16)v[0]; r[1] = (__bf16)v[1]; r[2] = (__bf16)v[2]; r[3] = (__bf16)v[3];
+    reinterpret_cast<bf16x4*>(out)[t] = r;
+  } else {
+    reinterpret_cast<f32x4*>(out)[t] = v;
+  }
+}
+
+// One thread per item.  The groups' results go to group_out / group_lse, from
+// where the thread reads its own values again for the last level.
+template <bool OUT_BF16, bool BF16_NUM>
+__global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const MergeItem it(g, t);
+  if (t >= it.rows * g.dv4) return;
+  const float* out = g.out_part;
+  const float* lse = g.lse_part;
+  int p0 = g.begin[0], p1 = g.end[0];
+  float m, a;
+  f32x4 acc;
+  if (g.n_groups > 1) {
+    for (int k = 0; k < g.n_groups; ++k) {
+      merge_parts<false>(out, lse, g.begin[k], g.end[k], g.dv4, it, m, a, acc);
+      if (m != -INFINITY) acc *= 1.0f / a;
+      reinterpret_cast<f32x4*>(g.group_out)[(int64_t)k * it.rows * g.dv4 + t] = acc;
+      // (every thread of the row writes the same value, which it reads back)
+      g.group_lse[(int64_t)k * it.rows + it.lse_off] = merged_lse(m, a);
+    }
+    out = g.group_out;
+    lse = g.group_lse;
+    p0 = 0;
+    p1 = g.n_groups;
+  }
+  merge_parts<BF16_NUM>(out, lse, p0, p1, g.dv4, it, m, a, acc);
+  if (m != -INFINITY) acc *= 1.0f / a;
+  store_item<OUT_BF16>(g.out, t, acc);
+  if (it.d4 == 0) g.lse[it.lse_off] = merged_lse(m, a);
+}
+
+// 64 items per workgroup of 16 waves.  The groups' parts are cut into units of
+// at most `per` parts (no more than kMergeUnits in all); waves take units in
+// turn and leave their sums in LDS, then take groups, then wave 0 composes
+// these.
+constexpr int kMergeUnits = 64;
+template <bool OUT_BF16, bool BF16_NUM>
+__global__ __launch_bounds__(1024) void merge_narrow_kernel(MergeArgs g) {
+  __shared__ f32x4 s_acc[kMergeUnits][64];
+  __shared__ float s_m[kMergeUnits][64], s_a[kMergeUnits][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t t = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t last = (int64_t)g.n_q * g.n_heads * g.dv4 - 1;
+  const MergeItem it(g, min(t, last));
+  float m, a;
+  f32x4 acc;
+  // units are numbered group by group: lane k holds group k's parts and units
+  const int gk = min(lane, g.n_groups - 1);
+  const int g_begin = g.begin[gk], g_end = g.end[gk];
+  const int g_units = lane < g.n_groups ? (g_end - g_begin + g.per - 1) / g.per : 0;
+  int g_last = g_units;   // one past the group's last unit
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(g_last, d);
+    if (lane >= d) g_last += o;
+  }
+  const int g_first = g_last - g_units;
+  const int n_units = __builtin_amdgcn_readlane(g_last, 63);
+  for (int u = w; u < n_units; u += 16) {
+    const int k = __popcll(__ballot(g_last <= u));
+    const int p = __builtin_amdgcn_readlane(g_begin, k) +
+                  (u - __builtin_amdgcn_readlane(g_first, k)) * g.per;
+    merge_parts<false>(g.out_part, g.lse_part, p,
+                       min(p + g.per, __builtin_amdgcn_readlane(g_end, k)), g.dv4, it, m, a, acc);
+    s_acc[u][lane] = acc;
+    s_m[u][lane] = m;
+    s_a[u][lane] = a;
+  }
+  __syncthreads();
+  // group k's result replaces its first unit (only the group's wave reads its units)
+  for (int k = w; k < g.n_groups; k += 16) {
+    const int u0 = __builtin_amdgcn_readlane(g_first, k), u1 = __builtin_amdgcn_readlane(g_last, k);
+    m = -INFINITY;
+    for (int v = u0; v < u1; ++v) m = fmaxf(m, s_m[v][lane]);
+    acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    a = 0.f;
+    if (m != -INFINITY) {
+      for (int v = u0; v < u1; ++v) {
+        const float x = __builtin_amdgcn_exp2f((s_m[v][lane] - m) * kLog2e);
+        a = fmaf(x, s_a[v][lane], a);
+        acc += x * s_acc[v][lane];
       }
+      acc *= 1.0f / a;
+    }
+    const float l = merged_lse(m, a);
+    if (g.n_groups == 1) {
+      if (t <= last) {
+        store_item<OUT_BF16>(g.out, t, acc);
+        if (it.d4 == 0) g.lse[it.lse_off] = l;
+      }
+    } else {
+      s_acc[u0][lane] = acc;
+      s_m[u0][lane] = l;
+      if (t <= last) {
+        reinterpret_cast<f32x4*>(g.group_out)[(int64_t)k * it.rows * g.dv4 + t] = acc;
+        if (it.d4 == 0) g.group_lse[(int64_t)k * it.rows + it.lse_off] = l;
+      }
+    }
+  }
+  if (g.n_groups == 1) return;
+  __syncthreads();
+  if (w > 0) return;
+  m = -INFINITY;
+  for (int k = 0; k < g.n_groups; ++k)
+    m = fmaxf(m, s_m[__builtin_amdgcn_readlane(g_first, k)][lane]);
+  acc = f32x4{0.f, 0.f, 0.f, 0.f};
+  a = 0.f;
+  if (m != -INFINITY) {
+    for (int k = 0; k < g.n_groups; ++k) {
+      const int u = __builtin_amdgcn_readlane(g_first, k);
+      const float x = __builtin_amdgcn_exp2f((s_m[u][lane] - m) * kLog2e);
+      a += x;
+      const f32x4 o = s_acc[u][lane];
+      if (BF16_NUM) {
 #pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        if (s0 + u >= n_splits) break;
-        const float w = __builtin_amdgcn_exp2f(fmaf(l[u], kLog2e, -m2));   // 0 for l = -inf
-        a += w;
-        if (BF16_NUM) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[e] = round_bf16(acc[e] + round_bf16(w * o[u][e]));
-        } else {
-          acc += w * o[u];
-        }
+        for (int e = 0; e < 4; ++e) acc[e] = round_bf16(acc[e] + round_bf16(x * o[e]));
+      } else {
+        acc += x * o;
       }
     }
     acc *= 1.0f / a;
   }
-  if (OUT_BF16) {
-    bf16x4 r;
-    r[0] = (__bf16)acc[0]; r[1] = (__bf16)acc[1]; r[2] = (__bf16)acc[2]; r[3] = (__bf16)acc[3];
-    reinterpret_cast<bf16x4*>(out)[t] = r;
-  } else {
-    reinterpret_cast<f32x4*>(out)[t] = acc;
-  }
-  if (d4 == 0) lse[lse_off] = (m == -INFINITY) ? -INFINITY : m + __builtin_amdgcn_logf(a) * kLn2;
+  if (t > last) return;
+  store_item<OUT_BF16>(g.out, t, acc);
+  if (it.d4 == 0) g.lse[it.lse_off] = merged_lse(m, a);
 }
 
 // ---------------------------------------------------------------- bwd prep
@@ -283,19 +462,60 @@ hipError_t launch_scatter(void* k_pool, void* v_pool, const int32_t* page_table,
   return hipGetLastError();
 }
 
-hipError_t launch_merge(const float* out_part, const float* lse_part, int n_splits, int n_q,
-                        int n_heads, int dv, bool out_bf16, bool bf16_numerator, void* out,
-                        float* lse, hipStream_t stream) {
-  const int dv4 = dv / 4;
-  const int64_t threads = (int64_t)n_q * n_heads * dv4;
-  const unsigned blocks = (unsigned)((threads + 255) / 256);
-#define LS_MERGE(OB, BN)                                                                  \
-  hipLaunchKernelGGL((merge_kernel<OB, BN>), dim3(blocks), dim3(256), 0, stream, out_part, \
-                     lse_part, n_splits, n_q, n_heads, dv4, out, lse)
-  if (out_bf16 && bf16_numerator) LS_MERGE(true, true);
-  else if (out_bf16) LS_MERGE(true, false);
-  else if (bf16_numerator) LS_MERGE(false, true);
-  else LS_MERGE(false, false);
+hipError_t launch_merge(const float* out_part, const float* lse_part, const int32_t* begin,
+                        const int32_t* end, int n_groups, int n_q, int n_heads, int dv,
+                        bool out_bf16, bool bf16_numerator, float* group_out, float* group_lse,
+                        void* out, float* lse, hipStream_t stream) {
+  MergeArgs g = {};
+  g.out_part = out_part;
+  g.lse_part = lse_part;
+  g.group_out = group_out;
+  g.group_lse = group_lse;
+  g.out = out;
+  g.lse = lse;
+  g.n_q = n_q;
+  g.n_heads = n_heads;
+  g.dv4 = dv / 4;
+  g.n_groups = n_groups;
+  int most = 0;
+  for (int k = 0; k < n_groups; ++k) {
+    g.begin[k] = begin[k];
+    g.end[k] = end[k];
+    most = std::max(most, end[k] - begin[k]);
+  }
+  const int64_t items = (int64_t)n_q * n_heads * g.dv4;
+  // The narrow kernel: where one thread per item leaves under two waves per
+  // SIMD and the parts are more than one batch of loads (16 rows x 16 heads,
+  // 257 parts in 9 groups: 79 us in ten launches of one thread per item, 17 us
+  // here; 1 row, 65 parts: 37 us in ten launches, 7 us here with 129 parts).  A single group's bf16 numerator is added in
+  // part order, which one thread does.
+  const bool narrow = items <= 512 * 64 && (most > kMU || n_groups > 1) &&
+                      !(bf16_numerator && n_groups == 1);
+  if (narrow) {
+    auto units = [&](int per) {
+      int n = 0;
+      for (int k = 0; k < n_groups; ++k) n += (end[k] - begin[k] + per - 1) / per;
+      return n;
+    };
+    g.per = kMU;
+    while (units(g.per) > kMergeUnits) g.per += kMU;   // (n_groups <= kMergeUnits)
+  }
+#define LS_MERGE(OB, BN)                                                                       \
+  if (narrow)                                                                                  \
+    hipLaunchKernelGGL((merge_narrow_kernel<OB, BN>), dim3((unsigned)((items + 63) / 64)),     \
+                       dim3(1024), 0, stream, g);                                              \
+  else                                                                                         \
+    hipLaunchKernelGGL((merge_kernel<OB, BN>), dim3((unsigned)((items + 255) / 256)), dim3(256), \
+                       0, stream, g)
+  if (out_bf16 && bf16_numerator) {
+    LS_MERGE(true, true);
+  } else if (out_bf16) {
+    LS_MERGE(true, false);
+  } else if (bf16_numerator) {
+    LS_MERGE(false, true);
+  } else {
+    LS_MERGE(false, false);
+  }
 #undef LS_MERGE
   return hipGetLastError();
 }

@@ -1,10 +1,10 @@
 """One response-replay step over a paged prefix, composed from the library calls.
 
 forward  : every split's local (o_r, l_r)        -> ls_prefix_attn_fwd (one launch)
-           splits of a shard -> shard (o_s, l_s)  -> ls_lse_merge (fp32)
-           shards + response -> global (o, l)     -> ls_lse_merge (q dtype; with
-           bf16_numerator the numerator is reduced in bf16, as the production
-           composition noted after Eq. qwen-global-attn)
+           splits of a shard -> shard (o_s, l_s)  -> ls_lse_merge_groups (one launch;
+           shards + response -> global (o, l)        fp32 per shard, q dtype for the
+           result; with bf16_numerator the last numerator is reduced in bf16, as
+           the production composition noted after Eq. qwen-global-attn)
            (the single-GPU form of the cross-rank merge, Eq. qwen-lse-parts and
            Eq. qwen-global-attn)
 backward : per shard key range, dq accumulated in shard order (Eq. qwen-dq-reduce);
@@ -12,12 +12,12 @@ backward : per shard key range, dq accumulated in shard order (Eq. qwen-dq-reduc
            prefix keys get none).
 
 Shards own contiguous prefix ranges, or, with ``ownership="cyclic"``, the pages
-p with p mod n_shards = c (Eq. qwen-page-owner).  A cyclic shard gets a page
-table of its own whose first entries are its owned pages in order, so its keys
-form one range 0 .. shard_len - 1 of that table, and it takes one forward launch
-and one backward call.  Renumbering is exact here because every prefix position
-precedes every query row, so each prefix key is visible to each row whatever
-its position; the response split keeps the global table and coordinates.
+p with p mod n_shards = c (Eq. qwen-page-owner).  A cyclic step reads the store
+through a table of its own that names the prefix pages shard by shard, so that
+each shard's keys form one range of it.  Renumbering is exact here because every
+prefix position precedes every query row, so each prefix key is visible to each
+row whatever its position; the shard that owns a partly filled last page comes
+last, which keeps that page in its place before the response's positions.
 """
 from __future__ import annotations
 
@@ -42,6 +42,72 @@ def device_inputs(host: dict, device="cuda") -> dict:
     return out
 
 
+def cyclic_shards(cfg):
+    """Cyclic ownership: the ranges of the shards that own positions (in shard
+    order, then the response's) in a table that names the prefix pages shard by
+    shard, and that table's prefix pages (logical page numbers, in table order).
+    A partly filled last page stays last, so the shard that owns it comes last
+    in the table."""
+    owners = [c for c in range(cfg.n_shards) if cfg.shard_len(c)]
+    last = (cfg.n_prefix_pages - 1) % cfg.n_shards
+    in_table = owners
+    if cfg.prefix_len % cfg.page_size:
+        in_table = [c for c in owners if c != last] + [last]
+    start, order = {}, []
+    for c in in_table:
+        start[c] = len(order) * cfg.page_size
+        order += cfg.shard_pages(c)
+    shards = [(start[c], start[c] + cfg.shard_len(c)) for c in owners]
+    return shards + [(cfg.prefix_len, cfg.kv_len)], order
+
+
+_CUS = 256
+
+
+def fine_splits(cfg, splits):
+    """The shards' splits (lists of key ranges, the response's list last), each cut
+    into the number of equal pieces that makes the forward and merge shortest.
+
+    A workgroup takes 32-key tiles of one split for 256 packed query rows (128
+    where there are no more, and in the fp32 kernels) and one runs per CU, so a
+    launch takes ceil(workgroups / 256) rounds of a split's tiles plus about 6
+    for its start and end, and one more short round where the response's
+    workgroups find no idle CU.  Each further part is written and read once
+    more: 0.41 ns per KiB row (1,111 rows, 33 -> 65 parts: +241 us), against
+    1.6 us (0.95 us) for a tile of 256 (128) rows.  Measured, whole -> cut: 1 row
+    x 131,075 keys in 64 splits 72 -> 64 us (2 pieces), 16 rows x 262,144 keys
+    in 32 splits 248 -> 137 us (4), 150 rows x 1M 3,071 -> 2,276 us (4).  77 rows
+    x 262,144 (198 workgroups) gain nothing (421, 434, 430 us for 1, 2, 4), so a
+    cut must promise 8%; 4,096 rows fill 33 rounds and stay whole."""
+    rows = cfg.resp_len * cfg.group
+    per_wg = 256 if cfg.dtype == "bf16" and cfg.page_size >= 32 and rows > 128 else 128
+    prefix = [r for sp in splits[:-1] for r in sp]
+    if not prefix:
+        return splits
+    own = -(-rows // per_wg) * cfg.n_kv_heads   # workgroups of one split
+    tiles = -(-max(e - b for b, e in prefix) // 32)
+    tile_ns = 1600 if per_wg == 256 else 950
+    part = 0.41 / tile_ns * cfg.resp_len * cfg.n_q_heads * cfg.head_dim_v / 256 * len(prefix)
+
+    def cost(f):
+        wgs = own * len(prefix) * f
+        rounds = -(-wgs // _CUS)
+        late = 6 + min(tiles, -(-cfg.resp_len // 32)) if rounds * _CUS - wgs < own else 0
+        return rounds * (-(-tiles // f) + 6) + late + part * f
+
+    most = max(1, min(16, tiles // 8, 1024 // len(prefix)))
+    f = min(range(1, most + 1), key=cost)
+    if cost(f) > 0.92 * cost(1):
+        return splits
+
+    def cut(b, e):
+        lo = b // 32 * 32   # pieces begin with a tile
+        step = -(-(e - lo) // (32 * f)) * 32
+        return [(max(b, x), min(e, x + step)) for x in range(lo, e, step)]
+
+    return [[p for r in sp for p in cut(*r)] for sp in splits[:-1]] + splits[-1:]
+
+
 class ReplayStep:
     """Buffers and call sequence of one fwd(+bwd) replay over a config's shards."""
 
@@ -54,30 +120,26 @@ class ReplayStep:
         self.stream = stream
         q = dev["q"]
         R, Hq, D, Dv = cfg.resp_len, cfg.n_q_heads, cfg.head_dim, cfg.head_dim_v
-        self.cyclic = cfg.ownership == "cyclic"
-        if self.cyclic:
-            # per shard: its own PagedKV (owned pages first) and its virtual ranges;
-            # the response shard keeps the global table
+        if cfg.ownership == "cyclic":
+            self.shards, order = cyclic_shards(cfg)
             table = dev["page_table"].cpu().numpy()
-            self.shard_kv, self.shard_splits, self.shards = [], [], []
-            for c in range(cfg.n_shards):
-                n = cfg.shard_len(c)
-                if n == 0:
-                    continue
-                t = table.copy()
-                pages = cfg.shard_pages(c)
-                t[:len(pages)] = table[pages]
-                self.shard_kv.append(B.PagedKV(dev["k_pool"], dev["v_pool"],
-                                               torch.from_numpy(t).to(q.device)))
-                self.shard_splits.append(cfg.virtual_splits(c))
-                self.shards.append((0, n))
-            self.shard_kv.append(self.kv)
-            self.shard_splits.append([(cfg.prefix_len, cfg.kv_len)])
-            self.shards.append((cfg.prefix_len, cfg.kv_len))
-            self.splits = [r for sp in self.shard_splits for r in sp]
+            t = table.copy()
+            t[:len(order)] = table[order]
+            self.kv = B.PagedKV(dev["k_pool"], dev["v_pool"], torch.from_numpy(t).to(q.device))
+            splits = [[(b + i, b + j) for i, j in cfg.virtual_splits(c)]
+                      for c, (b, _) in zip((c for c in range(cfg.n_shards) if cfg.shard_len(c)),
+                                           self.shards)]
+            splits.append([(cfg.prefix_len, cfg.kv_len)])
         else:
-            self.splits = [r for r in cfg.splits() if r[0] < r[1]]
             self.shards = [r for r in cfg.shard_ranges() if r[0] < r[1]]
+            every = [r for r in cfg.splits() if r[0] < r[1]]
+            splits = [[r for r in every if b <= r[0] and r[1] <= e] for b, e in self.shards]
+            assert sum(map(len, splits)) == len(every)
+        splits = fine_splits(cfg, splits)
+        # launch order is key order; the splits of shard s are parts groups[s] of it
+        self.splits = sorted(r for sp in splits for r in sp)
+        at = [self.splits.index(sp[0]) for sp in splits]
+        self.groups = [(i, i + len(sp)) for i, sp in zip(at, splits)]
         kw = dict(dtype=torch.float32, device=q.device)
         self.out_part = torch.empty((len(self.splits), R, Hq, Dv), **kw)
         self.lse_part = torch.empty((len(self.splits), Hq, R), **kw)
@@ -85,21 +147,6 @@ class ReplayStep:
         self.shard_lse = torch.empty((len(self.shards), Hq, R), **kw)
         self.out = torch.empty((R, Hq, Dv), dtype=q.dtype, device=q.device)
         self.lse = torch.empty((Hq, R), **kw)
-        # which splits belong to which shard (splits are listed shard by shard)
-        self.groups = []
-        i = 0
-        if self.cyclic:
-            for sp in self.shard_splits:
-                self.groups.append((i, i + len(sp)))
-                i += len(sp)
-        else:
-            for b, e in self.shards:
-                j = i
-                while j < len(self.splits) and self.splits[j][1] <= e:
-                    j += 1
-                self.groups.append((i, j))
-                i = j
-        assert i == len(self.splits)
         if self.backward_enabled:
             self.dq = torch.empty((R, Hq, D), **kw)
             self.dk = torch.zeros((cfg.kv_len - cfg.prefix_len, cfg.n_kv_heads, D), **kw)
@@ -107,24 +154,24 @@ class ReplayStep:
             self.ws = B.bwd_workspace(q, self.kv, prefix_len=cfg.prefix_len, q_pos0=cfg.q_pos0)
 
     def forward_splits(self):
-        """Local (o_r, l_r) of every split: one launch (one per shard when cyclic)."""
+        """Local (o_r, l_r) of every split, in one launch."""
         c = self.cfg
-        kw = dict(prefix_len=c.prefix_len, q_pos0=c.q_pos0, scale=c.scale, stream=self.stream)
-        if not self.cyclic:
-            B.prefix_attn_fwd(self.dev["q"], self.kv, self.splits, out_part=self.out_part,
-                              lse_part=self.lse_part, **kw)
-            return
-        for s, (i, j) in enumerate(self.groups):
-            B.prefix_attn_fwd(self.dev["q"], self.shard_kv[s], self.shard_splits[s],
-                              out_part=self.out_part[i:j], lse_part=self.lse_part[i:j], **kw)
+        B.prefix_attn_fwd(self.dev["q"], self.kv, self.splits, prefix_len=c.prefix_len,
+                          q_pos0=c.q_pos0, scale=c.scale, out_part=self.out_part,
+                          lse_part=self.lse_part, stream=self.stream)
 
     def merge(self):
         """Splits -> per-shard results (fp32) -> global result (q dtype)."""
+        flags = B.FLAG_BF16_NUMERATOR if self.cfg.bf16_numerator else 0
+        if len(self.groups) <= B.MAX_MERGE_GROUPS:
+            B.lse_merge_groups(self.out_part, self.lse_part, self.groups, group_out=self.shard_out,
+                               group_lse=self.shard_lse, out=self.out, lse=self.lse, flags=flags,
+                               stream=self.stream)
+            return
         for s, (i, j) in enumerate(self.groups):
             B.lse_merge(self.out_part[i:j], self.lse_part[i:j], out=self.shard_out[s],
                         lse=self.shard_lse[s], stream=self.stream)
-        B.lse_merge(self.shard_out, self.shard_lse, out=self.out, lse=self.lse,
-                    flags=B.FLAG_BF16_NUMERATOR if self.cfg.bf16_numerator else 0,
+        B.lse_merge(self.shard_out, self.shard_lse, out=self.out, lse=self.lse, flags=flags,
                     stream=self.stream)
 
     def forward(self):
@@ -139,8 +186,7 @@ class ReplayStep:
         workspace, so ranges must run in order, starting at 0."""
         c = self.cfg
         b, e = self.shards[r]
-        kv = self.shard_kv[r] if self.cyclic else self.kv
-        B.prefix_attn_bwd(self.dev["q"], kv, self.dev["d_out"], self.out, self.lse,
+        B.prefix_attn_bwd(self.dev["q"], self.kv, self.dev["d_out"], self.out, self.lse,
                           prefix_len=c.prefix_len, q_pos0=c.q_pos0, scale=c.scale,
                           kv_begin=b, kv_end=e,
                           flags=(B.FLAG_ACCUMULATE_DQ | B.FLAG_PREP_READY) if r > 0 else 0,

@@ -70,3 +70,51 @@ def _bf16(name, prefix, resp, hq=16, hkv=2, page=256, shards=1, splits=2, **kw):
 ], ids=lambda c: c.name)
 def test_bf16_shapes(cfg):
     full_case(cfg)
+
+
+@pytest.mark.parametrize("flag", [0, B.FLAG_BF16_NUMERATOR], ids=["f32num", "bf16num"])
+@pytest.mark.parametrize("R,H,Dv,groups", [
+    # the narrow kernel (16 waves share an item's parts): one row; units of more
+    # than 8 parts; groups of one part and of many, out of order; items that do
+    # not fill a workgroup
+    (1, 2, 64, [(0, 3), (3, 4)]),
+    (2, 3, 20, [(200, 201), (0, 200), (201, 209)]),
+    (16, 16, 256, [(32 * i, 32 * i + 32) for i in range(8)] + [(256, 257)]),
+    # the most groups; one group; past the narrow kernel's largest call
+    (3, 4, 32, [(i, i + 1) for i in range(64)]),
+    (5, 4, 64, [(0, 21)]),
+    (520, 1, 256, [(0, 5), (5, 14)]),
+], ids=["row", "ragged", "r16", "g64", "one_group", "wide"])
+def test_merge_groups(R, H, Dv, groups, flag):
+    """Both levels in one launch against the oracle's merge of each group and of
+    the groups' results; rows and groups with no key at all included."""
+    import numpy as np
+    import torch
+
+    import oracle as O
+    from paper_2607_14952_amd import inputs
+    from tests._gpu import host, lse_err, rel_l2
+    n = max(e for _, e in groups)
+    o, lse = inputs.merge_parts(77 + n, n, R, H, Dv)
+    b0, e0 = groups[0]
+    lse[b0:e0, 0, 0] = -np.inf          # a whole group empty for one row
+    o[b0:e0, 0, 0] = 0.0
+    f32 = dict(dtype=torch.float32, device="cuda")
+    go, gl = torch.full((len(groups), R, H, Dv), 7.0, **f32), torch.full((len(groups), H, R), 7.0, **f32)
+    out, l = torch.empty((R, H, Dv), **f32), torch.empty((H, R), **f32)
+    B.lse_merge_groups(torch.from_numpy(o).cuda(), torch.from_numpy(lse).cuda(), groups,
+                       group_out=go, group_lse=gl, out=out, lse=l, flags=flag)
+    torch.cuda.synchronize()
+    parts = [O.lse_merge(list(o[b:e]), list(lse[b:e])) for b, e in groups]
+    for k, (ro, rl) in enumerate(parts):
+        assert rel_l2(host(go[k]), ro) <= 1e-6 and lse_err(host(gl[k]), rl) <= 1e-5
+    want, want_l = O.lse_merge([p[0] for p in parts], [p[1] for p in parts])
+    assert lse_err(host(l), want_l) <= 1e-5
+    # bf16 numerator: each of the additions rounds to bf16 (2^-9 of the running
+    # sum, and of the term); the norm over the elements stays under their sum
+    bar = (len(groups) + 1) * 2.0 ** -9 if flag else 1e-6
+    assert rel_l2(host(out), want) <= bar
+    if flag:   # and the same bits as the two-step composition
+        two, _ = B.lse_merge(go, gl, out_dtype=torch.float32, flags=flag)
+        close = np.abs(host(two) - host(out)) <= 1e-6 * (np.abs(host(two)) + 1e-30)
+        assert close.mean() >= 0.99
