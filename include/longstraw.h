@@ -247,8 +247,11 @@ ls_status ls_prefix_attn_bwd(const ls_attn_params* p, int64_t kv_begin, int64_t 
  * returns the composed result directly (out and lse over the union) rather
  * than one partial per part: the parts would only be merged again.  The
  * workspace (size from ls_sparse_attn_workspace_size with backward = 0 or 1)
- * holds each token's resolved key list and, for the backward, Delta, lse *
- * log2(e) and dS; its contents need not survive between calls.
+ * holds each token's resolved key list, for the backward Delta and lse *
+ * log2(e), and where tokens are few the partial results of the key chunks that
+ * each list is cut into; its contents need not survive between calls.  One
+ * made for more tokens also serves fewer: without room for the partial results
+ * (up to 64 MiB) a call works in one chunk, with other rounding.
  */
 size_t ls_sparse_attn_workspace_size(const ls_attn_params* p, int32_t topk, int32_t backward);
 

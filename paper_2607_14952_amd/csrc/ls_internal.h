@@ -145,8 +145,10 @@ struct SparseArgs {
 
 // Launchers (return the hipError_t of the launch).
 hipError_t launch_sparse_phys(const SparseArgs& a, hipStream_t stream);
-hipError_t launch_sparse_fwd(const SparseArgs& a, hipStream_t stream);
-hipError_t launch_sparse_bwd(const SparseArgs& a, hipStream_t stream);
+// n_chunks > 1: a.out / a.lse ([chunks, ...]) or a.dq ([chunks, n_q, H, 576]) hold
+// the partial results of each token's key chunks
+hipError_t launch_sparse_fwd(const SparseArgs& a, int n_chunks, hipStream_t stream);
+hipError_t launch_sparse_bwd(const SparseArgs& a, int n_chunks, hipStream_t stream);
 hipError_t launch_gather(const void* k_pool, const void* v_pool, const int32_t* page_table,
                          int64_t pos_begin, int64_t pos_end, int log2_page, int64_t k_row_elems,
                          int64_t v_row_elems, int esize, void* k_out, void* v_out,
@@ -168,8 +170,13 @@ hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t stream);
 hipError_t launch_fwd_f32_mfma(const FwdArgs& a, hipStream_t stream);
 // dq over the range and dk/dv of its keys from key0 on (none when key0 >= kv_end)
 hipError_t launch_bwd_f32_mfma(const BwdArgs& a, bool need_dq, int64_t key0, hipStream_t stream);
-// dq (+)= scale * the sum of a.dq_part's n_chunks partials, in order
-hipError_t launch_dq_reduce(const BwdArgs& a, int n_chunks, hipStream_t stream);
+// dq (+)= scale * the sum of n_chunks partials of n values (a multiple of 4), in order
+hipError_t launch_dq_reduce(const float* part, int n_chunks, int64_t n, float scale,
+                            bool accumulate, float* dq, hipStream_t stream);
+inline hipError_t launch_dq_reduce(const BwdArgs& a, int n_chunks, hipStream_t stream) {
+  return launch_dq_reduce(a.dq_part, n_chunks, (int64_t)a.n_q * a.n_q_heads * a.head_dim, a.scale,
+                          a.accumulate_dq != 0, a.dq, stream);
+}
 hipError_t launch_hbm_read(const void* buf, int64_t n16, uint32_t* out, hipStream_t stream);
 hipError_t launch_dsa_scores(const DsaArgs& a, hipStream_t stream);
 hipError_t launch_topk(const TopkArgs& a, hipStream_t stream);

@@ -551,11 +551,11 @@ hipError_t launch_bwd_prep(const void* d_out, const void* out, bool dout_bf16, b
   return hipGetLastError();
 }
 
-hipError_t launch_dq_reduce(const BwdArgs& a, int n_chunks, hipStream_t stream) {
-  const int64_t n4 = (int64_t)a.n_q * a.n_q_heads * a.head_dim / 4;
+hipError_t launch_dq_reduce(const float* part, int n_chunks, int64_t n, float scale,
+                            bool accumulate, float* dq, hipStream_t stream) {
+  const int64_t n4 = n / 4;
   hipLaunchKernelGGL(dq_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream,
-                     (const f32x4*)a.dq_part, n4, n_chunks, a.scale, a.accumulate_dq,
-                     (f32x4*)a.dq);
+                     (const f32x4*)part, n4, n_chunks, scale, accumulate ? 1 : 0, (f32x4*)dq);
   return hipGetLastError();
 }
 

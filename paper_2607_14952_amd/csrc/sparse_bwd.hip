@@ -102,6 +102,7 @@ __device__ __forceinline__ void fused_step(const SparseArgs& a, char* __restrict
   dsb = (g & 1) ? pack_halves(hi, lo) : pack_halves(lo, hi);
 }
 
+template <bool kChunks>
 __global__ __launch_bounds__(256, 1) void sparse_bwd_kernel(SparseArgs a) {
   constexpr int kSl = kPSlots;
   __shared__ __attribute__((aligned(1024))) char smem[kSl * kTile];
@@ -115,7 +116,16 @@ __global__ __launch_bounds__(256, 1) void sparse_bwd_kernel(SparseArgs a) {
   const int t = a.n_q - 1 - tk;
   const int head = (int)blockIdx.y * 128 + 64 * half + 16 * w + c;
   const int n_t = a.ntok[t];
-  const int n_tiles = (n_t + kKeys - 1) / kKeys;
+  // chunk z of the token's tiles (sparse_fwd.hip); with several chunks a.dq holds
+  // their partial sums, which are added afterwards
+  const int z = kChunks ? (int)blockIdx.z : 0;
+  const int T0 = chunk_begin<kChunks>(n_t, z), n_tiles = chunk_begin<kChunks>(n_t, z + 1);
+  float* dq = a.dq + (((int64_t)z * a.n_q + t) * a.n_heads + head) * kDk + 4 * g;
+  if (kChunks && T0 >= n_tiles) {   // fewer tiles than chunks (a.accumulate_dq is off: there are several)
+#pragma unroll
+    for (int db = 0; db < 36; ++db) *reinterpret_cast<f32x4*>(dq + 16 * db) = zero4();
+    return;
+  }
   const __amdgpu_buffer_rsrc_t phys_t = phys_rsrc(a, t);
   const __amdgpu_buffer_rsrc_t pool = pool_rsrc(a.latent);
   auto clamp = [&](int T) { return T < n_tiles ? T : n_tiles - 1; };
@@ -125,8 +135,8 @@ __global__ __launch_bounds__(256, 1) void sparse_bwd_kernel(SparseArgs a) {
   f.init(lane, w);
   const BOffsets bo = b_offsets(lane);
   // the row lists of the first three tiles load before any tile does
-  const int32_t r0 = fr.rows_of(phys_t, 0, lane), r1 = fr.rows_of(phys_t, clamp(1), lane);
-  int32_t pr = fr.rows_of(phys_t, clamp(2), lane), pn;
+  const int32_t r0 = fr.rows_of(phys_t, T0, lane), r1 = fr.rows_of(phys_t, clamp(T0 + 1), lane);
+  int32_t pr = fr.rows_of(phys_t, clamp(T0 + 2), lane), pn;
 #pragma unroll
   for (int i = 0; i < 9; ++i) f.issue_one(smem, pool, r0, w, i, lane);
 #pragma unroll
@@ -151,20 +161,21 @@ __global__ __launch_bounds__(256, 1) void sparse_bwd_kernel(SparseArgs a) {
   tile_barrier();
 
   bf16x8 dsb;
-  pn = fr.rows_of(phys_t, clamp(3), lane);
+  pn = fr.rows_of(phys_t, clamp(T0 + 3), lane);
   __builtin_amdgcn_sched_barrier(0);   // the row list loads ahead of this stage's direct loads
-  fused_step<true>(a, smem + 2 * kTile, smem, smem, f, pool, pr, w, lane, qreg, dreg, bo, 0, n_t, g,
-                   lse2, delta, acc, dsb);
+  fused_step<true>(a, smem + 2 * kTile, smem, smem, f, pool, pr, w, lane, qreg, dreg, bo, T0, n_t,
+                   g, lse2, delta, acc, dsb);
   pr = pn;
   // vmcnt(9): only this iteration's stage in flight; lgkmcnt(0): the step's
   // LDS reads have landed (the next stage refills the slot of the tile before)
   __builtin_amdgcn_s_waitcnt(0x0079);
   tile_barrier();
-  for (int T = 1; T < n_tiles; ++T) {
+  for (int T = T0 + 1; T < n_tiles; ++T) {
+    const int i = T - T0;
     pn = fr.rows_of(phys_t, clamp(T + 3), lane);
     __builtin_amdgcn_sched_barrier(0);
-    fused_step<false>(a, smem + ((T + 2) % kSl) * kTile, smem + (T % kSl) * kTile,
-                      smem + ((T + kSl - 1) % kSl) * kTile, f, pool, pr, w, lane, qreg, dreg, bo, T,
+    fused_step<false>(a, smem + ((i + 2) % kSl) * kTile, smem + (i % kSl) * kTile,
+                      smem + ((i + kSl - 1) % kSl) * kTile, f, pool, pr, w, lane, qreg, dreg, bo, T,
                       n_t, g, lse2, delta, acc, dsb);
     pr = pn;
     __builtin_amdgcn_s_waitcnt(0x0079);
@@ -172,12 +183,11 @@ __global__ __launch_bounds__(256, 1) void sparse_bwd_kernel(SparseArgs a) {
   }
   wait_fetch();   // no direct load is left in flight (the last tile's slot was never a target)
   // the last tile's dq product
-  const char* last = smem + ((n_tiles - 1) % kSl) * kTile;
+  const char* last = smem + ((n_tiles - 1 - T0) % kSl) * kTile;
 #pragma unroll
   for (int db = 0; db < 36; ++db) acc[db] = mfma16(b_col8(last, bo, db), dsb, acc[db]);
 
   // dq^T block db: channels 16 db + 4 g + {0..3} of head c
-  float* dq = a.dq + ((int64_t)t * a.n_heads + head) * kDk + 4 * g;
 #pragma unroll
   for (int db = 0; db < 36; ++db) {
     f32x4* dst = reinterpret_cast<f32x4*>(dq + 16 * db);
@@ -189,10 +199,13 @@ __global__ __launch_bounds__(256, 1) void sparse_bwd_kernel(SparseArgs a) {
 
 }  // namespace
 
-hipError_t launch_sparse_bwd(const SparseArgs& a, hipStream_t stream) {
+hipError_t launch_sparse_bwd(const SparseArgs& a, int n_chunks, hipStream_t stream) {
   const unsigned tokens8 = (unsigned)((a.n_q + 7) / 8 * 8);
-  hipLaunchKernelGGL(sparse_bwd_kernel, dim3(2 * tokens8, a.n_heads / 128), dim3(256), 0, stream,
-                     a);
+  const dim3 grid(2 * tokens8, a.n_heads / 128, n_chunks);
+  if (n_chunks > 1)
+    hipLaunchKernelGGL(sparse_bwd_kernel<true>, grid, dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL(sparse_bwd_kernel<false>, grid, dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

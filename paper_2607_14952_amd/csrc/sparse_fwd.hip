@@ -11,7 +11,8 @@
 // with the stage of tile t: no register holds a row list that is still in
 // flight, and the two kinds of direct load into a slot share its pointer.
 // Tokens with more keys (later ones: the response window grows with t) are
-// dispatched first.
+// dispatched first.  Where tokens are few, each one's tiles are cut into chunks
+// (grid z), whose results are merged like split-KV parts.
 #include <type_traits>
 
 #include "sparse_common.h"
@@ -57,6 +58,7 @@ __device__ __forceinline__ void fwd_tile(const SparseArgs& a, char* __restrict__
   s_pv<16>(tile, pack8(s, 0), pack8(s, 1), oacc, so, 0);
 }
 
+template <bool kChunks>
 __global__ __launch_bounds__(256, 1) void sparse_fwd_kernel(SparseArgs a) {
   __shared__ __attribute__((aligned(1024))) char smem[kFSlots * kSlotBytes];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -65,7 +67,18 @@ __global__ __launch_bounds__(256, 1) void sparse_fwd_kernel(SparseArgs a) {
   const int t = a.n_q - 1 - (int)blockIdx.x;
   const int head = blockIdx.y * 128 + w * 32 + l32;
   const int n_t = a.ntok[t];
-  const int n_tiles = (n_t + kKeys - 1) / kKeys;
+  // this workgroup's tiles of the token's list: chunk z of gridDim.z equal ones
+  const int z = kChunks ? (int)blockIdx.z : 0;
+  const int T0 = chunk_begin<kChunks>(n_t, z), n_tiles = chunk_begin<kChunks>(n_t, z + 1);
+  float* out = a.out + (((int64_t)z * a.n_q + t) * a.n_heads + head) * kDv;
+  float* lse = a.lse + ((int64_t)z * a.n_heads + head) * a.n_q + t;
+  if (kChunks && T0 >= n_tiles) {   // fewer tiles than chunks: an empty part
+#pragma unroll
+    for (int c = 0; c < kDv / 8; ++c)
+      *reinterpret_cast<f32x4*>(out + 8 * c + 4 * hh) = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (hh == 0) *lse = -INFINITY;
+    return;
+  }
   const __amdgpu_buffer_rsrc_t phys_t = phys_rsrc(a, t);
   const __amdgpu_buffer_rsrc_t pool = pool_rsrc(a.latent);
   // tiles past the last one are clamped to it: every iteration issues one
@@ -79,17 +92,17 @@ __global__ __launch_bounds__(256, 1) void sparse_fwd_kernel(SparseArgs a) {
   fl.init(lane, w);
   const SOffsets so = s_offsets(lane);
   // the row lists of the first three tiles and Q load before any tile does
-  const int32_t r0 = f.rows_of(phys_t, 0, lane), r1 = f.rows_of(phys_t, clamp(1), lane),
-                r2 = f.rows_of(phys_t, clamp(2), lane);
+  const int32_t r0 = f.rows_of(phys_t, T0, lane), r1 = f.rows_of(phys_t, clamp(T0 + 1), lane),
+                r2 = f.rows_of(phys_t, clamp(T0 + 2), lane);
   auto rows_area = [&](int slot) {
     return reinterpret_cast<int32_t*>(smem + slot * kSlotBytes + kTile + 256 * w);
   };
   f.issue(smem, pool, r0, w);
-  f.rows_to_lds(rows_area(0), phys_t, clamp(3), lane);
+  f.rows_to_lds(rows_area(0), phys_t, clamp(T0 + 3), lane);
   f.issue(smem + kSlotBytes, pool, r1, w);
-  f.rows_to_lds(rows_area(1), phys_t, clamp(4), lane);
+  f.rows_to_lds(rows_area(1), phys_t, clamp(T0 + 4), lane);
   f.issue(smem + 2 * kSlotBytes, pool, r2, w);
-  f.rows_to_lds(rows_area(2), phys_t, clamp(5), lane);
+  f.rows_to_lds(rows_area(2), phys_t, clamp(T0 + 5), lane);
 
   bf16x8 qreg[36];   // Q^T operand: q[t][head][16*ks + 8*hh .. +7]
   {
@@ -105,8 +118,9 @@ __global__ __launch_bounds__(256, 1) void sparse_fwd_kernel(SparseArgs a) {
   wait_fetch();
   tile_barrier();
 
-  for (int T = 0; T < n_tiles; ++T) {
-    fwd_tile(a, smem + ((T + 3) % kFSlots) * kSlotBytes, smem + (T % kFSlots) * kSlotBytes, f, fl,
+  for (int T = T0; T < n_tiles; ++T) {
+    const int i = T - T0;
+    fwd_tile(a, smem + ((i + 3) % kFSlots) * kSlotBytes, smem + (i % kFSlots) * kSlotBytes, f, fl,
              pool, w, qreg, so, T, n_t, hh, oacc, m_run, l_run, phys_t, clamp(T + 6), lane);
     // vmcnt(20): the stages of tiles T + 2 and T + 3 may be in flight;
     // lgkmcnt(0): this tile's LDS reads have landed (the stage issued after
@@ -119,7 +133,6 @@ __global__ __launch_bounds__(256, 1) void sparse_fwd_kernel(SparseArgs a) {
 
   const float l_tot = half_sum(l_run);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  float* out = a.out + ((int64_t)t * a.n_heads + head) * kDv;
 #pragma unroll
   for (int db = 0; db < 16; ++db) {
 #pragma unroll
@@ -133,15 +146,17 @@ __global__ __launch_bounds__(256, 1) void sparse_fwd_kernel(SparseArgs a) {
     }
   }
   if (hh == 0)
-    a.lse[(int64_t)head * a.n_q + t] =
-        l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
+    *lse = l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
 }
 
 }  // namespace
 
-hipError_t launch_sparse_fwd(const SparseArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(sparse_fwd_kernel, dim3((unsigned)a.n_q, a.n_heads / 128), dim3(256), 0,
-                     stream, a);
+hipError_t launch_sparse_fwd(const SparseArgs& a, int n_chunks, hipStream_t stream) {
+  const dim3 grid((unsigned)a.n_q, a.n_heads / 128, n_chunks);
+  if (n_chunks > 1)
+    hipLaunchKernelGGL(sparse_fwd_kernel<true>, grid, dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL(sparse_fwd_kernel<false>, grid, dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

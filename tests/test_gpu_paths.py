@@ -118,3 +118,55 @@ def test_merge_groups(R, H, Dv, groups, flag):
         two, _ = B.lse_merge(go, gl, out_dtype=torch.float32, flags=flag)
         close = np.abs(host(two) - host(out)) <= 1e-6 * (np.abs(host(two)) + 1e-30)
         assert close.mean() >= 0.99
+
+
+@pytest.mark.parametrize("R,topk,heads", [(1, 2048, 128), (3, 515, 128), (9, 300, 256),
+                                          (24, 2048, 128), (130, 700, 128)])
+def test_sparse_key_chunks(R, topk, heads):
+    """Few tokens: each one's key list is cut into chunks whose results are
+    merged (the forward) or added (dq), among them tokens whose selection is
+    mostly pads, with fewer tiles than chunks.  The lists straddle the batches
+    in which they are resolved.  A workspace too small for the partial results
+    (the size before any chunk) gives the same within rounding, and
+    accumulation adds to dq once."""
+    import ctypes
+
+    import numpy as np
+    import torch
+
+    from paper_2607_14952_amd import inputs
+    from paper_2607_14952_amd.replay import to_device
+    from tests._gpu import announce, host, rel_l2
+    from tests.test_gpu_sparse import run
+    cfg = configs.C5.scaled(name=f"sparse_chunks_{R}", prefix_len=8192, resp_len=R, topk=topk,
+                            n_q_heads=heads)
+    h = inputs.sparse_inputs(cfg)
+    idx = h["idx"].copy()
+    if R > 2:
+        idx[1, 3:] = -1            # one tile, where the others have many
+        idx[2, : topk // 2] = -1
+    h = dict(h, idx=idx)
+    run(cfg, h)
+    q, lat, di = to_device(h["q"]), to_device(h["latent_pool"]), to_device(idx)
+    kv = B.PagedKV(lat, lat, to_device(h["page_table"]))
+    kw = dict(prefix_len=cfg.prefix_len, q_pos0=cfg.q_pos0, scale=cfg.scale)
+    do = to_device(h["d_out"])
+    out, lse = B.sparse_attn_fwd(q, kv, di, **kw)
+    dq = B.sparse_attn_bwd(q, kv, di, do, out, lse, **kw)
+    pad = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    lists = pad(R * -(-(topk + R) // 32) * 32 * 4) + pad(R * 4)
+    small = torch.empty(lists + 2 * pad(R * heads * 4), dtype=torch.uint8, device="cuda")
+    announce(f"sparse R={R}: workspace without partial results")
+    out1, _ = B.sparse_attn_fwd(q, kv, di, workspace=small[:lists], **kw)
+    acc = torch.ones_like(dq)
+    B.sparse_attn_bwd(q, kv, di, do, out, lse, dq=acc, workspace=small,
+                      flags=B.FLAG_ACCUMULATE_DQ, **kw)
+    acc2 = torch.ones_like(dq)
+    B.sparse_attn_bwd(q, kv, di, do, out, lse, dq=acc2, flags=B.FLAG_ACCUMULATE_DQ, **kw)
+    torch.cuda.synchronize()
+    # P and dS are rounded to bf16 relative to another maximum: 2^-9 each
+    assert rel_l2(host(out1), host(out)) <= 2.0 ** -8
+    assert rel_l2(host(acc) - 1, host(dq)) <= 2.0 ** -8
+    assert rel_l2(host(acc2) - 1, host(dq)) <= 1e-5
+    p = B._sparse_params(q, kv, **kw)
+    assert lists <= B.load_library().ls_sparse_attn_workspace_size(ctypes.byref(p), topk, 0) <= 64 << 20
