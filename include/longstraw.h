@@ -314,6 +314,19 @@ ls_status ls_topk_select(const float* scores, int64_t ld, const int32_t* positio
                          int32_t* out_pos, float* out_scores, int64_t out_ld, void* stream);
 
 /*
+ * ls_topk_select_ws: ls_topk_select with a workspace (device, 16-byte aligned),
+ * which lets it share a long row among several workgroups where rows are few:
+ * same arguments, same result.  ls_topk_workspace_size gives the bytes that a
+ * shape can use (0: none); with less, or NULL, a row has one workgroup, as in
+ * ls_topk_select.  The workspace's contents need not survive between calls.
+ */
+size_t ls_topk_workspace_size(int32_t n_rows, int64_t n, int32_t k);
+ls_status ls_topk_select_ws(const float* scores, int64_t ld, const int32_t* positions,
+                            int32_t n_rows, int64_t n, int64_t pos_offset, int32_t k,
+                            int32_t* out_pos, float* out_scores, int64_t out_ld, void* workspace,
+                            size_t workspace_bytes, void* stream);
+
+/*
  * ls_sparse_attn_fwd_noalloc: ls_sparse_attn_fwd for callers that cannot
  * allocate device memory or pass a workspace (code under HIP graph capture,
  * tight serving loops, harnesses that forbid allocation).  Same arguments,

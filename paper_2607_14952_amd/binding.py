@@ -26,6 +26,7 @@ EXPORTS = ["ls_abi_version", "ls_status_string", "ls_last_error", "ls_gather_kv"
            "ls_prefix_attn_fwd", "ls_lse_merge", "ls_lse_merge_groups",
            "ls_prefix_attn_bwd_workspace_size", "ls_prefix_attn_bwd", "ls_sparse_attn_workspace_size",
            "ls_sparse_attn_fwd", "ls_sparse_attn_bwd", "ls_dsa_index_scores", "ls_topk_select",
+           "ls_topk_select_ws", "ls_topk_workspace_size",
            "ls_hbm_read_probe", "ls_sparse_attn_fwd_noalloc"]
 
 
@@ -107,6 +108,12 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.ls_topk_select.restype = c_int32
     lib.ls_topk_select.argtypes = [c_void_p, c_int64, c_void_p, c_int32, c_int64, c_int64, c_int32,
                                    c_void_p, c_void_p, c_int64, c_void_p]
+    lib.ls_topk_select_ws.restype = c_int32
+    lib.ls_topk_select_ws.argtypes = [c_void_p, c_int64, c_void_p, c_int32, c_int64, c_int64,
+                                      c_int32, c_void_p, c_void_p, c_int64, c_void_p, c_size_t,
+                                      c_void_p]
+    lib.ls_topk_workspace_size.restype = c_size_t
+    lib.ls_topk_workspace_size.argtypes = [c_int32, c_int64, c_int32]
     lib.ls_sparse_attn_fwd_noalloc.restype = c_int32
     lib.ls_sparse_attn_fwd_noalloc.argtypes = [P, c_void_p, c_int32, c_void_p, c_void_p, c_void_p]
     lib.ls_hbm_read_probe.restype = c_int32
@@ -461,12 +468,19 @@ def topk_select(scores, k: int, *, n: int | None = None, positions=None, pos_off
                          "have unit column stride")
     if positions is not None and positions.stride(0) != scores.stride(0):
         raise ValueError("topk_select: positions must have the row stride of scores")
-    check(load_library().ls_topk_select(
+    # few long rows are shared among workgroups, through candidates kept here (memory
+    # of the stream the call runs on, so that it is not handed out again before)
+    need = load_library().ls_topk_workspace_size(rows, n, k)
+    ws = None
+    if need:
+        with torch.cuda.stream(stream):
+            ws = torch.empty(need, dtype=torch.uint8, device=scores.device)
+    check(load_library().ls_topk_select_ws(
         _ptr(scores, torch.float32, "scores", dense=False), scores.stride(0),
         _ptr(positions, torch.int32, "positions", dense=False), rows, n, pos_offset, k,
         _ptr(out_pos, torch.int32, "out_pos", dense=False),
         _ptr(out_scores, torch.float32, "out_scores", dense=False), out_pos.stride(0),
-        _stream(stream)))
+        _ptr(ws, None, "workspace"), need, _stream(stream)))
     return out_pos, out_scores
 
 

@@ -897,10 +897,24 @@ LS_API ls_status ls_dsa_index_scores(const ls_dsa_params* p, int64_t pos_begin, 
   return e == hipSuccess ? LS_OK : hip_fail(e, "dsa score launch");
 }
 
+LS_API size_t ls_topk_workspace_size(int32_t n_rows, int64_t n, int32_t k) {
+  if (n_rows <= 0 || n <= 0 || k < 1) return 0;
+  const int chunks = ls::topk_chunks(n_rows, n, k);
+  return chunks > 1 ? 2 * pad256((size_t)n_rows * chunks * k * 4) : 0;
+}
+
 LS_API ls_status ls_topk_select(const float* scores, int64_t ld, const int32_t* positions,
                                 int32_t n_rows, int64_t n, int64_t pos_offset, int32_t k,
                                 int32_t* out_pos, float* out_scores, int64_t out_ld,
                                 void* stream) {
+  return ls_topk_select_ws(scores, ld, positions, n_rows, n, pos_offset, k, out_pos, out_scores,
+                           out_ld, nullptr, 0, stream);
+}
+
+LS_API ls_status ls_topk_select_ws(const float* scores, int64_t ld, const int32_t* positions,
+                                   int32_t n_rows, int64_t n, int64_t pos_offset, int32_t k,
+                                   int32_t* out_pos, float* out_scores, int64_t out_ld,
+                                   void* workspace, size_t workspace_bytes, void* stream) {
   if (k < 1 || n < 0 || n_rows < 0 || ld < n || out_ld < k || pos_offset < 0 ||
       pos_offset + n > (int64_t(1) << 31))
     return fail(LS_ERR_INVALID_ARG, "bad top-k shape (rows %d, n %lld, ld %lld, k %d)", n_rows,
@@ -913,6 +927,13 @@ LS_API ls_status ls_topk_select(const float* scores, int64_t ld, const int32_t* 
   const size_t out_bytes = ((size_t)(n_rows - 1) * out_ld + k) * 4;
   std::vector<Range> outs{rng("out_pos", out_pos, out_bytes),
                           rng("out_scores", out_scores, out_scores ? out_bytes : 0)};
+  const size_t need = ls_topk_workspace_size(n_rows, n, k);
+  const bool cut = need > 0 && workspace && workspace_bytes >= need;
+  if (cut) {
+    if (!aligned16(workspace))
+      return fail(LS_ERR_INVALID_ARG, "workspace must be 16-byte aligned");
+    outs.push_back(rng("workspace", workspace, need));
+  }
   ls_status st = check_alias(outs, ins);
   if (st != LS_OK) return st;
   ls::TopkArgs a{};
@@ -926,7 +947,9 @@ LS_API ls_status ls_topk_select(const float* scores, int64_t ld, const int32_t* 
   a.pos_offset = pos_offset;
   a.n_rows = n_rows;
   a.k = k;
-  hipError_t e = ls::launch_topk(a, (hipStream_t)stream);
+  hipError_t e = ls::launch_topk(a, cut ? ls::topk_chunks(n_rows, n, k) : 1, (int32_t*)workspace,
+                                 (float*)((char*)workspace + (cut ? need / 2 : 0)),
+                                 (hipStream_t)stream);
   return e == hipSuccess ? LS_OK : hip_fail(e, "top-k launch");
 }
 

@@ -3,8 +3,8 @@
 //
 // Score kernel.  I[t, s] = sum_j w[t, j] ReLU(<q[t, j], k_s>) with H index
 // heads of width 128 and one index key per position (shared by the heads).
-// Workgroup = 8 waves (4 for 8 or 24 heads) = 32 tokens x a chunk of 16,384
-// positions; wave w holds the queries of its H/8 (H/4) heads for the 32 tokens
+// Workgroup = 8 waves (4 for 8 or 24 heads) = 32 tokens x a chunk of up to 16,384
+// positions (score_tiles); wave w holds the queries of its H/8 (H/4) heads for the 32 tokens
 // in registers, and two waves share each SIMD.  The token blocks of a chunk
 // are consecutive work items mapped onto one XCD, so its keys are read once
 // into that XCD's L2.
@@ -18,7 +18,8 @@
 // I (fp32).  Partials are double buffered, so one barrier per tile serves the
 // ring and the exchange.
 //
-// Top-k kernel.  One workgroup per row.  A histogram of the top 12 bits of an
+// Top-k kernel.  One workgroup per row, or per chunk of a row where rows are few
+// and long (topk_chunks), with a second launch over the candidates.  A histogram of the top 12 bits of an
 // order-preserving 32-bit key of the fp32 scores finds the bin holding the
 // k-th largest key.  When that bin holds at most 4,096 keys (the usual case),
 // one more pass over the row gathers them into LDS and counts the keys above
@@ -29,6 +30,7 @@
 // first), writing positions in ascending order: each of the 8 waves owns a
 // contiguous segment of the row, and per-segment counts set its output base.
 // The row is read three times (five when the fallback runs).
+#include <algorithm>
 #include <type_traits>
 
 #include "ls_internal.h"
@@ -42,10 +44,7 @@ constexpr int kIRow = kID * 2;            // bytes per index key
 constexpr int kITile = 32 * kIRow;        // 32 positions: 8 KiB
 constexpr int kIAhead = 2;
 constexpr int kISlots = kIAhead + 2;
-#ifndef LS_DSA_CHUNK
-#define LS_DSA_CHUNK 16384
-#endif
-constexpr int kIChunk = LS_DSA_CHUNK;     // positions per workgroup
+constexpr int kIMaxTiles = 512;           // most key tiles per workgroup (16,384 positions)
 constexpr int kXWave = 32 * 32 * 4;       // one wave's partial tile (fp32)
 typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
 constexpr int kIKAhead = 3;               // key operand reads in flight
@@ -112,8 +111,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void dsa_score_kernel(DsaArgs a) {
   const int tok0 = wi.x * 32;
   const int tok = tok0 + l32;
   const bool row_ok = tok < a.n_q;
-  const int64_t c0 = a.pos_begin + (int64_t)wi.y * kIChunk;   // multiple of 32
-  const int64_t c1 = min(a.pos_end, c0 + kIChunk);
+  const int64_t c0 = a.pos_begin + (int64_t)wi.y * a.chunk;   // multiple of 32
+  const int64_t c1 = min(a.pos_end, c0 + a.chunk);
   const int n_tiles = (int)((c1 - c0 + 31) / 32);
 
   // this wave's heads: queries (B operand: lane = token, dims 16ks + 8hh ..) and weights
@@ -271,7 +270,8 @@ __device__ __forceinline__ uint32_t okey(float x) {
 // below; one pass then gathers every key at or above the bound into a
 // per-wave LDS region (in position order), and the selection is resolved
 // there.  A region overflow, or fewer than k keys at or above the bound,
-// falls back to the full-row passes.
+// falls back to the full-row passes.  One workgroup looks through about 5 keys
+// per ns, however many CUs are idle, so few long rows are cut (topk_chunks).
 constexpr int64_t kFMinN = 65536;
 constexpr int kFMaxK = 2048;
 constexpr int kFCap = 1000;     // candidates per wave region (LDS <= 80 KiB: two rows per CU)
@@ -289,7 +289,7 @@ struct TopkShared {
       int32_t widx[kKWaves][kFCap];
     };
   };
-  uint32_t wave_gt[kKWaves], wave_eq[kKWaves], wcount[kKWaves];
+  uint32_t wave_gt[kKWaves], wave_eq[kKWaves], wcount[kKWaves], wave_sum[kKWaves];
   uint32_t bin, above, count;
 };
 
@@ -299,52 +299,63 @@ __device__ __forceinline__ float key_float(uint32_t key) {
   return __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key);
 }
 
-// Wave 0: the bin b of hist[0 .. nbins) holding the need-th largest (counting
-// from the top) and the number of keys in bins above it.  need >= 1 and the
-// histogram holds at least need keys.
-__device__ __forceinline__ void find_crossing(TopkShared& sh, int nbins, uint32_t need, int lane) {
-  const int per = nbins / 64;
+// The bin b of hist[0 .. nbins) holding the need-th largest (counting from the
+// top) and the number of keys in bins above it, by the whole workgroup: need >= 1
+// and the histogram holds at least need keys (else bin 0, 0 above).  A thread
+// sums kPer neighbouring bins, from its own start so that a wave's reads
+// spread over the banks.
+template <int kPer>
+__device__ __forceinline__ void find_crossing(TopkShared& sh, uint32_t need, int tid) {
+  const int lane = tid & 63, wv = tid >> 6;
   uint32_t mine = 0;
-  for (int b = 0; b < per; ++b) mine += sh.hist[lane * per + b];
-  uint32_t incl = mine;   // keys in this lane's bins and above
+#pragma unroll
+  for (int b = 0; b < kPer; ++b) mine += sh.hist[tid * kPer + ((b + tid) & (kPer - 1))];
+  uint32_t incl = mine;   // keys in this thread's bins and above, within the wave
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     const uint32_t o = __shfl_down(incl, d);
     if (lane + d < 64) incl += o;
   }
+  if (lane == 0) sh.wave_sum[wv] = incl;
+  if (tid == 0) sh.bin = sh.above = 0;
+  __syncthreads();
+  for (int v = wv + 1; v < kKWaves; ++v) incl += sh.wave_sum[v];
   const uint32_t excl = incl - mine;
   if (excl < need && need <= incl) {
     uint32_t acc = excl;
-    int b = lane * per + per - 1;
-    for (; b > lane * per; --b) {
+    int b = tid * kPer + kPer - 1;
+    for (; b > tid * kPer; --b) {
       if (acc + sh.hist[b] >= need) break;
       acc += sh.hist[b];
     }
     sh.bin = (uint32_t)b;
     sh.above = acc;
   }
+  __syncthreads();
 }
 
 __global__ __launch_bounds__(kKThreads) void topk_kernel(TopkArgs a) {
   __shared__ TopkShared sh;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int64_t row = blockIdx.x;
-  const float* x = a.scores + row * a.ld;
-  const int32_t* px = a.positions ? a.positions + row * a.ld : nullptr;
-  int32_t* op = a.out_pos + row * a.out_ld;
-  float* os = a.out_scores ? a.out_scores + row * a.out_ld : nullptr;
-  auto pos_of = [&](int64_t i) { return px ? px[i] : (int32_t)(a.pos_offset + i); };
+  // chunk y of the row (the whole row when it is not cut)
+  const int64_t row = blockIdx.x, col0 = (int64_t)blockIdx.y * a.seg;
+  const int64_t n = min(a.seg, a.n - col0);
+  const float* x = a.scores + row * a.ld + col0;
+  const int32_t* px = a.positions ? a.positions + row * a.ld + col0 : nullptr;
+  int32_t* op = a.out_pos + row * a.out_ld + (int64_t)blockIdx.y * a.k;
+  float* os = a.out_scores ? a.out_scores + row * a.out_ld + (int64_t)blockIdx.y * a.k : nullptr;
+  auto pos_of = [&](int64_t i) { return px ? px[i] : (int32_t)(a.pos_offset + col0 + i); };
 
-  if (a.n <= a.k) {   // everything is selected
+  if (n <= a.k) {   // everything is selected
     for (int64_t i = tid; i < a.k; i += kKThreads) {
-      op[i] = i < a.n ? pos_of(i) : -1;
-      if (os) os[i] = i < a.n ? x[i] : -INFINITY;
+      op[i] = i < n ? pos_of(i) : -1;
+      if (os) os[i] = i < n ? x[i] : -INFINITY;
     }
     return;
   }
   // wave v owns the contiguous segment [lo, hi) in the gather and write passes
-  const int64_t seg = ((a.n + kKWaves - 1) / kKWaves + 63) / 64 * 64;
-  const int64_t lo = (int64_t)wv * seg, hi = min(a.n, lo + seg);
+  const int64_t seg = ((n + kKWaves - 1) / kKWaves + 63) / 64 * 64;
+  const int64_t lo = (int64_t)wv * seg, hi = min(n, lo + seg);
   const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 
   // histogram of a digit of the keys whose higher bits equal `prefix`
@@ -352,17 +363,17 @@ __global__ __launch_bounds__(kKThreads) void topk_kernel(TopkArgs a) {
     const int nbins = 1 << bits;
     for (int b = tid; b < nbins; b += kKThreads) sh.hist[b] = 0;
     __syncthreads();
-    for (int64_t i0 = tid; i0 < a.n; i0 += kKUnroll * kKThreads) {
+    for (int64_t i0 = tid; i0 < n; i0 += kKUnroll * kKThreads) {
       float v[kKUnroll];
 #pragma unroll
       for (int u = 0; u < kKUnroll; ++u) {
         const int64_t i = i0 + (int64_t)u * kKThreads;
-        v[u] = i < a.n ? x[i] : 0.f;
+        v[u] = i < n ? x[i] : 0.f;
       }
 #pragma unroll
       for (int u = 0; u < kKUnroll; ++u) {
         const uint32_t key = okey(v[u]);
-        const bool in = i0 + (int64_t)u * kKThreads < a.n &&
+        const bool in = i0 + (int64_t)u * kKThreads < n &&
                         (pbits == 0 || (key >> (shift + bits)) == prefix);
         if (in) atomicAdd(&sh.hist[(key >> shift) & (nbins - 1)], 1u);
       }
@@ -370,33 +381,38 @@ __global__ __launch_bounds__(kKThreads) void topk_kernel(TopkArgs a) {
     __syncthreads();
   };
   auto crossing = [&](int nbins, uint32_t need) {
-    if (tid == 0) {
-      sh.bin = 0;
-      sh.above = 0;
-    }
-    __syncthreads();
-    if (wv == 0) find_crossing(sh, nbins, need, lane);
-    __syncthreads();
+    __syncthreads();   // (every thread has read the last result)
+    if (nbins == 4096) find_crossing<4096 / kKThreads>(sh, need, tid);
+    else find_crossing<1024 / kKThreads>(sh, need, tid);
   };
 
-  if (a.n >= kFMinN && a.k <= kFMaxK && (reinterpret_cast<uintptr_t>(x) & 15) == 0) {
+  if (n >= kFMinN && a.k <= kFMaxK && (reinterpret_cast<uintptr_t>(x) & 15) == 0) {
     // --- sample: 64 blocks spread over the row; digit histograms of their keys
-    const int blk = (int)min<int64_t>(1024, max<int64_t>(256, (a.n / 512) / 256 * 256));
+    const int blk = (int)min<int64_t>(1024, max<int64_t>(256, (n / 2048) / 256 * 256));
     auto sample_hist = [&](int shift, int bits, int pbits, uint32_t prefix) {
       for (int b = tid; b < (1 << bits); b += kKThreads) sh.hist[b] = 0;
       __syncthreads();
-      for (int j = wv; j < 64; j += kKWaves) {
-        const int64_t start = ((int64_t)j * a.n / 64) & ~int64_t(3);
-        for (int c0 = 0; c0 < blk; c0 += 256) {
-          const int64_t i = start + c0 + 4 * lane;
-          if (i + 3 < a.n) {
-            const f32x4 v = *reinterpret_cast<const f32x4*>(x + i);
+      // the wave's blocks in 256-key pieces, eight loads in flight
+      const int per_blk = blk / 256, pieces = 64 / kKWaves * per_blk;
+      for (int p0 = 0; p0 < pieces; p0 += kFUnroll) {
+        f32x4 v[kFUnroll];
+        bool in[kFUnroll];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-              const uint32_t key = okey(v[c]);
-              if (pbits == 0 || (key >> (shift + bits)) == prefix)
-                atomicAdd(&sh.hist[(key >> shift) & ((1u << bits) - 1)], 1u);
-            }
+        for (int u = 0; u < kFUnroll; ++u) {
+          const int p = p0 + u, j = wv + kKWaves * (p / per_blk);
+          const int64_t start = ((int64_t)j * n / 64) & ~int64_t(3);
+          const int64_t i = start + 256 * (p % per_blk) + 4 * lane;
+          in[u] = p < pieces && i + 3 < n;
+          v[u] = *reinterpret_cast<const f32x4*>(x + (in[u] ? i : 0));
+        }
+#pragma unroll
+        for (int u = 0; u < kFUnroll; ++u) {
+          if (!in[u]) continue;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const uint32_t key = okey(v[u][c]);
+            if (pbits == 0 || (key >> (shift + bits)) == prefix)
+              atomicAdd(&sh.hist[(key >> shift) & ((1u << bits) - 1)], 1u);
           }
         }
       }
@@ -412,9 +428,12 @@ __global__ __launch_bounds__(kKThreads) void topk_kernel(TopkArgs a) {
     n_s = 0;
     for (int v = 0; v < kKWaves; ++v) n_s += sh.wave_gt[v];
     // bound: the sample key, to 22 bits, at which the sample count from the
-    // top reaches twice the count expected above the k-th key (at least 16)
-    const double want = 2.0 * (double)a.k * (double)n_s / (double)a.n;
-    const uint32_t need_s = (uint32_t)min<double>((double)n_s, max<double>(16.0, ceil(want)));
+    // top reaches the count expected above the k-th key and six of its standard
+    // deviations more (a row in random order then falls short of k about once
+    // in 10^8)
+    const double expect = (double)a.k * (double)n_s / (double)n;
+    const double want = ceil(expect + 6.0 * sqrt(expect) + 8.0);
+    const uint32_t need_s = (uint32_t)min<double>((double)n_s, want);
     uint32_t lkey = 0;
     if (need_s >= 1) {
       crossing(4096, need_s);
@@ -424,49 +443,65 @@ __global__ __launch_bounds__(kKThreads) void topk_kernel(TopkArgs a) {
       lkey = (s1 << 20) | (sh.bin << 10);
     }
     // --- one pass: wave v gathers its segment's keys >= lkey, in position order
-    const int64_t fseg = ((a.n + kKWaves - 1) / kKWaves + 255) / 256 * 256;
-    const int64_t flo = (int64_t)wv * fseg, fhi = min(a.n, flo + fseg);
+    const int64_t fseg = ((n + kKWaves - 1) / kKWaves + 255) / 256 * 256;
+    const int64_t flo = (int64_t)wv * fseg, fhi = min(n, flo + fseg);
     uint32_t wcount = 0;
-    for (int64_t i0 = flo; i0 < fhi && wcount <= (uint32_t)kFCap; i0 += 256 * kFUnroll) {
-      f32x4 v[kFUnroll];
+    const float bound = key_float(lkey);
+    f32x4 nv[kFUnroll];   // the next batch, loaded while this one is looked through
+    auto load = [&](int64_t i0) {
 #pragma unroll
       for (int u = 0; u < kFUnroll; ++u) {
         const int64_t i = i0 + 256 * u + 4 * lane;
-        if (i + 3 < fhi) {
-          v[u] = *reinterpret_cast<const f32x4*>(x + i);
-        } else {
+        nv[u] = *reinterpret_cast<const f32x4*>(x + (i + 3 < fhi ? i : 0));
+      }
+    };
+    load(flo);
+    for (int64_t i0 = flo; i0 < fhi && wcount <= (uint32_t)kFCap; i0 += 256 * kFUnroll) {
+      f32x4 v[kFUnroll];
 #pragma unroll
-          for (int c = 0; c < 4; ++c) v[u][c] = i + c < fhi ? x[i + c] : -INFINITY;
+      for (int u = 0; u < kFUnroll; ++u) v[u] = nv[u];
+      if (i0 + 256 * kFUnroll < fhi) load(i0 + 256 * kFUnroll);
+      const bool full = i0 + 256 * kFUnroll <= fhi;
+      if (!full) {   // the segment's last, partly filled pieces
+#pragma unroll
+        for (int u = 0; u < kFUnroll; ++u) {
+          const int64_t i = i0 + 256 * u + 4 * lane;
+          if (i + 3 >= fhi) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[u][c] = i + c < fhi ? x[i + c] : 0.f;
+          }
         }
       }
 #pragma unroll
       for (int u = 0; u < kFUnroll; ++u) {
         const int64_t i = i0 + 256 * u + 4 * lane;
-        uint32_t key[4];
+        // (the float order puts -0 and the NaNs of the key order's low end in
+        // too; keys below the bound among the candidates do no harm)
         bool in[4];
-        uint32_t cnt = 0;
+        uint64_t m[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-          key[c] = okey(v[u][c]);
-          in[c] = i + c < fhi && key[c] >= lkey;
-          cnt += in[c] ? 1u : 0u;
+          in[c] = !(v[u][c] < bound) && (full || i + c < fhi);
+          m[c] = __ballot(in[c]);
         }
-        // exclusive prefix of the per-lane counts (0..4) over the lanes
-        const uint64_t m0 = __ballot(cnt & 1), m1 = __ballot(cnt & 2), m2 = __ballot(cnt & 4);
-        const uint32_t pre = (uint32_t)(__popcll(m0 & below) + 2 * __popcll(m1 & below) +
-                                        4 * __popcll(m2 & below));
-        uint32_t slot = wcount + pre;
+        if ((m[0] | m[1] | m[2] | m[3]) == 0) continue;
+        uint32_t slot = wcount;   // + the candidates of lower lanes
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          slot = __builtin_amdgcn_mbcnt_lo((uint32_t)m[c], slot);
+          slot = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[c] >> 32), slot);
+          wcount += (uint32_t)__popcll(m[c]);
+        }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           if (in[c]) {
             if (slot < (uint32_t)kFCap) {
-              sh.wkey[wv][slot] = key[c];
+              sh.wkey[wv][slot] = okey(v[u][c]);
               sh.widx[wv][slot] = (int32_t)(i + c);
             }
             ++slot;
           }
         }
-        wcount += (uint32_t)(__popcll(m0) + 2 * __popcll(m1) + 4 * __popcll(m2));
       }
     }
     if (lane == 0) sh.wcount[wv] = wcount;
@@ -685,9 +720,38 @@ __global__ __launch_bounds__(kKThreads) void topk_kernel(TopkArgs a) {
 
 }  // namespace
 
-hipError_t launch_dsa_scores(const DsaArgs& a, hipStream_t stream) {
-  const unsigned chunks = (unsigned)((a.pos_end - a.pos_begin + kIChunk - 1) / kIChunk);
-  const dim3 grid((unsigned)((a.n_q + 31) / 32), chunks);
+namespace {
+// Key tiles per score workgroup.  `blocks` token blocks times the chunks of
+// `tiles` tiles run `slots` at a time; a workgroup costs its tiles and about 4
+// for its queries and first loads.  The least sum of rounds is taken, with the
+// longest chunks among equals (the token blocks of a chunk share its keys in
+// L2).  Measured, 32 heads, 512 tiles each before -> this rule: 1 row x 16,384
+// positions 707 -> 15 us, 32 rows x 524,288 759 -> 143 us, 500 rows x 524,288
+// (2 whole rounds either way) 1,850 us.
+int score_tiles(int64_t blocks, int64_t tiles, int64_t slots) {
+  int64_t best = 1, least = INT64_MAX;
+  const int64_t least_chunks = (tiles + kIMaxTiles - 1) / kIMaxTiles;
+  const int64_t most_chunks = std::max(least_chunks, std::min(tiles, 4 * slots / blocks));
+  for (int64_t c = least_chunks; c <= most_chunks; ++c) {
+    const int64_t per = (tiles + c - 1) / c;
+    const int64_t chunks = (tiles + per - 1) / per;   // (65,535: a grid dimension)
+    const int64_t cost = (blocks * chunks + slots - 1) / slots * (per + 4);
+    if (cost < least) {
+      least = cost;
+      best = per;
+    }
+  }
+  return (int)best;
+}
+}  // namespace
+
+hipError_t launch_dsa_scores(const DsaArgs& args, hipStream_t stream) {
+  DsaArgs a = args;
+  const int64_t blocks = (a.n_q + 31) / 32, tiles = (a.pos_end - a.pos_begin + 31) / 32;
+  // workgroups of 8 waves run one per CU (96 KiB of LDS), of 4 waves two
+  const int per = score_tiles(blocks, tiles, a.n_heads % 16 == 0 ? 256 : 512);
+  a.chunk = (int64_t)per * 32;
+  const dim3 grid((unsigned)blocks, (unsigned)((tiles + per - 1) / per));
   // 16 and 32 heads: 8 waves (two per SIMD, 2 or 4 heads each); 8 and 24: 4 waves
   switch (a.n_heads) {
     case 8: hipLaunchKernelGGL((dsa_score_kernel<2, 4>), grid, dim3(256), 0, stream, a); break;
@@ -699,7 +763,46 @@ hipError_t launch_dsa_scores(const DsaArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_topk(const TopkArgs& a, hipStream_t stream) {
+// Chunks of a row.  A workgroup takes about 20 us and 0.17 us per 1,024 keys,
+// 512 run at a time (two per CU); a second launch selects from the chunks' k
+// candidates each, about 20 us and 0.3 us per 1,024 of these.  Chunks keep at
+// least kFMinN keys (and so more than k).  Measured, k = 2,048: 1 row x 1M 196
+// -> 93 us (16 chunks), 128 rows x 1M 238 -> 158 us (4), 32 rows x 524,288 132
+// -> 80 us (8); 131,072 columns stay whole.
+int topk_chunks(int64_t n_rows, int64_t n, int k) {
+  if (k > kFMaxK || n_rows <= 0) return 1;
+  int best = 1;
+  double least = 20 + 1.7e-4 * (double)n;
+  for (int c = 2; c <= 16 && n_rows * c <= 512 && n / c >= kFMinN; ++c) {
+    const double cost = 40 + 1.7e-4 * (double)n / c + 3e-4 * (double)c * k;
+    if (cost < least) {
+      best = c;
+      least = cost;
+    }
+  }
+  return best;
+}
+
+hipError_t launch_topk(const TopkArgs& args, int n_chunks, int32_t* cand_pos, float* cand_scores,
+                       hipStream_t stream) {
+  TopkArgs a = args;
+  a.seg = a.n;
+  if (n_chunks > 1) {
+    // each chunk's k largest, in ascending position order, chunk after chunk:
+    // the row's selection is among them, ties still resolved by position
+    a.seg = ((a.n + n_chunks - 1) / n_chunks + 255) / 256 * 256;
+    a.out_pos = cand_pos;
+    a.out_scores = cand_scores;
+    a.out_ld = (int64_t)n_chunks * a.k;
+    hipLaunchKernelGGL(topk_kernel, dim3((unsigned)a.n_rows, (unsigned)n_chunks), dim3(kKThreads),
+                       0, stream, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    a = args;
+    a.scores = cand_scores;
+    a.positions = cand_pos;
+    a.ld = a.n = a.seg = (int64_t)n_chunks * a.k;
+  }
   hipLaunchKernelGGL(topk_kernel, dim3((unsigned)a.n_rows), dim3(kKThreads), 0, stream, a);
   return hipGetLastError();
 }

@@ -110,6 +110,7 @@ struct DsaArgs {
   const int32_t* page_table;
   float* scores;             // [n_q, ld]: I[t, s] at t * ld + (s - pos_begin)
   int64_t ld, pos_begin, pos_end;
+  int64_t chunk;             // positions per workgroup, a multiple of 32 (set by the launcher)
   int32_t n_q, n_heads, log2_page;
 };
 
@@ -120,6 +121,7 @@ struct TopkArgs {
   int32_t* out_pos;          // [n_rows, out_ld], k used per row
   float* out_scores;         // [n_rows, out_ld] or null
   int64_t ld, out_ld, n, pos_offset;
+  int64_t seg;               // columns per workgroup (set by the launcher)
   int32_t n_rows, k;
 };
 
@@ -179,7 +181,11 @@ inline hipError_t launch_dq_reduce(const BwdArgs& a, int n_chunks, hipStream_t s
 }
 hipError_t launch_hbm_read(const void* buf, int64_t n16, uint32_t* out, hipStream_t stream);
 hipError_t launch_dsa_scores(const DsaArgs& a, hipStream_t stream);
-hipError_t launch_topk(const TopkArgs& a, hipStream_t stream);
+// n_chunks > 1 (from topk_chunks): the rows' chunks are selected from first, into
+// cand_pos / cand_scores [n_rows, n_chunks * k]
+int topk_chunks(int64_t n_rows, int64_t n, int k);
+hipError_t launch_topk(const TopkArgs& a, int n_chunks, int32_t* cand_pos, float* cand_scores,
+                       hipStream_t stream);
 hipError_t launch_fwd_bf16_d256(const FwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd_prep(const void* d_out, const void* out, bool dout_bf16, bool out_bf16,
                            const float* lse, int n_q, int n_heads, int dv, float* delta,

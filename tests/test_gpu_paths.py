@@ -170,3 +170,67 @@ def test_sparse_key_chunks(R, topk, heads):
     assert rel_l2(host(acc2) - 1, host(dq)) <= 1e-5
     p = B._sparse_params(q, kv, **kw)
     assert lists <= B.load_library().ls_sparse_attn_workspace_size(ctypes.byref(p), topk, 0) <= 64 << 20
+
+
+@pytest.mark.parametrize("kind", ["normal", "ties", "equal", "mostly_inf", "ascending"])
+@pytest.mark.parametrize("rows,n,k,ld_pad", [
+    (3, 300_003, 2048, 1),      # several chunks a row, a ragged last one
+    (1, 1_050_000, 1, 0),       # the most chunks
+    (2, 262_145, 700, 3),       # rows that are not 16-byte aligned
+    (40, 200_000, 64, 0), (5, 70_001, 2048, 3), (2, 5_000, 300, 0),
+], ids=["r3", "r1", "unaligned", "r40", "whole", "short"])
+def test_topk_shared_rows(rows, n, k, ld_pad, kind):
+    """The selection equals a stable sort's (ties to the lower position) however
+    a row is shared, with given positions too."""
+    import numpy as np
+    import torch
+    rng = np.random.default_rng(rows * 1000 + k)
+    x = rng.standard_normal((rows, n + ld_pad)).astype(np.float32)
+    if kind == "ties":
+        x = np.round(x * 4) / 4 * np.float32(1.0)
+        x[x == 0] = np.where(rng.random((x == 0).sum()) < 0.5, 0.0, -0.0)
+    elif kind == "equal":
+        x[:] = -2.5
+    elif kind == "mostly_inf":
+        x[:, k // 2:] = -np.inf
+    elif kind == "ascending":    # the largest keys all in the last chunk
+        x.sort(axis=1)
+    sc = torch.from_numpy(x).cuda()
+    pos = np.sort(rng.choice(1 << 30, size=n + ld_pad, replace=False)).astype(np.int32)
+    pos = np.broadcast_to(pos, x.shape).copy()
+    print(f"[gpu] top-k {kind} rows={rows} n={n} k={k}", flush=True)
+    idx, val = B.topk_select(sc, k, n=n, pos_offset=7)
+    named, _ = B.topk_select(sc, k, n=n, positions=torch.from_numpy(pos).cuda())
+    torch.cuda.synchronize()
+    # the key order of the library: -0 below +0
+    key = x[:, :n].view(np.int32)
+    key = np.where(key < 0, key ^ 0x7FFFFFFF, key)
+    for r in range(rows):
+        want = np.sort(np.argsort(-key[r].astype(np.int64), kind="stable")[:k])
+        assert np.array_equal(idx[r].cpu().numpy(), want + 7)
+        assert np.array_equal(val[r].cpu().numpy().view(np.int32), x[r, want].view(np.int32))
+        assert np.array_equal(named[r].cpu().numpy(), pos[r, want])
+
+
+@pytest.mark.parametrize("R,P,heads", [(1, 1_000, 8), (33, 4_100, 16), (70, 16_385 + 32, 24),
+                                       (40, 33_000, 32)])
+def test_dsa_scores_chunks(R, P, heads):
+    """Key chunks of a few tiles (the last one short) against fp64 products."""
+    import numpy as np
+    import torch
+
+    from paper_2607_14952_amd import inputs
+    from paper_2607_14952_amd.replay import to_device
+    from tests._gpu import host, rel_l2
+    h = inputs.dsa_index_inputs(5, R, heads, P, 64)
+    d = {k: to_device(v) for k, v in h.items()}
+    print(f"[gpu] dsa scores R={R} P={P}", flush=True)
+    s = B.dsa_index_scores(d["q_index"], d["w_index"], d["k_index_pool"], d["page_table"],
+                           pos_begin=32, pos_end=P)
+    torch.cuda.synchronize()
+    j = np.arange(32, P)
+    k = host(d["k_index_pool"])[h["page_table"][j // 64], j % 64]
+    q = host(d["q_index"])
+    want = sum(h["w_index"][:, i, None].astype(np.float64) * np.maximum(q[:, i] @ k.T, 0)
+               for i in range(heads))
+    assert rel_l2(host(s), want) <= 1e-6   # fp32 sums of exact products
