@@ -1,6 +1,6 @@
 // bf16 split-KV forward for head_dim = 256 on gfx950 (Eq. qwen-local-attn).
 //
-// Workgroup = 8 waves (4 for pages shorter than a tile) = 32 packed query rows
+// Workgroup = 8 waves (4 for few rows or the shortest pages) = 32 packed query rows
 // per wave of one KV head: packed row r is (token r / G, head g*G + r % G), so
 // every K/V tile staged in LDS feeds all G query heads that share it.  Lane l
 // owns row l % 32 (scores are computed transposed, S^T = K Q^T, so row
@@ -224,13 +224,13 @@ __device__ __forceinline__ void rescale_pv(const char* Vs, const OnlineSoftmax& 
 // lets it keep LDS reads running while the direct loads into `next` are in
 // flight.  `pe` holds the page-table entry of t0_next on entry and that of
 // t0_after on return.
-template <bool kPerKey, bool kFirst, bool kOverlap, int kInstr, int kAheadK, int kAheadV>
+template <PageForm kForm, bool kFirst, bool kOverlap, int kInstr, int kAheadK, int kAheadV>
 __device__ __forceinline__ void step(const FwdArgs& a, char* __restrict__ next,
                                      const char* __restrict__ ks_cur,
                                      const char* __restrict__ vs_prev, const TileFetchN<kInstr>& kf,
                                      const TileFetchN<kInstr>& vf, const PageLookup& pl, int32_t& pe,
                                      int64_t t0_next, int64_t t0_after, int64_t k_hi, int64_t t0,
-                                     int64_t k_lo, int64_t kb, int64_t k_all, int lim_rel,
+                                     int64_t k_lo, int64_t kb, int64_t k_all, int lim_rel, int w,
                                      const bf16x8* qreg,
                                      const TileBase& to, int hh, f32x16* oacc, f32x16& s_prev,
                                      f32x16& s_out,
@@ -246,20 +246,22 @@ __device__ __forceinline__ void step(const FwdArgs& a, char* __restrict__ next,
     if constexpr (kDefer > 0) tail.run(oacc);
   };
   f32x16 s;
-  if (kPerKey) {
+  if (kForm == kRowPage) {
     kf.issue_rows(next, a.page_table, a.log2_page, t0_next, k_hi);
     vf.issue_rows(next + kTileBytes, a.page_table, a.log2_page, t0_next, k_hi);
     s = scores<0, kAheadK>(ks_cur, qreg, to, [](int) {}, valu, pre);
   } else {
-    const int64_t prow_next = pl.row(pe, t0_next);
-    pe = pl.load(t0_after);
+    using Fetch = TileFetchN<kInstr>;
+    const int64_t pos_next = Fetch::template lookup_pos<kForm>(t0_next, k_hi, w);
+    const int64_t prow_next = pl.row(pe, pos_next);
+    pe = pl.load(Fetch::template lookup_pos<kForm>(t0_after, k_hi, w));
     // the entry load stays ahead of the stage's loads; with one wave per SIMD
     // (kSpread) ALU work may cross, so the next stage's descriptors are built
     // among the MFMAs (as in dq)
     if (kOverlap) __builtin_amdgcn_sched_barrier(0x0006);
     else __builtin_amdgcn_sched_barrier(0);
     const __amdgpu_buffer_rsrc_t rk = kf.page_rsrc(prow_next), rv = vf.page_rsrc(prow_next);
-    const int nv = (int)min(k_hi - t0_next, (int64_t)kBN);
+    const int nv = (int)min(k_hi - pos_next, (int64_t)kBN);
     s = scores<2 * kInstr, kAheadK>(ks_cur, qreg, to, [&](int i) {
       if (kOverlap) {
         if (i < kInstr) kf.issue_one_u24(next, rk, i, nv);
@@ -283,7 +285,7 @@ __device__ __forceinline__ void step(const FwdArgs& a, char* __restrict__ next,
 
 // Workgroup = kWaves waves = 32 * kWaves packed rows; with 8 waves two waves
 // share each SIMD (one's VALU and LDS work overlaps the other's MFMAs).
-template <bool kPerKey, int kWaves>
+template <PageForm kForm, int kWaves>
 __global__ __launch_bounds__(64 * kWaves, 1) void fwd_bf16_d256_kernel(FwdArgs a) {
   constexpr int kAhead = kAheadOf<kWaves>, kSlots = kSlotsOf<kWaves>;
   __shared__ __attribute__((aligned(1024))) char smem[kSlots * kStage];
@@ -331,31 +333,33 @@ __global__ __launch_bounds__(64 * kWaves, 1) void fwd_bf16_d256_kernel(FwdArgs a
   }
 
   TileFetchN<kInstr> kf, vf;
-  kf.init(static_cast<const __bf16*>(a.k_pool) + (int64_t)g * kD, a.k_pos_stride, lane, w);
-  vf.init(static_cast<const __bf16*>(a.v_pool) + (int64_t)g * kD, a.v_pos_stride, lane, w);
-  // Tile t lies in one page unless pages are shorter than a tile; in the loop
-  // its page-table entry is loaded one iteration before the fetch, so
-  // consuming it never waits on the direct loads in flight.  The tile that
-  // reaches k_hi takes per-row lookups.
+  kf.template init<kForm>(static_cast<const __bf16*>(a.k_pool) + (int64_t)g * kD, a.k_pos_stride,
+                          lane, w);
+  vf.template init<kForm>(static_cast<const __bf16*>(a.v_pool) + (int64_t)g * kD, a.v_pos_stride,
+                          lane, w);
+  // In the loop a tile's page-table entry is loaded one iteration before the
+  // fetch, so consuming it never waits on the direct loads in flight.
   PageLookup pl;
   pl.init(a.page_table, a.log2_page);
-  auto page_row = [&](int t) -> int64_t {
-    return kPerKey ? 0 : phys_pos_uniform(a.page_table, k_lo + (int64_t)t * kBN, a.log2_page);
+  auto lookup = [&](int64_t t0) {
+    return TileFetchN<kInstr>::template lookup_pos<kForm>(t0, k_hi, w);
   };
-  auto fetch = [&](int t, int slot, int64_t prow) {
-    const int64_t t0 = k_lo + (int64_t)t * kBN;
+  auto fetch = [&](int t, int slot) {
+    const int64_t t0 = k_lo + (int64_t)t * kBN, pos = lookup(t0);
+    const int64_t prow =
+        kForm == kRowPage ? 0 : phys_pos_uniform(a.page_table, pos, a.log2_page);
     char* st = smem + slot * kStage;
-    kf.template issue<kPerKey>(st, a.page_table, a.log2_page, t0, k_hi, prow);
-    vf.template issue<kPerKey>(st + kTileBytes, a.page_table, a.log2_page, t0, k_hi, prow);
+    kf.template issue<kForm>(st, a.page_table, a.log2_page, t0, k_hi, pos, prow);
+    vf.template issue<kForm>(st + kTileBytes, a.page_table, a.log2_page, t0, k_hi, pos, prow);
   };
   const TileBase to = tile_base(lane);
   // tiles past the last one are clamped to it (refetched into an unread slot),
   // so every iteration issues exactly one stage of direct loads
   auto clamp = [&](int t) { return t < n_tiles ? t : n_tiles - 1; };
 #pragma unroll
-  for (int i = 0; i < kAhead; ++i) fetch(clamp(i), i, page_row(clamp(i)));
+  for (int i = 0; i < kAhead; ++i) fetch(clamp(i), i);
   auto tile0 = [&](int t) { return k_lo + (int64_t)clamp(t) * kBN; };
-  int32_t pe = kPerKey ? 0 : pl.load(tile0(kAhead));
+  int32_t pe = kForm == kRowPage ? 0 : pl.load(lookup(tile0(kAhead)));
 
   // Q^T operand: lane holds q[row][16*ks + 8*hh .. +7]
   bf16x8 qreg[16];
@@ -397,19 +401,19 @@ __global__ __launch_bounds__(64 * kWaves, 1) void fwd_bf16_d256_kernel(FwdArgs a
   // and the last tile's softmax and PV follow the loop.
   auto st = [&](int t, f32x16& s_in, f32x16& s_out) {
     const int64_t t0 = k_lo + (int64_t)t * kBN;
-    step<kPerKey, false, kOverlap, kInstr, kAK, kAV>(
+    step<kForm, false, kOverlap, kInstr, kAK, kAV>(
         a, smem + ((t + kAhead) % kSlots) * kStage, smem + (t % kSlots) * kStage,
         smem + ((t + kSlots - 1) % kSlots) * kStage + kTileBytes, kf, vf, pl, pe, tile0(t + kAhead),
-        tile0(t + kAhead + 1), k_hi, t0, k_lo, kb, k_all, lim_rel, qreg, to, hh, oacc, s_in, s_out,
+        tile0(t + kAhead + 1), k_hi, t0, k_lo, kb, k_all, lim_rel, w, qreg, to, hh, oacc, s_in, s_out,
         m_run, l_run, tail);
     wait_vmcnt<(kAhead - 1) * 2 * kInstr>();
     __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the step's LDS reads have landed
     tile_barrier();
   };
   if constexpr (kOverlap) {
-    step<kPerKey, true, kOverlap, kInstr, kAK, kAV>(
+    step<kForm, true, kOverlap, kInstr, kAK, kAV>(
         a, smem + kAhead * kStage, smem, smem + kTileBytes, kf, vf, pl, pe, tile0(kAhead),
-        tile0(kAhead + 1), k_hi, k_lo, k_lo, kb, k_all, lim_rel, qreg, to, hh, oacc, s_b, s_a,
+        tile0(kAhead + 1), k_hi, k_lo, k_lo, kb, k_all, lim_rel, w, qreg, to, hh, oacc, s_b, s_a,
         m_run, l_run, tail);
     wait_vmcnt<(kAhead - 1) * 2 * kInstr>();
     __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the step's LDS reads have landed
@@ -461,25 +465,31 @@ __global__ __launch_bounds__(64 * kWaves, 1) void fwd_bf16_d256_kernel(FwdArgs a
 #define LS_FWD_WAVES 8
 #endif
 
-template <bool kPerKey, int kWaves>
+template <PageForm kForm, int kWaves>
 hipError_t launch_waves(const FwdArgs& a, hipStream_t stream) {
   constexpr int kBM = 32 * kWaves;
   const unsigned row_tiles = (unsigned)(((int64_t)a.n_q * a.group + kBM - 1) / kBM);
   const dim3 grid(row_tiles, a.n_kv_heads, a.n_splits);
-  hipLaunchKernelGGL((fwd_bf16_d256_kernel<kPerKey, kWaves>), grid, dim3(64 * kWaves), 0, stream, a);
+  hipLaunchKernelGGL((fwd_bf16_d256_kernel<kForm, kWaves>), grid, dim3(64 * kWaves), 0, stream, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
-// Pages of at least one tile take the two-waves-per-SIMD kernel; shorter
-// pages (one lookup per key row, more registers) take four waves, and so do
-// calls with at most 128 packed rows, which would leave half of a 256-row
-// workgroup empty.
+// Calls with more than 128 packed rows take the two-waves-per-SIMD kernel; with
+// fewer, half of its 256-row workgroup would be empty, and four waves do.
+// Pages of 4 rows or fewer (one lookup per key row, more registers) always take
+// four.  Pages of 8 and 16 rows measured 2,421 -> 1,949 us with the lookup per wave
+// instead of per row (1,111 rows x 100,000 keys; 1,844 with pages of 64).
 hipError_t launch_fwd_bf16_d256(const FwdArgs& a, hipStream_t stream) {
-  if (a.log2_page < 5) return launch_waves<true, 4>(a, stream);
-  if ((int64_t)a.n_q * a.group <= 128) return launch_waves<false, 4>(a, stream);
-  return launch_waves<false, LS_FWD_WAVES>(a, stream);
+  const PageForm form = page_form(a.log2_page);
+  if (form == kRowPage) return launch_waves<kRowPage, 4>(a, stream);
+  const bool few = (int64_t)a.n_q * a.group <= 128;
+  if (form == kWavePage)
+    return few ? launch_waves<kWavePage, 4>(a, stream)
+               : launch_waves<kWavePage, LS_FWD_WAVES>(a, stream);
+  return few ? launch_waves<kTilePage, 4>(a, stream)
+             : launch_waves<kTilePage, LS_FWD_WAVES>(a, stream);
 }
 
 }  // namespace ls

@@ -267,16 +267,37 @@ struct PageLookup {
 // the resource base and 32-bit lane offsets.  Unlike the FLAT-encoded
 // global_load_lds, these do not count as possible out-of-order LDS accesses
 // for the compiler's wait insertion, so LDS reads issued while they are in
-// flight keep partial waits.  Pages shorter than a tile use the per-row FLAT
-// form.
+// flight keep partial waits.  The same serves pages of 8 and 16 rows, where the
+// rows that one wave loads (8, or 4 with eight waves, at a multiple of as many)
+// still lie in one page: each wave then looks its own rows' page up.  Shorter
+// pages use the per-row FLAT form.
+enum PageForm {
+  kTilePage,   // a tile lies in one page (32 rows or more)
+  kWavePage,   // a wave's rows of a tile do (8 or 16)
+  kRowPage     // a lookup per row (4 or fewer)
+};
+inline PageForm page_form(int log2_page) {
+  return log2_page >= 5 ? kTilePage : log2_page >= 3 ? kWavePage : kRowPage;
+}
 template <int kInstr = 4>   // 1 KiB instructions per wave per 16 KiB tile (16 / waves)
 struct TileFetchN {
   const char* pool;    // pool base + KV head offset (bytes)
   int64_t row_bytes;   // bytes between positions
   int lane_off[kInstr];  // byte offset (logical chunk * 16) of the lane's source in its row
   int lds_row[kInstr];   // first LDS row written by instruction i
-  int lane_row[kInstr];  // row carried by this lane in instruction i
+  int lane_row[kInstr];  // row carried by this lane in instruction i, counted from the row
+                         // whose page is looked up (the tile's first; kWavePage: the wave's)
 
+  // First row of a tile that wave w loads.
+  __host__ __device__ static inline int wave_row(int w) { return 2 * kInstr * w; }
+  // Position whose page is looked up for wave w's loads of the tile at t0: its
+  // first one, which at the range's end may lie past the last key.
+  template <PageForm kForm>
+  __device__ __forceinline__ static int64_t lookup_pos(int64_t t0, int64_t k_hi, int w) {
+    return kForm == kWavePage ? min(t0 + wave_row(w), k_hi - 1) : t0;
+  }
+
+  template <PageForm kForm = kTilePage>
   __host__ __device__ inline void init(const void* pool_head, int64_t pos_stride_elems, int lane,
                                         int w) {
     pool = static_cast<const char*>(pool_head);
@@ -286,6 +307,7 @@ struct TileFetchN {
       lds_row[i] = 2 * kInstr * w + 2 * i;
       lane_row[i] = lds_row[i] + (lane >> 5);
       lane_off[i] = ((lane & 31) ^ tile_swz(lane_row[i])) * 16;
+      if (kForm == kWavePage) lane_row[i] -= wave_row(w);
     }
   }
 
@@ -296,8 +318,8 @@ struct TileFetchN {
   }
 
   // Load instruction i (< kInstr) of a tile inside one page (resource from
-  // page_rsrc of its first row); rows at or beyond n_valid (1 <= n_valid <= 32)
-  // repeat row n_valid - 1.  32 rows of a page span less than 2 GiB, so the
+  // page_rsrc of the row looked up); rows at or beyond n_valid (1 <= n_valid <=
+  // 32, from that row on) repeat row n_valid - 1.  32 rows of a page span less than 2 GiB, so the
   // lane offsets are 32-bit.
   __device__ __forceinline__ void issue_one(char* tile, __amdgpu_buffer_rsrc_t r, int i,
                                             int n_valid) const {
@@ -338,14 +360,14 @@ struct TileFetchN {
     }
   }
 
-  // Tile [t0, t0 + 32) with k_hi > t0: page path unless pages are shorter than a tile.
-  template <bool kPerKey>
+  // Tile [t0, t0 + 32) with k_hi > t0; pos = lookup_pos, prow its physical row.
+  template <PageForm kForm>
   __device__ __forceinline__ void issue(char* tile, const int32_t* table, int log2_page, int64_t t0,
-                                        int64_t k_hi, int64_t prow) const {
-    if (kPerKey) {
+                                        int64_t k_hi, int64_t pos, int64_t prow) const {
+    if (kForm == kRowPage) {
       issue_rows(tile, table, log2_page, t0, k_hi);
     } else {
-      issue_page(tile, prow, (int)min(k_hi - t0, (int64_t)kTileKeys));
+      issue_page(tile, prow, (int)min(k_hi - pos, (int64_t)kTileKeys));
     }
   }
 };

@@ -80,7 +80,7 @@ def fine_splits(cfg, splits):
     x 262,144 (198 workgroups) gain nothing (421, 434, 430 us for 1, 2, 4), so a
     cut must promise 8%; 4,096 rows fill 33 rounds and stay whole."""
     rows = cfg.resp_len * cfg.group
-    per_wg = 256 if cfg.dtype == "bf16" and cfg.page_size >= 32 and rows > 128 else 128
+    per_wg = 256 if cfg.dtype == "bf16" and cfg.page_size >= 8 and rows > 128 else 128
     prefix = [r for sp in splits[:-1] for r in sp]
     if not prefix:
         return splits

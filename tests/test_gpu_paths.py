@@ -234,3 +234,23 @@ def test_dsa_scores_chunks(R, P, heads):
     want = sum(h["w_index"][:, i, None].astype(np.float64) * np.maximum(q[:, i] @ k.T, 0)
                for i in range(heads))
     assert rel_l2(host(s), want) <= 1e-6   # fp32 sums of exact products
+
+
+@pytest.mark.parametrize("page", [4, 8, 16])
+@pytest.mark.parametrize("R", [15, 77], ids=["four_waves", "eight_waves"])
+def test_bf16_short_pages(page, R):
+    """Pages shorter than a key tile: a wave's rows in one page (8 and 16), or a
+    lookup per row (4).  Splits and ranges begin and end inside pages, tiles and
+    waves' rows; the last ones hold 1, 5 and 9 keys of a tile."""
+    from paper_2607_14952_amd import inputs
+    from paper_2607_14952_amd.replay import device_inputs
+    from tests.test_gpu_parity import check_backward, check_forward
+    cfg = _bf16(f"page{page}_r{R}", 1_003, R, page=page)
+    h = inputs.dense_inputs(cfg)
+    dev = device_inputs(h)
+    P = cfg.prefix_len
+    splits = [(0, 32), (32, 33), (33, 69), (69, 500), (500, 521), (521, 1_001), (1_001, P),
+              (P, P + 7), (P + 7, P + R)]
+    out, lse, o_ref, l_ref = check_forward(cfg, h, dev, splits, P=P, q_pos0=P)
+    check_backward(cfg, h, dev, out, lse, o_ref, l_ref,
+                   [(0, 41), (41, 42), (42, 777), (777, P + 5), (P + 5, P + R)], P=P, q_pos0=P)
