@@ -229,6 +229,21 @@ ls_status ls_prefix_attn_bwd(const ls_attn_params* p, int64_t kv_begin, int64_t 
                              void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * ls_prefix_attn_bwd_ranges: ls_prefix_attn_bwd over several key ranges (host
+ * array, in the order given) in one call, with the result, to the bit, of one
+ * call per range where the calls after the first add LS_FLAG_ACCUMULATE_DQ and
+ * LS_FLAG_PREP_READY.  Ranges that would leave CUs idle share launches.  Empty
+ * ranges contribute nothing; dk_resp / dv_resp are needed when any range holds
+ * a response key, and ranges that hold the same one need
+ * LS_FLAG_ACCUMULATE_DKV, as calls do.
+ */
+ls_status ls_prefix_attn_bwd_ranges(const ls_attn_params* p, const ls_split* ranges,
+                                    int32_t n_ranges, const void* d_out, const void* out,
+                                    int32_t out_dtype, const float* lse, float* dq,
+                                    float* dk_resp, float* dv_resp, void* workspace,
+                                    size_t workspace_bytes, void* stream);
+
+/*
  * Sparse latent replay (MLA keys with a DSA-style selection; Eq. dsa-attention,
  * Sec. "Layer Anatomy: MLA/DSA Before Dense or Routed FFNs"): one latent row of
  * head_dim = 576 bf16 per position (n_kv_heads = 1, v_pool == k_pool); keys are

@@ -24,7 +24,7 @@ STATUS = {0: "LS_OK", -1: "LS_ERR_INVALID_ARG", -2: "LS_ERR_UNSUPPORTED", -3: "L
           -4: "LS_ERR_ALIAS", -5: "LS_ERR_STALE", -6: "LS_ERR_PAGE_OOB", -7: "LS_ERR_HIP"}
 EXPORTS = ["ls_abi_version", "ls_status_string", "ls_last_error", "ls_gather_kv", "ls_scatter_kv",
            "ls_prefix_attn_fwd", "ls_lse_merge", "ls_lse_merge_groups",
-           "ls_prefix_attn_bwd_workspace_size", "ls_prefix_attn_bwd", "ls_sparse_attn_workspace_size",
+           "ls_prefix_attn_bwd_workspace_size", "ls_prefix_attn_bwd", "ls_prefix_attn_bwd_ranges", "ls_sparse_attn_workspace_size",
            "ls_sparse_attn_fwd", "ls_sparse_attn_bwd", "ls_dsa_index_scores", "ls_topk_select",
            "ls_topk_select_ws", "ls_topk_workspace_size",
            "ls_hbm_read_probe", "ls_sparse_attn_fwd_noalloc"]
@@ -94,6 +94,10 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.ls_prefix_attn_bwd.restype = c_int32
     lib.ls_prefix_attn_bwd.argtypes = [P, c_int64, c_int64, c_void_p, c_void_p, c_int32, c_void_p,
                                        c_void_p, c_void_p, c_void_p, c_void_p, c_size_t, c_void_p]
+    lib.ls_prefix_attn_bwd_ranges.restype = c_int32
+    lib.ls_prefix_attn_bwd_ranges.argtypes = [P, POINTER(Split), c_int32, c_void_p, c_void_p,
+                                              c_int32, c_void_p, c_void_p, c_void_p, c_void_p,
+                                              c_void_p, c_size_t, c_void_p]
     lib.ls_sparse_attn_workspace_size.restype = c_size_t
     lib.ls_sparse_attn_workspace_size.argtypes = [P, c_int32, c_int32]
     lib.ls_sparse_attn_fwd.restype = c_int32
@@ -324,14 +328,25 @@ def prefix_attn_bwd(q, kv: PagedKV, d_out, out, lse, *, prefix_len: int, q_pos0:
                     stream=None):
     """ls_prefix_attn_bwd: dq over keys [kv_begin, kv_end) and dK/dV of the
     response keys in that range (rows j - prefix_len of dk_resp / dv_resp)."""
+    kv_end = q_pos0 + q.shape[0] if kv_end is None else kv_end
+    return prefix_attn_bwd_ranges(q, kv, d_out, out, lse, [(kv_begin, kv_end)],
+                                  prefix_len=prefix_len, q_pos0=q_pos0, scale=scale, flags=flags,
+                                  dq=dq, dk_resp=dk_resp, dv_resp=dv_resp, workspace=workspace,
+                                  expected_epoch=expected_epoch, stream=stream)
+
+
+def prefix_attn_bwd_ranges(q, kv: PagedKV, d_out, out, lse, ranges, *, prefix_len: int,
+                           q_pos0: int, scale: float, flags: int = 0, dq=None, dk_resp=None,
+                           dv_resp=None, workspace=None, expected_epoch=None, stream=None):
+    """ls_prefix_attn_bwd_ranges: dq over the key ranges, accumulated in the order
+    given, and dK/dV of the response keys in them."""
     torch = _torch()
     R, Hq, D = q.shape
     Hkv, Dv = kv.k_pool.shape[2], kv.v_pool.shape[3]
     kv_len = q_pos0 + R
-    kv_end = kv_len if kv_end is None else kv_end
     if dq is None:
         dq = torch.empty((R, Hq, D), dtype=torch.float32, device=q.device)
-    if kv_end > prefix_len:
+    if any(e > prefix_len for _, e in ranges):
         n_resp = kv_len - prefix_len
         if dk_resp is None:
             dk_resp = torch.zeros((n_resp, Hkv, D), dtype=torch.float32, device=q.device)
@@ -341,9 +356,11 @@ def prefix_attn_bwd(q, kv: PagedKV, d_out, out, lse, *, prefix_len: int, q_pos0:
         workspace = bwd_workspace(q, kv, prefix_len=prefix_len, q_pos0=q_pos0)
     p = make_params(q, kv, prefix_len=prefix_len, q_pos0=q_pos0, scale=scale, flags=flags,
                     expected_epoch=expected_epoch)
+    n = len(ranges)
+    arr = (Split * n)(*[Split(int(b), int(e)) for b, e in ranges])
     f32 = torch.float32
-    check(load_library().ls_prefix_attn_bwd(
-        ctypes.byref(p), kv_begin, kv_end, _ptr(d_out, q.dtype, "d_out"), _ptr(out, None, "out"),
+    check(load_library().ls_prefix_attn_bwd_ranges(
+        ctypes.byref(p), arr, n, _ptr(d_out, q.dtype, "d_out"), _ptr(out, None, "out"),
         _dtype_code(out), _ptr(lse, f32, "lse"), _ptr(dq, f32, "dq"),
         _ptr(dk_resp, f32, "dk_resp"), _ptr(dv_resp, f32, "dv_resp"),
         _ptr(workspace, None, "workspace"), workspace.numel() * workspace.element_size(),

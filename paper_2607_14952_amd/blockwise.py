@@ -10,7 +10,7 @@ blocks), and the pages are popped afterwards.  The prefix pages are never
 written and never get a gradient.
 
 Every step runs in the library: ls_scatter_kv (append), ls_prefix_attn_fwd,
-ls_lse_merge and ls_prefix_attn_bwd.
+ls_lse_merge and ls_prefix_attn_bwd_ranges.
 """
 from __future__ import annotations
 
@@ -115,14 +115,13 @@ class BlockwiseReplay:
             self.ws = B.bwd_workspace(q[:c.rows_per_call], self.prefix.kv, prefix_len=c.prefix_len,
                                       q_pos0=c.prefix_len + (c.blocks - 1) * c.rows_per_call)
         dq = self.dq[rows]
-        for r, (kb, ke) in enumerate(self.prefix_ranges + [(c.prefix_len, kv_end)]):
-            B.prefix_attn_bwd(qb, self.prefix.kv, dob, out, lse, prefix_len=c.prefix_len,
-                              q_pos0=q0, scale=c.scale, kv_begin=kb, kv_end=ke,
-                              flags=((B.FLAG_ACCUMULATE_DQ | B.FLAG_PREP_READY) if r else 0)
-                              | (0 if first else B.FLAG_ACCUMULATE_DKV),
-                              dq=dq, dk_resp=self.dk[:kv_end - c.prefix_len],
-                              dv_resp=self.dv[:kv_end - c.prefix_len], workspace=self.ws,
-                              stream=self.stream)
+        B.prefix_attn_bwd_ranges(qb, self.prefix.kv, dob, out, lse,
+                                 self.prefix_ranges + [(c.prefix_len, kv_end)],
+                                 prefix_len=c.prefix_len, q_pos0=q0, scale=c.scale,
+                                 flags=0 if first else B.FLAG_ACCUMULATE_DKV, dq=dq,
+                                 dk_resp=self.dk[:kv_end - c.prefix_len],
+                                 dv_resp=self.dv[:kv_end - c.prefix_len], workspace=self.ws,
+                                 stream=self.stream)
 
     def run_member(self, resp_dev: dict, keep=None, block_events=None):
         """append -> blocks in reverse -> pop; returns (dq, dk, dv) of the member.

@@ -431,11 +431,11 @@ BwdWorkspace bwd_workspace_layout(const ls_attn_params* p) {
   if (p->dtype == LS_BF16) {
     w.part_bytes = (size_t)ls::dkdv_row_chunks(p->n_q, group) * 2 * p->n_kv_heads *
                    (size_t)n_resp * p->head_dim * 4;
-    w.dq_bytes = (size_t)ls::dq_part_rows(p->n_q, group) * p->head_dim * 4;
+    w.dq_bytes = ls::dq_part_bytes(p->n_q, group, p->head_dim);
   } else if (ls::f32_mfma_fits(p->head_dim, p->head_dim_v, p->n_kv_heads)) {
     w.part_bytes = pad((size_t)ls::f32_dkdv_chunks(p->n_q, group) * p->n_kv_heads *
                        (size_t)n_resp * (p->head_dim + p->head_dim_v) * 4);
-    w.dq_bytes = (size_t)ls::dq_part_rows(p->n_q, group) * p->head_dim * 4;
+    w.dq_bytes = ls::dq_part_bytes(p->n_q, group, p->head_dim);
   }
   return w;
 }
@@ -445,20 +445,98 @@ LS_API size_t ls_prefix_attn_bwd_workspace_size(const ls_attn_params* p) {
   return bwd_workspace_layout(p).total();
 }
 
+namespace {
+// The launches of a backward over `ranges` (non-empty ones), in order: ranges
+// whose plan says so share dq launches, as many at a time as the partial sums
+// have room for.  A range keeps the chunks it would have alone
+// and the sums keep their order, so the result is that of a call per range.
+hipError_t launch_backward(ls::BwdArgs& a, bool bf16, const std::vector<ls_split>& ranges,
+                           size_t part_bytes, hipStream_t s) {
+  hipError_t e = hipSuccess;
+  auto key0 = [&](const ls_split& r) { return std::max(r.kv_begin, a.prefix_len); };
+  if (!bf16 && !ls::f32_mfma_fits(a.head_dim, a.head_dim_v, a.n_kv_heads)) {
+    for (const ls_split& r : ranges) {
+      a.kv_begin = r.kv_begin;
+      a.kv_end = r.kv_end;
+      if ((e = ls::launch_bwd_f32_generic(a, key0(r), s)) != hipSuccess) return e;
+      a.accumulate_dq = 1;
+    }
+    return e;
+  }
+  const int64_t n = (int64_t)a.n_q * a.n_q_heads * a.head_dim;   // values of one partial dq
+  const int64_t room = (int64_t)(part_bytes / 4) / n;
+  for (size_t i = 0; i < ranges.size();) {
+    ls::DqRanges r;
+    r.n = 0;
+    r.z0[0] = 0;
+    int form = 0;
+    for (; i < ranges.size() && r.n < ls::kMaxDqRanges; ++i) {
+      const int64_t begin = ranges[i].kv_begin, end = ranges[i].kv_end;
+      const ls::DqPlan p = bf16 ? ls::plan_dq_bf16_d256(a, begin, end)
+                                : ls::plan_dq_f32_mfma(a, begin, end);
+      if (r.n > 0 && (!p.joins || p.form != form || r.z0[r.n] + p.chunks > room)) break;
+      form = p.form;
+      r.begin[r.n] = p.begin;
+      r.end[r.n] = p.end;
+      r.per[r.n] = p.per;
+      r.z0[r.n + 1] = r.z0[r.n] + p.chunks;
+      ++r.n;
+      if (!p.joins) {
+        ++i;
+        break;
+      }
+    }
+    float* part = r.z0[r.n] > 1 ? a.dq_part : nullptr;
+    e = bf16 ? ls::launch_dq_bf16_d256(a, r, part, s) : ls::launch_dq_f32_mfma(a, r, form, part, s);
+    if (e == hipSuccess && part)
+      e = ls::launch_dq_reduce(part, r, n, a.scale, a.accumulate_dq != 0, a.dq, s);
+    if (e != hipSuccess) return e;
+    a.accumulate_dq = 1;
+  }
+  for (const ls_split& r : ranges) {
+    if (r.kv_end <= a.prefix_len) continue;
+    a.kv_begin = r.kv_begin;
+    a.kv_end = r.kv_end;
+    e = bf16 ? ls::launch_dkdv_bf16_d256(a, key0(r), s) : ls::launch_dkdv_f32_mfma(a, key0(r), s);
+    if (e != hipSuccess) return e;
+  }
+  return e;
+}
+}  // namespace
+
 LS_API ls_status ls_prefix_attn_bwd(const ls_attn_params* p, int64_t kv_begin, int64_t kv_end,
                                     const void* d_out, const void* out, int32_t out_dtype,
                                     const float* lse, float* dq, float* dk_resp, float* dv_resp,
                                     void* workspace, size_t workspace_bytes, void* stream) {
+  const ls_split range = {kv_begin, kv_end};
+  return ls_prefix_attn_bwd_ranges(p, &range, 1, d_out, out, out_dtype, lse, dq, dk_resp, dv_resp,
+                                   workspace, workspace_bytes, stream);
+}
+
+LS_API ls_status ls_prefix_attn_bwd_ranges(const ls_attn_params* p, const ls_split* ranges,
+                                           int32_t n_ranges, const void* d_out, const void* out,
+                                           int32_t out_dtype, const float* lse, float* dq,
+                                           float* dk_resp, float* dv_resp, void* workspace,
+                                           size_t workspace_bytes, void* stream) {
   ls_status st = check_params(p, true);
   if (st != LS_OK) return st;
   if ((st = check_supported(p)) != LS_OK) return st;
   if (out_dtype != LS_BF16 && out_dtype != LS_F32)
     return fail(LS_ERR_UNSUPPORTED, "out_dtype %d", out_dtype);
   const int64_t kv_len = kv_len_of(p);
-  if (kv_begin < 0 || kv_end < kv_begin || kv_end > kv_len)
-    return fail(LS_ERR_INVALID_ARG, "key range [%lld, %lld) outside [0, %lld)",
-                (long long)kv_begin, (long long)kv_end, (long long)kv_len);
-  if (p->n_q == 0 || kv_end == kv_begin) return LS_OK;
+  if (!ranges || n_ranges <= 0) return fail(LS_ERR_INVALID_ARG, "need at least one key range");
+  std::vector<ls_split> todo;   // the non-empty ones
+  int64_t kv_end = 0;
+  for (int32_t i = 0; i < n_ranges; ++i) {
+    const ls_split& r = ranges[i];
+    if (r.kv_begin < 0 || r.kv_end < r.kv_begin || r.kv_end > kv_len)
+      return fail(LS_ERR_INVALID_ARG, "key range [%lld, %lld) outside [0, %lld)",
+                  (long long)r.kv_begin, (long long)r.kv_end, (long long)kv_len);
+    if (r.kv_end == r.kv_begin) continue;
+    todo.push_back(r);
+    kv_end = std::max(kv_end, r.kv_end);
+  }
+  if (p->n_q == 0 || todo.empty()) return LS_OK;
   const bool has_resp = kv_end > p->prefix_len;
   if (!d_out || !out || !lse || !dq)
     return fail(LS_ERR_INVALID_ARG, "NULL device pointer (d_out/out/lse/dq)");
@@ -515,8 +593,6 @@ LS_API ls_status ls_prefix_attn_bwd(const ls_attn_params* p, int64_t kv_begin, i
   a.dq_part = wl.dq_bytes ? (float*)((char*)workspace + 2 * wl.stat_bytes + wl.part_bytes) : nullptr;
   a.q_pos0 = p->q_pos0;
   a.prefix_len = p->prefix_len;
-  a.kv_begin = kv_begin;
-  a.kv_end = kv_end;
   a.k_pos_stride = (int64_t)p->n_kv_heads * p->head_dim;
   a.v_pos_stride = (int64_t)p->n_kv_heads * p->head_dim_v;
   a.n_q = p->n_q;
@@ -533,8 +609,7 @@ LS_API ls_status ls_prefix_attn_bwd(const ls_attn_params* p, int64_t kv_begin, i
   a.accumulate_dkv = (p->flags & LS_FLAG_ACCUMULATE_DKV) ? 1 : 0;
   const int64_t packed = (int64_t)p->n_q * a.group, chunks = ls::dkdv_row_chunks(p->n_q, a.group);
   a.dkdv_rows = (int32_t)(((packed + chunks - 1) / chunks + 31) / 32 * 32);
-  e = p->dtype == LS_BF16 ? ls::launch_bwd_bf16_d256(a, true, has_resp, s)
-                          : ls::launch_bwd_f32(a, true, has_resp, s);
+  e = launch_backward(a, p->dtype == LS_BF16, todo, wl.dq_bytes, s);
   return e == hipSuccess ? LS_OK : hip_fail(e, "backward launch");
 }
 
@@ -844,9 +919,14 @@ LS_API ls_status ls_sparse_attn_bwd(const ls_attn_params* p, const int32_t* idx,
     e = ls::launch_bwd_prep(d_out, out, true, out_dtype == LS_BF16, lse, p->n_q, p->n_q_heads,
                             512, delta, lse2, s);
   if (e == hipSuccess) e = ls::launch_sparse_bwd(a, chunks, s);
-  if (e == hipSuccess && chunks > 1)
-    e = ls::launch_dq_reduce(a.dq, chunks, (int64_t)rows * 576, p->softmax_scale,
+  if (e == hipSuccess && chunks > 1) {
+    ls::DqRanges one;
+    one.n = 1;
+    one.z0[0] = 0;
+    one.z0[1] = chunks;
+    e = ls::launch_dq_reduce(a.dq, one, (int64_t)rows * 576, p->softmax_scale,
                              (p->flags & LS_FLAG_ACCUMULATE_DQ) != 0, dq, s);
+  }
   return e == hipSuccess ? LS_OK : hip_fail(e, "sparse backward launch");
 }
 

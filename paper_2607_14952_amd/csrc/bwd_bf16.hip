@@ -230,11 +230,11 @@ __device__ __forceinline__ void dq_step(const BwdArgs& a, char* __restrict__ nex
                                       &tail);
 }
 
-// Workgroup z works on key tiles z * tiles_per_chunk .. + tiles_per_chunk - 1 of
-// the range.  With several chunks (part not null) each writes its unscaled sums
-// to part[z] and dq_reduce_kernel adds them in order; dq_chunks chooses.
+// Workgroup z works on a chunk of one of the key ranges.  With `part` each writes
+// its unscaled sums to part[z] and dq_reduce_kernel adds them in order; without,
+// there is one range in one chunk.
 template <PageForm kForm>
-__global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a, int tiles_per_chunk,
+__global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a, DqRanges ranges,
                                                                   float* __restrict__ part) {
   __shared__ __attribute__((aligned(1024))) char smem[kQSlots * kQStage];
 
@@ -256,9 +256,11 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a, int
   const int head = (g << lg) + (prow & ((1 << lg) - 1));
   const int tok_first = row0 >> lg;
   const int tok_last = min(a.n_q - 1, (row0 + kQBM - 1) >> lg);
-  const int64_t c_lo = (a.kv_begin & ~int64_t(kQBN - 1)) + (int64_t)wi.z * tiles_per_chunk * kQBN;
-  const int64_t kb = max(a.kv_begin, c_lo);
-  const int64_t ke = min(a.kv_end, c_lo + (int64_t)tiles_per_chunk * kQBN);
+  const int ri = ranges.of(wi.z);
+  const int64_t kv_begin = ranges.begin[ri], chunk_keys = (int64_t)ranges.per[ri] * kQBN;
+  const int64_t c_lo = (kv_begin & ~int64_t(kQBN - 1)) + (wi.z - ranges.z0[ri]) * chunk_keys;
+  const int64_t kb = max(kv_begin, c_lo);
+  const int64_t ke = min(ranges.end[ri], c_lo + chunk_keys);
   const int64_t k_hi = min(ke, a.q_pos0 + tok_last + 1);
   const int64_t k_all = min(ke, a.q_pos0 + tok_first + 1);
   const int64_t my_lim = min(ke, a.q_pos0 + tok + 1);
@@ -386,12 +388,16 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a, int
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         f32x4* dst = reinterpret_cast<f32x4*>(dq + 32 * db + 8 * q4 + 4 * hh);
+        // (one rounding where it is added, as in dq_reduce_kernel)
         f32x4 v;
-        v[0] = acc[db][4 * q4 + 0] * c;
-        v[1] = acc[db][4 * q4 + 1] * c;
-        v[2] = acc[db][4 * q4 + 2] * c;
-        v[3] = acc[db][4 * q4 + 3] * c;
-        if (add) v += *dst;
+        if (add) {
+          const f32x4 old = *dst;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = fmaf(acc[db][4 * q4 + e], c, old[e]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = acc[db][4 * q4 + e] * c;
+        }
         *dst = v;
       }
     }
@@ -657,53 +663,54 @@ int dq_chunks(const BwdArgs& a, int64_t items, int64_t tiles) {
 
 }  // namespace
 
-hipError_t launch_bwd_bf16_d256(const BwdArgs& a, bool need_dq, bool need_dkv,
-                                hipStream_t stream) {
-  if (need_dq) {
-    const unsigned row_tiles = (unsigned)(((int64_t)a.n_q * a.group + kQBM - 1) / kQBM);
-    const int64_t tiles = (a.kv_end - (a.kv_begin & ~int64_t(kQBN - 1)) + kQBN - 1) / kQBN;
-    const int want = dq_chunks(a, (int64_t)row_tiles * a.n_kv_heads, tiles);
-    const int per = (int)((tiles + want - 1) / want);
-    const int n_chunks = (int)((tiles + per - 1) / per);
-    float* part = n_chunks > 1 ? a.dq_part : nullptr;
-    const dim3 grid(row_tiles, a.n_kv_heads, n_chunks);
-    // (pages of 8 and 16 rows: 2,336 -> 1,962 us per shard with the lookup per wave
-    // instead of per row, 2,048 rows x 50,000 keys, as with longer pages)
-    switch (page_form(a.log2_page)) {
-      case kTilePage:
-        hipLaunchKernelGGL(bwd_dq_bf16_d256_kernel<kTilePage>, grid, dim3(256), 0, stream, a, per,
-                           part);
-        break;
-      case kWavePage:
-        hipLaunchKernelGGL(bwd_dq_bf16_d256_kernel<kWavePage>, grid, dim3(256), 0, stream, a, per,
-                           part);
-        break;
-      case kRowPage:
-        hipLaunchKernelGGL(bwd_dq_bf16_d256_kernel<kRowPage>, grid, dim3(256), 0, stream, a, per,
-                           part);
-        break;
-    }
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess && part) e = launch_dq_reduce(a, n_chunks, stream);
-    if (e != hipSuccess) return e;
+DqPlan plan_dq_bf16_d256(const BwdArgs& a, int64_t begin, int64_t end) {
+  const int64_t items = ((int64_t)a.n_q * a.group + kQBM - 1) / kQBM * a.n_kv_heads;
+  const int64_t tiles = (end - (begin & ~int64_t(kQBN - 1)) + kQBN - 1) / kQBN;
+  const int want = dq_chunks(a, items, tiles);
+  const int per = (int)((tiles + want - 1) / want);
+  const int chunks = (int)((tiles + per - 1) / per);
+  // Ranges of no more than one round of workgroups share launches: without the
+  // gaps and ragged ends between them, 10 tokens over 8 ranges of 625 keys 166 ->
+  // 49 us, 77 over 8 of 32,768 634 -> 577, 952 over the same 5,183 -> 5,116.  A
+  // range of several rounds keeps its own, so that the row tiles that share keys
+  // stay together (1,111 tokens, 8 ranges of 12,500: 2,731 us apart, 2,825 joined),
+  // and one whose single chunk fills half the chip writes its result itself.
+  const int64_t wgs = items * chunks;
+  return DqPlan{begin, end, chunks, per, 0, wgs <= 256 && (chunks > 1 || wgs < 128)};
+}
+
+hipError_t launch_dq_bf16_d256(const BwdArgs& a, const DqRanges& r, float* part,
+                               hipStream_t stream) {
+  const dim3 grid((unsigned)(((int64_t)a.n_q * a.group + kQBM - 1) / kQBM), a.n_kv_heads,
+                  r.z0[r.n]);
+  // (pages of 8 and 16 rows: 2,336 -> 1,962 us per shard with the lookup per wave
+  // instead of per row, 2,048 rows x 50,000 keys, as with longer pages)
+  switch (page_form(a.log2_page)) {
+    case kTilePage:
+      hipLaunchKernelGGL(bwd_dq_bf16_d256_kernel<kTilePage>, grid, dim3(256), 0, stream, a, r, part);
+      break;
+    case kWavePage:
+      hipLaunchKernelGGL(bwd_dq_bf16_d256_kernel<kWavePage>, grid, dim3(256), 0, stream, a, r, part);
+      break;
+    case kRowPage:
+      hipLaunchKernelGGL(bwd_dq_bf16_d256_kernel<kRowPage>, grid, dim3(256), 0, stream, a, r, part);
+      break;
   }
-  if (need_dkv) {
-    const int64_t key0 = a.kv_begin > a.prefix_len ? a.kv_begin : a.prefix_len;
-    const int64_t n_keys = a.kv_end - key0;
-    if (n_keys > 0) {
-      const unsigned blocks = (unsigned)((n_keys + kKeysPerWG - 1) / kKeysPerWG);
-      const int n_chunks = dkdv_row_chunks(a.n_q, a.group);
-      hipLaunchKernelGGL(bwd_dkdv_bf16_d256_kernel, dim3(blocks, a.n_kv_heads, n_chunks),
-                         dim3(256), 0, stream, a, key0, a.kv_end);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-      const int64_t items = n_keys * a.n_kv_heads * (kD / 4);
-      hipLaunchKernelGGL(dkdv_reduce_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0,
-                         stream, a, key0, a.kv_end, n_chunks);
-      return hipGetLastError();
-    }
-  }
-  return hipSuccess;
+  return hipGetLastError();
+}
+
+hipError_t launch_dkdv_bf16_d256(const BwdArgs& a, int64_t key0, hipStream_t stream) {
+  const int64_t n_keys = a.kv_end - key0;
+  const unsigned blocks = (unsigned)((n_keys + kKeysPerWG - 1) / kKeysPerWG);
+  const int n_chunks = dkdv_row_chunks(a.n_q, a.group);
+  hipLaunchKernelGGL(bwd_dkdv_bf16_d256_kernel, dim3(blocks, a.n_kv_heads, n_chunks), dim3(256), 0,
+                     stream, a, key0, a.kv_end);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int64_t items = n_keys * a.n_kv_heads * (kD / 4);
+  hipLaunchKernelGGL(dkdv_reduce_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0,
+                     stream, a, key0, a.kv_end, n_chunks);
+  return hipGetLastError();
 }
 
 }  // namespace ls

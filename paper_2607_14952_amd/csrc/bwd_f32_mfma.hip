@@ -33,7 +33,7 @@ using namespace f32m;
 
 // ============================================================== dq
 template <int kDP, int kRW>
-__global__ __launch_bounds__(256) void bwd_dq_f32_mfma_kernel(BwdArgs a, int tiles_per_chunk,
+__global__ __launch_bounds__(256) void bwd_dq_f32_mfma_kernel(BwdArgs a, DqRanges ranges,
                                                               float* __restrict__ part) {
   constexpr int kKW = 4 / kRW;
   constexpr int kS = kRowS<kDP>;
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(256) void bwd_dq_f32_mfma_kernel(BwdArgs a, int til
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int rw = w % kRW, kw = w / kRW;
   const int j = lane & 31, h = lane >> 5;
-  const int g = blockIdx.y, chunk = blockIdx.z;
+  const int g = blockIdx.y, z = blockIdx.z;   // z: a chunk of one of the key ranges
   const int G = a.group, D = a.head_dim, Dv = a.head_dim_v;
   const int64_t rows_total = (int64_t)a.n_q * G;
   const int64_t row0 = (int64_t)blockIdx.x * (32 * kRW);
@@ -54,16 +54,17 @@ __global__ __launch_bounds__(256) void bwd_dq_f32_mfma_kernel(BwdArgs a, int til
   const int tok = (int)(prow / G);
   const int head = g * G + (int)(prow - (int64_t)tok * G);
   const int tok_last = (int)(min(rows_total, row0 + 32 * kRW) - 1) / G;
-  const int64_t kb = a.kv_begin;
-  const int64_t k_hi = min(a.kv_end, a.q_pos0 + tok_last + 1);
-  const int64_t my_lim = row_ok ? min(a.kv_end, a.q_pos0 + tok + 1) : kb;
+  const int ri = ranges.of(z);
+  const int64_t kb = ranges.begin[ri], kv_end = ranges.end[ri];
+  const int64_t k_hi = min(kv_end, a.q_pos0 + tok_last + 1);
+  const int64_t my_lim = row_ok ? min(kv_end, a.q_pos0 + tok + 1) : kb;
   // below: visible to every row (of a whole row group)
   const int64_t k_all =
-      row0 + 32 * kRW <= rows_total ? min(a.kv_end, a.q_pos0 + (int)(row0 / G) + 1) : kb;
+      row0 + 32 * kRW <= rows_total ? min(kv_end, a.q_pos0 + (int)(row0 / G) + 1) : kb;
   const int64_t k_lo = kb & ~int64_t(31);
   const int all_tiles = k_hi > kb ? (int)((k_hi - k_lo + 31) / 32) : 0;
-  const int t_begin = min(all_tiles, chunk * tiles_per_chunk);
-  const int t_end = min(all_tiles, t_begin + tiles_per_chunk);
+  const int t_begin = min(all_tiles, (z - ranges.z0[ri]) * ranges.per[ri]);
+  const int t_end = min(all_tiles, t_begin + ranges.per[ri]);
 
   const int64_t rh = row_ok ? (int64_t)tok * a.n_q_heads + head : 0;   // (rows past the end: row 0)
   float qv[kDP / 2], dov[kDP / 2];
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(256) void bwd_dq_f32_mfma_kernel(BwdArgs a, int til
   }
   if (row_ok) {
     // a chunk's partial sum (unscaled), or the result when there is one chunk
-    float* dst = part ? part + ((int64_t)chunk * a.n_q * a.n_q_heads + rh) * D : a.dq + rh * D;
+    float* dst = part ? part + ((int64_t)z * a.n_q * a.n_q_heads + rh) * D : a.dq + rh * D;
     const float c = part ? 1.f : a.scale;
     const bool add = !part && a.accumulate_dq;
 #pragma unroll
@@ -287,33 +288,16 @@ __global__ __launch_bounds__(256) void dkdv_f32_reduce_kernel(BwdArgs a, int64_t
 }
 
 template <int kDP>
-hipError_t launch_dq(const BwdArgs& a, hipStream_t stream) {
+void launch_dq(const BwdArgs& a, const DqRanges& r, bool share, float* part, hipStream_t stream) {
   const int64_t rows = (int64_t)a.n_q * a.group;
-  const int64_t n_tiles = (a.kv_end - (a.kv_begin & ~int64_t(31)) + 31) / 32;
-  const int64_t wide = (rows + 127) / 128 * a.n_kv_heads, narrow = (rows + 31) / 32 * a.n_kv_heads;
-  // Chunks of at least 8 (4) key tiles, enough for two workgroups on each CU
-  // and no more than the partial sums have room for.  Four row groups share
-  // a staged tile where that still gives every CU its two workgroups.
-  const int64_t room = dq_part_rows(a.n_q, a.group) / ((int64_t)a.n_q * a.n_q_heads);
-  const bool share = wide * std::min(std::max<int64_t>(room, 1), (n_tiles + 7) / 8) >= 512;
-  const int64_t items = share ? wide : narrow;
-  int64_t want = std::min((512 + items - 1) / items, (n_tiles + (share ? 7 : 3)) / (share ? 8 : 4));
-  want = std::max<int64_t>(1, std::min(want, room));
-  const int64_t unit = share ? 1 : 4;                // whole iterations of the workgroup
-  const int64_t per = ((n_tiles + want - 1) / want + unit - 1) / unit * unit;
-  const int64_t n_chunks = (n_tiles + per - 1) / per;
-  float* part = n_chunks > 1 ? a.dq_part : nullptr;
   if (share)
     hipLaunchKernelGGL((bwd_dq_f32_mfma_kernel<kDP, 4>),
-                       dim3((unsigned)((rows + 127) / 128), a.n_kv_heads, (unsigned)n_chunks),
-                       dim3(256), 0, stream, a, (int)per, part);
+                       dim3((unsigned)((rows + 127) / 128), a.n_kv_heads, r.z0[r.n]), dim3(256), 0,
+                       stream, a, r, part);
   else
     hipLaunchKernelGGL((bwd_dq_f32_mfma_kernel<kDP, 1>),
-                       dim3((unsigned)((rows + 31) / 32), a.n_kv_heads, (unsigned)n_chunks),
-                       dim3(256), 0, stream, a, (int)per, part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !part) return e;
-  return launch_dq_reduce(a, (int)n_chunks, stream);
+                       dim3((unsigned)((rows + 31) / 32), a.n_kv_heads, r.z0[r.n]), dim3(256), 0,
+                       stream, a, r, part);
 }
 
 template <int kDP>
@@ -335,13 +319,37 @@ hipError_t launch_dkdv(const BwdArgs& a, int64_t key0, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_bwd_f32_mfma(const BwdArgs& a, bool need_dq, int64_t key0, hipStream_t stream) {
+DqPlan plan_dq_f32_mfma(const BwdArgs& a, int64_t begin, int64_t end) {
+  const int64_t rows = (int64_t)a.n_q * a.group;
+  const int64_t n_tiles = (end - (begin & ~int64_t(31)) + 31) / 32;
+  const int64_t wide = (rows + 127) / 128 * a.n_kv_heads, narrow = (rows + 31) / 32 * a.n_kv_heads;
+  // Chunks of at least 8 (4) key tiles, enough for two workgroups on each CU
+  // and no more than the partial sums have room for.  Four row groups share
+  // a staged tile where that still gives every CU its two workgroups.
+  const int64_t room = dq_part_rows(a.n_q, a.group) / ((int64_t)a.n_q * a.n_q_heads);
+  const bool share = wide * std::min(std::max<int64_t>(room, 1), (n_tiles + 7) / 8) >= 512;
+  const int64_t items = share ? wide : narrow;
+  int64_t want = std::min((512 + items - 1) / items, (n_tiles + (share ? 7 : 3)) / (share ? 8 : 4));
+  want = std::max<int64_t>(1, std::min(want, room));
+  const int64_t unit = share ? 1 : 4;                // whole iterations of the workgroup
+  const int64_t per = ((n_tiles + want - 1) / want + unit - 1) / unit * unit;
+  const int64_t chunks = (n_tiles + per - 1) / per;
+  // (128 rows, 3 ranges: 63 us apart, 49 in one launch; 500 rows, 590 and 586)
+  return DqPlan{begin, end, (int32_t)chunks, (int32_t)per, share ? 1 : 0,
+                chunks > 1 || items < 128};
+}
+
+hipError_t launch_dq_f32_mfma(const BwdArgs& a, const DqRanges& r, int form, float* part,
+                              hipStream_t stream) {
   const int d = a.head_dim > a.head_dim_v ? a.head_dim : a.head_dim_v;
-  hipError_t e = hipSuccess;
-  if (need_dq)
-    e = d <= 64 ? launch_dq<64>(a, stream) : d <= 96 ? launch_dq<96>(a, stream)
-                                                     : launch_dq<128>(a, stream);
-  if (e != hipSuccess || key0 >= a.kv_end) return e;
+  if (d <= 64) launch_dq<64>(a, r, form == 1, part, stream);
+  else if (d <= 96) launch_dq<96>(a, r, form == 1, part, stream);
+  else launch_dq<128>(a, r, form == 1, part, stream);
+  return hipGetLastError();
+}
+
+hipError_t launch_dkdv_f32_mfma(const BwdArgs& a, int64_t key0, hipStream_t stream) {
+  const int d = a.head_dim > a.head_dim_v ? a.head_dim : a.head_dim_v;
   return d <= 64   ? launch_dkdv<64>(a, key0, stream)
          : d <= 96 ? launch_dkdv<96>(a, key0, stream)
                    : launch_dkdv<128>(a, key0, stream);

@@ -202,22 +202,15 @@ hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_f32(const BwdArgs& a, bool need_dq, bool need_dkv, hipStream_t stream) {
-  const int64_t key0 = need_dkv ? (a.kv_begin > a.prefix_len ? a.kv_begin : a.prefix_len) : a.kv_end;
-  if (f32_mfma_fits(a.head_dim, a.head_dim_v, a.n_kv_heads)) return launch_bwd_f32_mfma(a, need_dq, key0, stream);
-  if (need_dq) {
-    const unsigned blocks = (unsigned)(((int64_t)a.n_q * a.n_q_heads + 3) / 4);
-    hipLaunchKernelGGL(bwd_dq_f32_kernel, dim3(blocks), dim3(256), 0, stream, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
+hipError_t launch_bwd_f32_generic(const BwdArgs& a, int64_t key0, hipStream_t stream) {
+  unsigned blocks = (unsigned)(((int64_t)a.n_q * a.n_q_heads + 3) / 4);
+  hipLaunchKernelGGL(bwd_dq_f32_kernel, dim3(blocks), dim3(256), 0, stream, a);
+  hipError_t e = hipGetLastError();
   const int64_t n_keys = a.kv_end - key0;
-  if (n_keys > 0) {
-    const unsigned blocks = (unsigned)((n_keys * a.n_kv_heads + 3) / 4);
-    hipLaunchKernelGGL(bwd_dkdv_f32_kernel, dim3(blocks), dim3(256), 0, stream, a, key0, n_keys);
-    return hipGetLastError();
-  }
-  return hipSuccess;
+  if (e != hipSuccess || n_keys <= 0) return e;
+  blocks = (unsigned)((n_keys * a.n_kv_heads + 3) / 4);
+  hipLaunchKernelGGL(bwd_dkdv_f32_kernel, dim3(blocks), dim3(256), 0, stream, a, key0, n_keys);
+  return hipGetLastError();
 }
 
 }  // namespace ls

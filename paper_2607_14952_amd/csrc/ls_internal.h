@@ -38,13 +38,40 @@ inline int f32_dkdv_chunks(int n_q, int group) {
   return (int)(c < 16 ? c : 16);
 }
 
-// Rows (of head_dim floats) that the backward workspace has for dq partial sums
-// of key chunks: 512 workgroups, two per CU, of up to 128 packed rows.  It
-// grows with n_q, so that a workspace made for more rows serves fewer.
+// Most rows (of head_dim floats) of dq partial sums that one key range's chunks
+// take: 512 workgroups, two per CU, of up to 128 packed rows.  The workspace has
+// room for two such ranges (dq_part_bytes).  Both grow with n_q, so that a workspace made
+// for more rows serves fewer.
 inline int64_t dq_part_rows(int n_q, int group) {
   const int64_t rows = (int64_t)n_q * group;
   return 512 * (rows < 128 ? rows : 128);
 }
+inline size_t dq_part_bytes(int n_q, int group, int head_dim) {
+  return 2 * (size_t)dq_part_rows(n_q, group) * head_dim * 4;
+}
+
+// Key ranges of one dq launch: workgroups z0[i] .. z0[i + 1] - 1 (grid z) work on
+// range i, chunks of `per` 32-key tiles of it.
+constexpr int kMaxDqRanges = 16;
+struct DqRanges {
+  int32_t n;
+  int32_t z0[kMaxDqRanges + 1];
+  int32_t per[kMaxDqRanges];
+  int64_t begin[kMaxDqRanges], end[kMaxDqRanges];
+#ifdef __HIPCC__
+  __device__ __forceinline__ int of(int z) const {
+    int i = 0;
+    while (i + 1 < n && z >= z0[i + 1]) ++i;
+    return i;
+  }
+#endif
+};
+// One range's chunks; `form` tells launches that cannot be joined apart.
+struct DqPlan {
+  int64_t begin, end;
+  int32_t chunks, per, form;
+  bool joins;               // may share a launch with other ranges (through partial sums)
+};
 
 // Whether the fp32 matrix-core kernels take these shapes (the generic kernels
 // take the others).
@@ -73,7 +100,8 @@ struct FwdArgs {
 };
 static_assert(sizeof(FwdArgs) <= 4096, "kernel arguments");
 
-// Backward over one key range [kv_begin, kv_end).
+// Backward.  The dq launches take their key ranges from DqRanges, the dk/dv ones
+// from kv_begin / kv_end.
 struct BwdArgs {
   const void* q;
   const void* k_pool;
@@ -88,7 +116,7 @@ struct BwdArgs {
   float* dkdv_part;         // partial dk/dv sums of row chunks (bf16: [row chunks, 2, Hkv,
                             // kv_end - prefix_len, D]; fp32: [row chunks, keys, Hkv, D + Dv])
   float* dq_part;           // partial dq sums of key chunks [chunks, n_q, Hq, D], unscaled
-                            // (dq_part_rows rows in all)
+                            // (dq_part_bytes in all)
   int64_t q_pos0;
   int64_t prefix_len;
   int64_t kv_begin, kv_end;
@@ -170,15 +198,14 @@ hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t stream);
 // fp32 on the matrix cores, for the shapes f32_mfma_fits accepts (launch_fwd_f32
 // and launch_bwd_f32 take them for those and the generic kernels for the others)
 hipError_t launch_fwd_f32_mfma(const FwdArgs& a, hipStream_t stream);
-// dq over the range and dk/dv of its keys from key0 on (none when key0 >= kv_end)
-hipError_t launch_bwd_f32_mfma(const BwdArgs& a, bool need_dq, int64_t key0, hipStream_t stream);
-// dq (+)= scale * the sum of n_chunks partials of n values (a multiple of 4), in order
-hipError_t launch_dq_reduce(const float* part, int n_chunks, int64_t n, float scale,
+DqPlan plan_dq_f32_mfma(const BwdArgs& a, int64_t begin, int64_t end);
+hipError_t launch_dq_f32_mfma(const BwdArgs& a, const DqRanges& r, int form, float* part,
+                              hipStream_t stream);
+// dk/dv of the keys from key0 to a.kv_end
+hipError_t launch_dkdv_f32_mfma(const BwdArgs& a, int64_t key0, hipStream_t stream);
+// dq (+)= scale * the sum of each range's partials (n values each, a multiple of 4), in order
+hipError_t launch_dq_reduce(const float* part, const DqRanges& r, int64_t n, float scale,
                             bool accumulate, float* dq, hipStream_t stream);
-inline hipError_t launch_dq_reduce(const BwdArgs& a, int n_chunks, hipStream_t stream) {
-  return launch_dq_reduce(a.dq_part, n_chunks, (int64_t)a.n_q * a.n_q_heads * a.head_dim, a.scale,
-                          a.accumulate_dq != 0, a.dq, stream);
-}
 hipError_t launch_hbm_read(const void* buf, int64_t n16, uint32_t* out, hipStream_t stream);
 hipError_t launch_dsa_scores(const DsaArgs& a, hipStream_t stream);
 // n_chunks > 1 (from topk_chunks): the rows' chunks are selected from first, into
@@ -190,8 +217,11 @@ hipError_t launch_fwd_bf16_d256(const FwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd_prep(const void* d_out, const void* out, bool dout_bf16, bool out_bf16,
                            const float* lse, int n_q, int n_heads, int dv, float* delta,
                            float* lse2, hipStream_t stream);
-hipError_t launch_bwd_f32(const BwdArgs& a, bool need_dq, bool need_dkv, hipStream_t stream);
-hipError_t launch_bwd_bf16_d256(const BwdArgs& a, bool need_dq, bool need_dkv,
-                                hipStream_t stream);
+// the generic fp32 kernels over [a.kv_begin, a.kv_end); dk/dv of its keys from key0 on
+hipError_t launch_bwd_f32_generic(const BwdArgs& a, int64_t key0, hipStream_t stream);
+DqPlan plan_dq_bf16_d256(const BwdArgs& a, int64_t begin, int64_t end);
+hipError_t launch_dq_bf16_d256(const BwdArgs& a, const DqRanges& r, float* part,
+                               hipStream_t stream);
+hipError_t launch_dkdv_bf16_d256(const BwdArgs& a, int64_t key0, hipStream_t stream);
 
 }  // namespace ls

@@ -383,26 +383,36 @@ __global__ __launch_bounds__(256) void prep_vec_kernel(const TD* __restrict__ d_
 }
 
 // ---------------------------------------------------------------- dq chunks
-// dq (+)= scale * the sum of the key chunks' partials [n_chunks, rows, D], in
-// chunk order.  One thread per 4 values; four chunks' loads in flight.
+// dq (+)= scale * the sum of each key range's partials part[z0 .. z1) [., n4],
+// range by range: what a launch per range would leave, to the bit.  One thread
+// per 4 values; four chunks' loads in flight.
 __global__ __launch_bounds__(256) void dq_reduce_kernel(const f32x4* __restrict__ part,
-                                                        int64_t n4, int n_chunks, float scale,
+                                                        DqRanges r, int64_t n4, float scale,
                                                         int accumulate, f32x4* __restrict__ dq) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n4) return;
-  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-  int c = 0;
-  for (; c + 4 <= n_chunks; c += 4) {
-    f32x4 v[4];
+  f32x4 out = {0.f, 0.f, 0.f, 0.f};
+  if (accumulate) out = dq[i];
+  for (int k = 0; k < r.n; ++k) {
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    int c = r.z0[k];
+    const int end = r.z0[k + 1];
+    for (; c + 4 <= end; c += 4) {
+      f32x4 v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = part[(int64_t)(c + u) * n4 + i];
+      for (int u = 0; u < 4; ++u) v[u] = part[(int64_t)(c + u) * n4 + i];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) sum += v[u];
+      for (int u = 0; u < 4; ++u) sum += v[u];
+    }
+    for (; c < end; ++c) sum += part[(int64_t)c * n4 + i];
+    if (k == 0 && !accumulate) {
+      out = sum * scale;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[e] = fmaf(sum[e], scale, out[e]);
+    }
   }
-  for (; c < n_chunks; ++c) sum += part[(int64_t)c * n4 + i];
-  sum *= scale;
-  if (accumulate) sum += dq[i];
-  dq[i] = sum;
+  dq[i] = out;
 }
 
 // ---------------------------------------------------------------- HBM read probe
@@ -551,11 +561,11 @@ hipError_t launch_bwd_prep(const void* d_out, const void* out, bool dout_bf16, b
   return hipGetLastError();
 }
 
-hipError_t launch_dq_reduce(const float* part, int n_chunks, int64_t n, float scale,
+hipError_t launch_dq_reduce(const float* part, const DqRanges& r, int64_t n, float scale,
                             bool accumulate, float* dq, hipStream_t stream) {
   const int64_t n4 = n / 4;
   hipLaunchKernelGGL(dq_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream,
-                     (const f32x4*)part, n4, n_chunks, scale, accumulate ? 1 : 0, (f32x4*)dq);
+                     (const f32x4*)part, r, n4, scale, accumulate ? 1 : 0, (f32x4*)dq);
   return hipGetLastError();
 }
 

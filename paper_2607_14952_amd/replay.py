@@ -7,7 +7,8 @@ forward  : every split's local (o_r, l_r)        -> ls_prefix_attn_fwd (one laun
            the production composition noted after Eq. qwen-global-attn)
            (the single-GPU form of the cross-rank merge, Eq. qwen-lse-parts and
            Eq. qwen-global-attn)
-backward : per shard key range, dq accumulated in shard order (Eq. qwen-dq-reduce);
+backward : ls_prefix_attn_bwd_ranges over the shards' key ranges, dq accumulated
+           in shard order (Eq. qwen-dq-reduce);
            the response range also yields the response dK/dV (lazy gradient pages:
            prefix keys get none).
 
@@ -194,8 +195,12 @@ class ReplayStep:
                           stream=self.stream)
 
     def backward(self):
-        for r in range(len(self.shards)):
-            self.backward_range(r)
+        """Every shard range in one call: what backward_range leaves after the last."""
+        c = self.cfg
+        B.prefix_attn_bwd_ranges(self.dev["q"], self.kv, self.dev["d_out"], self.out, self.lse,
+                                 self.shards, prefix_len=c.prefix_len, q_pos0=c.q_pos0,
+                                 scale=c.scale, dq=self.dq, dk_resp=self.dk, dv_resp=self.dv,
+                                 workspace=self.ws, stream=self.stream)
         return self.dq, self.dk, self.dv
 
     def step(self):

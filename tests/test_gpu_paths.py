@@ -254,3 +254,40 @@ def test_bf16_short_pages(page, R):
     out, lse, o_ref, l_ref = check_forward(cfg, h, dev, splits, P=P, q_pos0=P)
     check_backward(cfg, h, dev, out, lse, o_ref, l_ref,
                    [(0, 41), (41, 42), (42, 777), (777, P + 5), (P + 5, P + R)], P=P, q_pos0=P)
+
+
+@pytest.mark.parametrize("cfg,cuts", [
+    (_bf16("ranges_few", 4_100, 20), [0, 1_000, 1_000, 1_033, 2_500, 4_100, 4_120]),
+    (_bf16("ranges_many", 3_000, 3), list(range(0, 3_003, 77)) + [3_003]),
+    (_bf16("ranges_whole", 600, 2_100), [0, 300, 600, 2_700]),
+    (_f32("ranges", 4, 2, 64, 64, 6_000, 40), [0, 2_000, 2_100, 6_000, 6_040]),
+    (_f32("ranges_generic", 2, 1, 160, 160, 300, 9), [0, 100, 300, 309]),
+], ids=lambda x: getattr(x, "name", ""))
+def test_bwd_ranges_equal_calls(cfg, cuts):
+    """Ranges that share launches leave the bits of one call per range: several
+    chunks each, more ranges than one launch takes, an empty one, ranges whose
+    one chunk fills the chip, and dq accumulated onto given values."""
+    import torch
+
+    from paper_2607_14952_amd import inputs
+    from paper_2607_14952_amd.replay import device_inputs
+    dev = device_inputs(inputs.dense_inputs(cfg))
+    kv = B.PagedKV(dev["k_pool"], dev["v_pool"], dev["page_table"])
+    P = cfg.prefix_len
+    kw = dict(prefix_len=P, q_pos0=P, scale=cfg.scale)
+    op, lp = B.prefix_attn_fwd(dev["q"], kv, [(0, cfg.kv_len)], **kw)
+    out, lse = B.lse_merge(op, lp, out_dtype=dev["q"].dtype)
+    ranges = list(zip(cuts, cuts[1:]))
+    print(f"[gpu] bwd ranges {cfg.name}", flush=True)
+    for first in (0, B.FLAG_ACCUMULATE_DQ):
+        start = torch.ones((cfg.resp_len, cfg.n_q_heads, cfg.head_dim), device="cuda")
+        dq, dk, dv = start.clone(), None, None
+        for r, (b, e) in enumerate(ranges):
+            dq, dk, dv = B.prefix_attn_bwd(dev["q"], kv, dev["d_out"], out, lse, kv_begin=b,
+                                           kv_end=e, dq=dq, dk_resp=dk, dv_resp=dv,
+                                           flags=B.FLAG_ACCUMULATE_DQ if r else first, **kw)
+        got = B.prefix_attn_bwd_ranges(dev["q"], kv, dev["d_out"], out, lse, ranges,
+                                       dq=start.clone(), flags=first, **kw)
+        torch.cuda.synchronize()
+        for x, y in zip((dq, dk, dv), got):
+            assert torch.equal(x, y)
