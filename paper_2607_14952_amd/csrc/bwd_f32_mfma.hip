@@ -20,9 +20,9 @@
 // Both are bound by the MFMAs (64 cycles each) once every SIMD has a wave, which
 // the chunk counts below see to.  Measured against the scalar kernels: 128 rows
 // x 4,096 keys, 2 heads of 64, dq + dk/dv 2,900 -> 38 us; 500 rows x 16,001
-// keys, 8 heads of 128 on 2 KV heads 25.8 -> 0.61 ms (81 TFLOP/s of the 154 an
-// fp32 GEMM reaches; the rest is the staging between the tile barriers, which
-// one wave per SIMD cannot cover).
+// keys, 8 heads of 128 on 2 KV heads 25.8 -> 0.55 ms (dq at 100 TFLOP/s of the
+// 154 an fp32 GEMM reaches: the matrix cores are busy 73% of the time, with two
+// waves per SIMD where four row groups share a tile; with one, 0.61 ms).
 #include <algorithm>
 
 #include "f32_mfma.h"
@@ -33,7 +33,7 @@ using namespace f32m;
 
 // ============================================================== dq
 template <int kDP, int kRW>
-__global__ __launch_bounds__(256) void bwd_dq_f32_mfma_kernel(BwdArgs a, DqRanges ranges,
+__global__ __launch_bounds__(256, kRW == 4 ? 2 : 1) void bwd_dq_f32_mfma_kernel(BwdArgs a, DqRanges ranges,
                                                               float* __restrict__ part) {
   constexpr int kKW = 4 / kRW;
   constexpr int kS = kRowS<kDP>;
@@ -76,17 +76,23 @@ __global__ __launch_bounds__(256) void bwd_dq_f32_mfma_kernel(BwdArgs a, DqRange
 #pragma unroll
   for (int b = 0; b < kDB; ++b) acc[b] = zero16();
 
+  // (128-wide rows with two waves per SIMD leave no registers to load ahead)
+  constexpr bool kPre = !(kDP == 128 && kRW == 4);
   KvStage<kDP, kKW> stage;
-  if (t_begin < t_end) {
+  if (kPre && t_begin < t_end) {
     stage.load_pages(a, k_lo + (int64_t)t_begin * 32, kb, k_hi, tid);
     stage.load(a, g, k_lo + (int64_t)t_begin * 32, kb, k_hi, tid);
   }
   for (int t = t_begin; t < t_end; t += kKW) {
     const int64_t t0 = k_lo + (int64_t)t * 32;
+    if (!kPre) {
+      stage.load_pages(a, t0, kb, k_hi, tid);
+      stage.load(a, g, t0, kb, k_hi, tid);
+    }
     __syncthreads();   // every wave is done with the previous tiles
     stage.template store<kS, kS>(a, ks, vs, tid);
     __syncthreads();
-    if (t + kKW < t_end) stage.load(a, g, t0 + 32 * kKW, kb, k_hi, tid);
+    if (kPre && t + kKW < t_end) stage.load(a, g, t0 + 32 * kKW, kb, k_hi, tid);
     if (t + kw >= t_end) continue;   // (uniform per wave; the barriers above are not skipped)
 
     const int64_t tw = t0 + 32 * kw;

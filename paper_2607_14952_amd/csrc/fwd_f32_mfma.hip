@@ -23,7 +23,7 @@ namespace {
 using namespace f32m;
 
 template <int kDP, int kRW>
-__global__ __launch_bounds__(256) void fwd_f32_mfma_kernel(FwdArgs a) {
+__global__ __launch_bounds__(256, kRW == 4 ? 2 : 1) void fwd_f32_mfma_kernel(FwdArgs a) {
   constexpr int kKW = 4 / kRW;                // key slots
   constexpr int kKS = kRowS<kDP>, kVS = kColS<kDP>;
   constexpr int kDB = kDP / 32;               // output dimension blocks

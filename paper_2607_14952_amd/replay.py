@@ -69,34 +69,54 @@ def fine_splits(cfg, splits):
     """The shards' splits (lists of key ranges, the response's list last), each cut
     into the number of equal pieces that makes the forward and merge shortest.
 
-    A workgroup takes 32-key tiles of one split for 256 packed query rows (128
-    where there are no more, and in the fp32 kernels) and one runs per CU, so a
-    launch takes ceil(workgroups / 256) rounds of a split's tiles plus about 6
-    for its start and end, and one more short round where the response's
-    workgroups find no idle CU.  Each further part is written and read once
-    more: 0.41 ns per KiB row (1,111 rows, 33 -> 65 parts: +241 us), against
-    1.6 us (0.95 us) for a tile of 256 (128) rows.  Measured, whole -> cut: 1 row
-    x 131,075 keys in 64 splits 72 -> 64 us (2 pieces), 16 rows x 262,144 keys
-    in 32 splits 248 -> 137 us (4), 150 rows x 1M 3,071 -> 2,276 us (4).  77 rows
-    x 262,144 (198 workgroups) gain nothing (421, 434, 430 us for 1, 2, 4), so a
-    cut must promise 8%; 4,096 rows fill 33 rounds and stay whole."""
+    A bf16 workgroup takes 32-key tiles of one split for 256 packed query rows
+    (128 where there are no more) and one runs per CU, so a launch takes
+    ceil(workgroups / 256) rounds of a split's tiles plus about 6 for its start
+    and end, and one more short round where the response's workgroups find no
+    idle CU.  In fp32, 128 rows a workgroup, two share a CU at 1.6 times the time,
+    or, where those would not fill the CUs once, 32 rows whose four waves share the
+    tiles.  Each further part is written and read once more: 0.41 ns per KiB row
+    (1,111 rows, 33 -> 65 parts: +241 us).
+
+    Measured, whole -> cut: bf16, 1 row x 131,075 keys in 64 splits 72 -> 64 us (2
+    pieces), 16 rows x 262,144 keys in 32 splits 248 -> 137 us (4), 150 rows x 1M
+    3,071 -> 2,276 us (4); fp32, 1 row x 30,000 keys in 2 splits 873 -> 56 us
+    (32), 128 rows x 4,096 in 2 66 -> 32 (8).  77 rows x 262,144 (198 workgroups)
+    gain nothing (421, 434, 430 us for 1, 2, 4), so a cut must promise 8%; 4,096
+    rows fill 33 rounds and stay whole."""
     rows = cfg.resp_len * cfg.group
-    per_wg = 256 if cfg.dtype == "bf16" and cfg.page_size >= 8 and rows > 128 else 128
     prefix = [r for sp in splits[:-1] for r in sp]
     if not prefix:
         return splits
-    own = -(-rows // per_wg) * cfg.n_kv_heads   # workgroups of one split
+    n, hkv = len(prefix), cfg.n_kv_heads
     tiles = -(-max(e - b for b, e in prefix) // 32)
-    tile_ns = 1600 if per_wg == 256 else 950
-    part = 0.41 / tile_ns * cfg.resp_len * cfg.n_q_heads * cfg.head_dim_v / 256 * len(prefix)
+
+    if cfg.dtype == "f32":
+        tile_ns = 4000 * max(cfg.head_dim, cfg.head_dim_v) / 128
+
+        def launch(f):
+            wide = -(-rows // 128) * hkv * n * f
+            if wide >= _CUS:
+                return -(-wide // (2 * _CUS)) * 1.6 * (-(-tiles // f) + 3)
+            return -(-(-(-rows // 32) * hkv * n * f) // _CUS) * (-(-tiles // (4 * f)) + 4)
+    else:
+        per_wg = 256 if cfg.page_size >= 8 and rows > 128 else 128
+        tile_ns = 1600 if per_wg == 256 else 950
+
+        def launch(f):
+            own = -(-rows // per_wg) * hkv   # workgroups of one split
+            rounds = -(-own * n * f // _CUS)
+            late = 0
+            if rounds * _CUS - own * n * f < own:
+                late = 6 + min(tiles, -(-cfg.resp_len // 32))
+            return rounds * (-(-tiles // f) + 6) + late
+
+    part = 0.41 / tile_ns * cfg.resp_len * cfg.n_q_heads * cfg.head_dim_v / 256 * n
 
     def cost(f):
-        wgs = own * len(prefix) * f
-        rounds = -(-wgs // _CUS)
-        late = 6 + min(tiles, -(-cfg.resp_len // 32)) if rounds * _CUS - wgs < own else 0
-        return rounds * (-(-tiles // f) + 6) + late + part * f
+        return launch(f) + part * f
 
-    most = max(1, min(16, tiles // 8, 1024 // len(prefix)))
+    most = max(1, min(64, tiles // 8, 1024 // n))
     f = min(range(1, most + 1), key=cost)
     if cost(f) > 0.92 * cost(1):
         return splits
