@@ -6,13 +6,14 @@ prompt is captured in fixed chunks: chunk c = positions [b, e) is written into
 its own pages of the pool (ls_scatter_kv through the page table: right-sized
 pages that belong to the store, not views of a chunk tensor), then its queries
 attend to every earlier position and causally within the chunk
-(ls_prefix_attn_fwd over the chunk's splits with q_pos0 = b, then
-ls_lse_merge).  Chunking does not change the result: row t's output is causal
+(ls_prefix_attn_fwd over the chunk's splits, cut finer where they leave CUs
+idle, with q_pos0 = b, then ls_lse_merge).  Chunking does not change the result: row t's output is causal
 attention over positions 0 .. t.
 """
 from __future__ import annotations
 
 from . import binding as B
+from .replay import fine_splits
 
 
 class PrefixCapture:
@@ -30,7 +31,15 @@ class PrefixCapture:
         self.k_pool = torch.zeros((cfg.n_phys_pages, S, Hkv, D), dtype=bf16, device=dv)
         self.v_pool = torch.zeros((cfg.n_phys_pages, S, Hkv, D), dtype=bf16, device=dv)
         self.kv = B.PagedKV(self.k_pool, self.v_pool, dev["page_table"])
-        n_split = max(len(cfg.chunk_splits(c)) for c in range(cfg.n_chunks))
+        # the earlier positions' splits, cut where a short chunk's rows would leave CUs
+        # idle (1,024 rows fill 64 workgroups of a split), then the chunk's own keys
+        self._splits = []
+        for c in range(cfg.n_chunks):
+            b, e = cfg.chunk_range(c)
+            *earlier, own = cfg.chunk_splits(c)
+            fine = fine_splits(cfg, [earlier, [own]], e - b)
+            self._splits.append([r for sp in fine for r in sp])
+        n_split = max(map(len, self._splits))
         kw = dict(dtype=torch.float32, device=dv)
         # flat storage, viewed per chunk as contiguous [splits, rows, ...] (a
         # short last chunk needs dense views, not slices of full-chunk ones)
@@ -47,7 +56,7 @@ class PrefixCapture:
         n = e - b
         B.scatter_kv(self.kv, b, self.dev["k"][b:e], self.dev["v"][b:e], stream=self.stream)
         q = self.dev["q_blocks"][c % cfg.n_q_blocks][:n]
-        splits = cfg.chunk_splits(c)
+        splits = self._splits[c]
         ns = len(splits)
         Hq, D = cfg.n_q_heads, cfg.head_dim
         out_part = self._out_part[:ns * n * Hq * D].view(ns, n, Hq, D)

@@ -65,9 +65,10 @@ def cyclic_shards(cfg):
 _CUS = 256
 
 
-def fine_splits(cfg, splits):
+def fine_splits(cfg, splits, n_rows=None):
     """The shards' splits (lists of key ranges, the response's list last), each cut
-    into the number of equal pieces that makes the forward and merge shortest.
+    into the number of equal pieces that makes the forward and merge of n_rows
+    (default: the response's) tokens shortest.
 
     A bf16 workgroup takes 32-key tiles of one split for 256 packed query rows
     (128 where there are no more) and one runs per CU, so a launch takes
@@ -81,14 +82,16 @@ def fine_splits(cfg, splits):
     Measured, whole -> cut: bf16, 1 row x 131,075 keys in 64 splits 72 -> 64 us (2
     pieces), 16 rows x 262,144 keys in 32 splits 248 -> 137 us (4), 150 rows x 1M
     3,071 -> 2,276 us (4); fp32, 1 row x 30,000 keys in 2 splits 873 -> 56 us
-    (32), 128 rows x 4,096 in 2 66 -> 32 (8).  77 rows x 262,144 (198 workgroups)
+    (32), 128 rows x 4,096 in 2 66 -> 32 (8); capture of 30,000 positions in chunks
+    of 1,024 17.9 -> 7.6 ms, of 100,000 93 -> 72 ms.  77 rows x 262,144 (198 workgroups)
     gain nothing (421, 434, 430 us for 1, 2, 4), so a cut must promise 8%; 4,096
     rows fill 33 rounds and stay whole."""
-    rows = cfg.resp_len * cfg.group
+    tokens = cfg.resp_len if n_rows is None else n_rows
+    rows = tokens * cfg.group
     prefix = [r for sp in splits[:-1] for r in sp]
-    if not prefix:
-        return splits
     n, hkv = len(prefix), cfg.n_kv_heads
+    if not prefix or -(-rows // 256) * hkv * n >= 4 * _CUS:
+        return splits   # four rounds or more: nothing to gain
     tiles = -(-max(e - b for b, e in prefix) // 32)
 
     if cfg.dtype == "f32":
@@ -108,10 +111,10 @@ def fine_splits(cfg, splits):
             rounds = -(-own * n * f // _CUS)
             late = 0
             if rounds * _CUS - own * n * f < own:
-                late = 6 + min(tiles, -(-cfg.resp_len // 32))
+                late = 6 + min(tiles, -(-tokens // 32))
             return rounds * (-(-tiles // f) + 6) + late
 
-    part = 0.41 / tile_ns * cfg.resp_len * cfg.n_q_heads * cfg.head_dim_v / 256 * n
+    part = 0.41 / tile_ns * tokens * cfg.n_q_heads * cfg.head_dim_v / 256 * n
 
     def cost(f):
         return launch(f) + part * f
