@@ -607,8 +607,7 @@ LS_API ls_status ls_prefix_attn_bwd_ranges(const ls_attn_params* p, const ls_spl
   a.scale_log2 = p->softmax_scale * ls::kLog2e;
   a.accumulate_dq = (p->flags & LS_FLAG_ACCUMULATE_DQ) ? 1 : 0;
   a.accumulate_dkv = (p->flags & LS_FLAG_ACCUMULATE_DKV) ? 1 : 0;
-  const int64_t packed = (int64_t)p->n_q * a.group, chunks = ls::dkdv_row_chunks(p->n_q, a.group);
-  a.dkdv_rows = (int32_t)(((packed + chunks - 1) / chunks + 31) / 32 * 32);
+  a.dkdv_rows = 0;
   e = launch_backward(a, p->dtype == LS_BF16, todo, wl.dq_bytes, s);
   return e == hipSuccess ? LS_OK : hip_fail(e, "backward launch");
 }
@@ -645,11 +644,12 @@ size_t pad256(size_t x) { return (x + 255) / 256 * 256; }
 // sum; from about 100 tokens on one chunk is taken.
 int sparse_chunks(int64_t items, int64_t tiles, double part, int64_t most) {
   int best = 1;
-  double least = 0;
-  for (int c = 1; c == 1 || (c <= most && c <= 64 && tiles / c >= 4); ++c) {
-    double cost = (double)((items * c + 255) / 256) * (double)((tiles + c - 1) / c + 8);
-    if (c > 1) cost = 1.05 * (cost + 5 + part * (double)(items * c));
-    if (c == 1 || cost < least) {
+  if (items >= 256) return best;   // (no chunk count is priced below one round's lists)
+  double least = (double)(tiles + 8);
+  for (int c = 2; c <= most && c <= 32 && tiles / c >= 4; ++c) {
+    const double cost = 1.05 * ((double)((items * c + 255) / 256) * (double)((tiles + c - 1) / c + 8) +
+                                5 + part * (double)(items * c));
+    if (cost < least) {
       best = c;
       least = cost;
     }
@@ -657,10 +657,15 @@ int sparse_chunks(int64_t items, int64_t tiles, double part, int64_t most) {
   return best;
 }
 
+// Entries of a token's key list, padded to a whole tile.
+int64_t sparse_list_len(const ls_attn_params* p, int32_t topk) {
+  const int64_t n = (int64_t)topk + (p->q_pos0 - p->prefix_len) + p->n_q;
+  return (n + 31) / 32 * 32;
+}
+
 SparseLayout sparse_layout(const ls_attn_params* p, int32_t topk) {
   SparseLayout L;
-  const int64_t n = (int64_t)topk + (p->q_pos0 - p->prefix_len) + p->n_q;
-  L.n_max = (n + 31) / 32 * 32;
+  L.n_max = sparse_list_len(p, topk);
   L.phys_bytes = pad256((size_t)p->n_q * L.n_max * 4);
   L.ntok_bytes = pad256((size_t)p->n_q * 4);
   L.stat_bytes = pad256((size_t)p->n_q * p->n_q_heads * 4);
@@ -697,7 +702,7 @@ ls_status check_sparse(const ls_attn_params* p, const int32_t* idx, int32_t topk
     return fail(LS_ERR_INVALID_ARG, "topk %d outside [0, prefix_len]", topk);
   if (topk > 0 && (!idx || !aligned16(idx)))
     return fail(LS_ERR_INVALID_ARG, "idx must be non-NULL and 16-byte aligned");
-  if (sparse_layout(p, topk).n_max > (int64_t)1 << 30)
+  if (sparse_list_len(p, topk) > (int64_t)1 << 30)
     return fail(LS_ERR_UNSUPPORTED, "key list too long");
   // rows are gathered with 32-bit offsets from the pool base
   if (p->n_phys_pages * p->page_size * (int64_t)p->head_dim * 2 > (int64_t)0xFFFFFFFF)

@@ -640,21 +640,27 @@ namespace {
 // result.  c chunks cut the rounds to whole shares of fewer tiles (10 items
 // leave 246 CUs idle, 140 leave 116) and add the partial sums' way through
 // memory, about 4.7e-4 tile times per row and chunk (1 KiB out and back in
-// against 32 KiB of K and V per 0.95 us) and a launch.  The chunk count with
-// the least sum is taken; one when items fill the rounds (512 items: 2 rounds
-// either way).  Measured: 77 rows x 16 heads over 32,768 keys 836 -> 76 us
+// against 32 KiB of K and V per 0.95 us) and a launch.  The chunk counts that
+// fill 1 to 8 rounds are priced, and within each the one that balances tiles
+// and partial sums, if smaller; one chunk where nothing is less (512 items: 2
+// rounds either way).  Measured: 77 rows x 16 heads over 32,768 keys 836 -> 76 us
 // (25 chunks), 1,111 rows over 12,500 keys 396 -> 345 us (3 chunks), 952 rows
 // over 32,768 keys 952 -> 568 us (2 chunks), the reduce included.
 int dq_chunks(const BwdArgs& a, int64_t items, int64_t tiles) {
-  const int64_t rows = (int64_t)a.n_q * a.n_q_heads;
-  const int64_t most = std::min(dq_part_rows(a.n_q, a.group) / rows, std::min<int64_t>(256, tiles / 4));
+  const double rows = (double)a.n_q * a.n_q_heads;
+  const int64_t most = std::min<int64_t>({dq_part_rows(a.n_q, a.group) / ((int64_t)a.n_q * a.n_q_heads),
+                                          256, tiles / 4});
   int best = 1;
-  double least = 0;
-  for (int c = 1; c == 1 || c <= most; ++c) {
-    double cost = (double)((items * c + 255) / 256) * (double)((tiles + c - 1) / c + 6);
-    if (c > 1) cost += 5 + 4.7e-4 * (double)rows * c;
-    if (c == 1 || cost < least) {
-      best = c;
+  double least = (double)((items + 255) / 256) * (double)(tiles + 6);
+  for (int k = 1; k <= 8; ++k) {
+    const int64_t fill = 256 * k / items;
+    const int64_t balance = (int64_t)sqrt((double)k * (double)tiles / (4.7e-4 * rows)) + 1;
+    const int64_t c = std::min({fill, balance, most});
+    if (c < 2) continue;
+    const double cost = (double)((items * c + 255) / 256) * (double)((tiles + c - 1) / c + 6) + 5 +
+                        4.7e-4 * rows * (double)c;
+    if (cost < least) {
+      best = (int)c;
       least = cost;
     }
   }
@@ -699,10 +705,17 @@ hipError_t launch_dq_bf16_d256(const BwdArgs& a, const DqRanges& r, float* part,
   return hipGetLastError();
 }
 
-hipError_t launch_dkdv_bf16_d256(const BwdArgs& a, int64_t key0, hipStream_t stream) {
-  const int64_t n_keys = a.kv_end - key0;
+hipError_t launch_dkdv_bf16_d256(const BwdArgs& args, int64_t key0, hipStream_t stream) {
+  BwdArgs a = args;
+  const int64_t n_keys = a.kv_end - key0, packed = (int64_t)a.n_q * a.group;
   const unsigned blocks = (unsigned)((n_keys + kKeysPerWG - 1) / kKeysPerWG);
-  const int n_chunks = dkdv_row_chunks(a.n_q, a.group);
+  // Row chunks (dkdv_row_chunks: the most, which the workspace has room for): two
+  // workgroups per CU, or chunks of 2,048 rows where there are more of these.
+  const int64_t fill = (512 + (int64_t)blocks * a.n_kv_heads - 1) / ((int64_t)blocks * a.n_kv_heads);
+  const int64_t want = std::min<int64_t>(dkdv_row_chunks(a.n_q, a.group),
+                                         std::max((packed + 2047) / 2048, fill));
+  a.dkdv_rows = (int32_t)(((packed + want - 1) / want + 31) / 32 * 32);
+  const int n_chunks = (int)((packed + a.dkdv_rows - 1) / a.dkdv_rows);
   hipLaunchKernelGGL(bwd_dkdv_bf16_d256_kernel, dim3(blocks, a.n_kv_heads, n_chunks), dim3(256), 0,
                      stream, a, key0, a.kv_end);
   hipError_t e = hipGetLastError();

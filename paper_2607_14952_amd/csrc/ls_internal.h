@@ -19,8 +19,8 @@ constexpr int kMaxMergeGroups = 64;        // groups of one merge call (kernel a
 // the launch's first key (64-bit bounds took a second launch from 129 splits on).
 constexpr int kMaxSplitsPerLaunch = 448;
 
-// Row chunks of the bf16 dk/dv kernel (partials in the backward workspace): up
-// to 16 chunks of at least 128 packed rows, so that the few key blocks of a
+// Most row chunks of the bf16 dk/dv kernel (partials in the backward workspace):
+// up to 16 chunks of at least 128 packed rows, so that the few key blocks of a
 // short response still give many workgroups, and more only where 16 would hold
 // over 2,048 rows each (the partials are written and read once per chunk).
 // Measured with the reduce: 77 tokens x 16 heads 59 -> 26 us, 1,111 tokens
@@ -127,7 +127,8 @@ struct BwdArgs {
   float scale;              // softmax_scale
   float scale_log2;         // softmax_scale * log2(e)
   int32_t accumulate_dq, accumulate_dkv;
-  int32_t dkdv_rows;        // bf16 path: packed rows per dk/dv chunk, a multiple of 32
+  int32_t dkdv_rows;        // bf16 path: packed rows per dk/dv chunk, a multiple of 32 (set by
+                            // the launcher)
 };
 
 // DSA index scores (Eq. dsa-index) over positions [pos_begin, pos_end).

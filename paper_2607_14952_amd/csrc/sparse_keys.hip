@@ -15,11 +15,12 @@ using namespace sparse;
 // then the response window prefix_len .. q_pos0 + t.  ntok[t] is the list's
 // length; entries past it repeat its last key so tile loads stay inside the
 // pool (the tile kernels mask keys at or past ntok[t]).
-// Eight entries of each thread are in flight at a time (2,048 of the list): the
+// kU entries of each thread are in flight at a time (8: 2,048 of the list; 2 for
+// lists of up to 512, where more would only be idle lanes' work): the
 // walk is a chain of dependent loads (entry, page, store), so what counts is how
 // few times it is entered (2,048 selections, 24 tokens: 8.0 -> 4.9 us).
+template <int kU>
 __global__ __launch_bounds__(256) void sparse_phys_kernel(SparseArgs a) {
-  constexpr int kU = 8;
   __shared__ int wave_total[kU][4];
   const int t = (int)blockIdx.x, tid = (int)threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int32_t* sel = a.idx + (int64_t)t * a.topk;
@@ -77,7 +78,10 @@ __global__ __launch_bounds__(256) void sparse_phys_kernel(SparseArgs a) {
 }  // namespace
 
 hipError_t launch_sparse_phys(const SparseArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(sparse_phys_kernel, dim3((unsigned)a.n_q), dim3(256), 0, stream, a);
+  if (a.n_max <= 512)
+    hipLaunchKernelGGL(sparse_phys_kernel<2>, dim3((unsigned)a.n_q), dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL(sparse_phys_kernel<8>, dim3((unsigned)a.n_q), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

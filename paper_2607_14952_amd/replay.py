@@ -18,7 +18,10 @@ through a table of its own that names the prefix pages shard by shard, so that
 each shard's keys form one range of it.  Renumbering is exact here because every
 prefix position precedes every query row, so each prefix key is visible to each
 row whatever its position; the shard that owns a partly filled last page comes
-last, which keeps that page in its place before the response's positions.
+last, which keeps that page in its place before the response's positions.  With
+pages shorter than a key tile a shard's range might begin inside a tile of that
+table, which would round its results differently from a shard's own store: such
+a step keeps a table and a launch per shard.
 """
 from __future__ import annotations
 
@@ -63,6 +66,7 @@ def cyclic_shards(cfg):
 
 
 _CUS = 256
+_PIECES = (1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 48, 64)   # of a split
 
 
 def fine_splits(cfg, splits, n_rows=None):
@@ -120,7 +124,7 @@ def fine_splits(cfg, splits, n_rows=None):
         return launch(f) + part * f
 
     most = max(1, min(64, tiles // 8, 1024 // n))
-    f = min(range(1, most + 1), key=cost)
+    f = min((x for x in _PIECES if x <= most), key=cost)
     if cost(f) > 0.92 * cost(1):
         return splits
 
@@ -144,26 +148,46 @@ class ReplayStep:
         self.stream = stream
         q = dev["q"]
         R, Hq, D, Dv = cfg.resp_len, cfg.n_q_heads, cfg.head_dim, cfg.head_dim_v
+        own = (cfg.prefix_len, cfg.kv_len)
         if cfg.ownership == "cyclic":
-            self.shards, order = cyclic_shards(cfg)
             table = dev["page_table"].cpu().numpy()
-            t = table.copy()
-            t[:len(order)] = table[order]
-            self.kv = B.PagedKV(dev["k_pool"], dev["v_pool"], torch.from_numpy(t).to(q.device))
-            splits = [[(b + i, b + j) for i, j in cfg.virtual_splits(c)]
-                      for c, (b, _) in zip((c for c in range(cfg.n_shards) if cfg.shard_len(c)),
-                                           self.shards)]
-            splits.append([(cfg.prefix_len, cfg.kv_len)])
+            owners = [c for c in range(cfg.n_shards) if cfg.shard_len(c)]
+            splits = [cfg.virtual_splits(c) for c in owners] + [[own]]
+
+            def store(pages):
+                t = table.copy()
+                t[:len(pages)] = table[pages]
+                return B.PagedKV(dev["k_pool"], dev["v_pool"], torch.from_numpy(t).to(q.device))
+
+            if cfg.page_size >= 32:
+                self.shards, order = cyclic_shards(cfg)
+                self.stores = [store(order)]
+                splits = [[(b + i, b + j) for i, j in sp]
+                          for sp, (b, _) in zip(splits, self.shards[:-1])] + [[own]]
+            else:
+                self.shards = [(0, cfg.shard_len(c)) for c in owners] + [own]
+                self.stores = [store(cfg.shard_pages(c)) for c in owners] + [self.kv]
         else:
             self.shards = [r for r in cfg.shard_ranges() if r[0] < r[1]]
+            self.stores = [self.kv]
             every = [r for r in cfg.splits() if r[0] < r[1]]
             splits = [[r for r in every if b <= r[0] and r[1] <= e] for b, e in self.shards]
             assert sum(map(len, splits)) == len(every)
-        splits = fine_splits(cfg, splits)
-        # launch order is key order; the splits of shard s are parts groups[s] of it
-        self.splits = sorted(r for sp in splits for r in sp)
-        at = [self.splits.index(sp[0]) for sp in splits]
-        self.groups = [(i, i + len(sp)) for i, sp in zip(at, splits)]
+        # With a bf16 backward the splits stay as configured: other ones round P, and
+        # with it the bf16 output inside Delta, in other places, which moves the dq of
+        # a few rows with concentrated probabilities by up to 1.3e-2 (10 rows x 33,374
+        # keys, one in 100 aimed at a row; both results are as far from 64 bits).
+        if len(self.stores) == 1 and (cfg.dtype == "f32" or not self.backward_enabled):
+            splits = fine_splits(cfg, splits)
+        # The parts in launch order (key order of one store, else shard by shard);
+        # shard s has the parts groups[s] and is launched from store_of(s).
+        order = splits if len(self.stores) > 1 else sorted(splits)
+        self.splits = [r for sp in order for r in sp]
+        start, at = 0, {}
+        for sp in order:
+            at[id(sp)] = start
+            start += len(sp)
+        self.groups = [(at[id(sp)], at[id(sp)] + len(sp)) for sp in splits]
         kw = dict(dtype=torch.float32, device=q.device)
         self.out_part = torch.empty((len(self.splits), R, Hq, Dv), **kw)
         self.lse_part = torch.empty((len(self.splits), Hq, R), **kw)
@@ -177,12 +201,21 @@ class ReplayStep:
             self.dv = torch.zeros((cfg.kv_len - cfg.prefix_len, cfg.n_kv_heads, Dv), **kw)
             self.ws = B.bwd_workspace(q, self.kv, prefix_len=cfg.prefix_len, q_pos0=cfg.q_pos0)
 
+    def store_of(self, s: int):
+        """The store that shard s's ranges refer to."""
+        return self.stores[s if len(self.stores) > 1 else 0]
+
     def forward_splits(self):
-        """Local (o_r, l_r) of every split, in one launch."""
+        """Local (o_r, l_r) of every split, one launch per store."""
         c = self.cfg
-        B.prefix_attn_fwd(self.dev["q"], self.kv, self.splits, prefix_len=c.prefix_len,
-                          q_pos0=c.q_pos0, scale=c.scale, out_part=self.out_part,
-                          lse_part=self.lse_part, stream=self.stream)
+        kw = dict(prefix_len=c.prefix_len, q_pos0=c.q_pos0, scale=c.scale, stream=self.stream)
+        if len(self.stores) == 1:
+            B.prefix_attn_fwd(self.dev["q"], self.stores[0], self.splits, out_part=self.out_part,
+                              lse_part=self.lse_part, **kw)
+            return
+        for s, (i, j) in enumerate(self.groups):
+            B.prefix_attn_fwd(self.dev["q"], self.stores[s], self.splits[i:j],
+                              out_part=self.out_part[i:j], lse_part=self.lse_part[i:j], **kw)
 
     def merge(self):
         """Splits -> per-shard results (fp32) -> global result (q dtype)."""
@@ -210,7 +243,7 @@ class ReplayStep:
         workspace, so ranges must run in order, starting at 0."""
         c = self.cfg
         b, e = self.shards[r]
-        B.prefix_attn_bwd(self.dev["q"], self.kv, self.dev["d_out"], self.out, self.lse,
+        B.prefix_attn_bwd(self.dev["q"], self.store_of(r), self.dev["d_out"], self.out, self.lse,
                           prefix_len=c.prefix_len, q_pos0=c.q_pos0, scale=c.scale,
                           kv_begin=b, kv_end=e,
                           flags=(B.FLAG_ACCUMULATE_DQ | B.FLAG_PREP_READY) if r > 0 else 0,
@@ -218,9 +251,14 @@ class ReplayStep:
                           stream=self.stream)
 
     def backward(self):
-        """Every shard range in one call: what backward_range leaves after the last."""
+        """Every shard range, in one call per store: what backward_range leaves after the
+        last."""
         c = self.cfg
-        B.prefix_attn_bwd_ranges(self.dev["q"], self.kv, self.dev["d_out"], self.out, self.lse,
+        if len(self.stores) > 1:
+            for r in range(len(self.shards)):
+                self.backward_range(r)
+            return self.dq, self.dk, self.dv
+        B.prefix_attn_bwd_ranges(self.dev["q"], self.stores[0], self.dev["d_out"], self.out, self.lse,
                                  self.shards, prefix_len=c.prefix_len, q_pos0=c.q_pos0,
                                  scale=c.scale, dq=self.dq, dk_resp=self.dk, dv_resp=self.dv,
                                  workspace=self.ws, stream=self.stream)

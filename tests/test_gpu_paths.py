@@ -291,3 +291,37 @@ def test_bwd_ranges_equal_calls(cfg, cuts):
         torch.cuda.synchronize()
         for x, y in zip((dq, dk, dv), got):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("page,prefix,backward", [(16, 16 * 61 + 5, True), (16, 16 * 64, False),
+                                                  (64, 64 * 37 + 1, True), (32, 32 * 9, True)])
+def test_cyclic_replay_pages(page, prefix, backward):
+    """Cyclic shards through one table (pages of a key tile or more) and through
+    a table each (shorter ones), with and without a partly filled last page."""
+    import torch
+
+    import oracle as O
+    from paper_2607_14952_amd import inputs
+    from paper_2607_14952_amd.replay import ReplayStep, device_inputs
+    from tests._gpu import TOL_BF16, host, lse_err, rel_l2
+    cfg = _bf16(f"cyclic_p{page}", prefix, 21, page=page, shards=5, ownership="cyclic",
+                backward=backward)
+    h = inputs.dense_inputs(cfg)
+    step = ReplayStep(cfg, device_inputs(h))
+    print(f"[gpu] {cfg.name}", flush=True)
+    step.step()
+    torch.cuda.synchronize()
+    kw = dict(page_size=page, q_pos0=cfg.q_pos0, scale=cfg.scale)
+    o, l = O.attn_fwd(h["q"], h["k_pool"], h["v_pool"], h["page_table"], **kw)
+    assert rel_l2(host(step.out), o) <= TOL_BF16["out"]
+    assert lse_err(host(step.lse), l) <= TOL_BF16["lse"]
+    for c in range(cfg.n_shards):
+        pos = O.cyclic_owned_positions(prefix, page, cfg.n_shards, c)
+        so, sl = O.attn_fwd(h["q"], h["k_pool"], h["v_pool"], h["page_table"], key_positions=pos, **kw)
+        assert rel_l2(host(step.shard_out[c]), so) <= TOL_BF16["out"]
+        assert lse_err(host(step.shard_lse[c]), sl) <= TOL_BF16["lse"]
+    if backward:
+        refs = O.attn_bwd(h["q"], h["k_pool"], h["v_pool"], h["page_table"], h["d_out"],
+                          prefix_len=prefix, out=o, lse=l, **kw)
+        for got, ref in zip((step.dq, step.dk, step.dv), refs):
+            assert rel_l2(host(got), ref) <= TOL_BF16["grad"]
