@@ -480,16 +480,28 @@ hipError_t launch_backward(ls::BwdArgs& a, bool bf16, const std::vector<ls_split
       r.end[r.n] = p.end;
       r.per[r.n] = p.per;
       r.z0[r.n + 1] = r.z0[r.n] + p.chunks;
+      r.tail_x = p.tail_x;   // (plans with a tail join no others)
+      r.tail_per = p.tail_per;
+      r.tail_chunks = p.tail_chunks;
       ++r.n;
       if (!p.joins) {
         ++i;
         break;
       }
     }
-    float* part = r.z0[r.n] > 1 ? a.dq_part : nullptr;
+    float* part = r.z0[r.n] > 1 || r.tail_chunks > 0 ? a.dq_part : nullptr;
     e = bf16 ? ls::launch_dq_bf16_d256(a, r, part, s) : ls::launch_dq_f32_mfma(a, r, form, part, s);
-    if (e == hipSuccess && part)
-      e = ls::launch_dq_reduce(part, r, n, a.scale, a.accumulate_dq != 0, a.dq, s);
+    // the values of the rows before the tail, which wrote their result if in one chunk
+    const int64_t n_head = r.tail_chunks == 0
+        ? n : ((int64_t)r.tail_x * ls::kDqRows / a.group) * a.n_q_heads * a.head_dim;
+    if (e == hipSuccess && r.z0[r.n] > 1) {
+      e = ls::launch_dq_reduce(part, r, n_head, a.scale, a.accumulate_dq != 0, a.dq, s);
+      part += r.z0[r.n] * n_head;
+    }
+    if (e == hipSuccess && r.tail_chunks > 0) {
+      r.z0[1] = r.tail_chunks;
+      e = ls::launch_dq_reduce(part, r, n - n_head, a.scale, a.accumulate_dq != 0, a.dq + n_head, s);
+    }
     if (e != hipSuccess) return e;
     a.accumulate_dq = 1;
   }

@@ -32,7 +32,7 @@ namespace {
 constexpr int kD = 256;
 
 // ============================================================== dq kernel
-constexpr int kQBM = 128;
+constexpr int kQBM = kDqRows;
 constexpr int kQBN = kTileKeys;                   // 32
 constexpr int kRowBytes = kD * 2;                 // 512 B: one key row
 constexpr int kQStage = 2 * kTileBytes;           // K tile + V tile (row-major, swizzled)
@@ -232,7 +232,9 @@ __device__ __forceinline__ void dq_step(const BwdArgs& a, char* __restrict__ nex
 
 // Workgroup z works on a chunk of one of the key ranges.  With `part` each writes
 // its unscaled sums to part[z] and dq_reduce_kernel adds them in order; without,
-// there is one range in one chunk.
+// there is one range in one chunk.  Under a tail (DqRanges) the row tiles before
+// tail_x write their chunks first, or their result where they have one chunk, and
+// the tail's chunks follow, [chunk][token past the first of tail_x].
 template <PageForm kForm>
 __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a, DqRanges ranges,
                                                                   float* __restrict__ part) {
@@ -241,14 +243,40 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a, DqR
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform (scalar)
   const int l32 = lane & 31, hh = lane >> 5;
-#if LS_XCD_MAP
-  const WorkItem wi = xcd_work_item();
-#else
-  const WorkItem wi{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z};
-#endif
-  const int g = wi.y;
   const int lg = a.log2_group;
   const int rows_total = a.n_q << lg;
+  WorkItem wi;
+  int64_t slice = 0;          // the partial sums' place: slice * n_q_heads rows, tokens from tok0
+  int tok0 = 0;
+  bool direct = !part, tail_rows = false;
+  if (ranges.tail_chunks == 0) {
+#if LS_XCD_MAP
+    wi = xcd_work_item();
+#else
+    wi = WorkItem{(int)blockIdx.x, (int)blockIdx.y, (int)blockIdx.z};
+#endif
+    slice = (int64_t)wi.z * a.n_q;
+  } else {
+    const uint32_t head_x = ranges.tail_x, tail_x = (rows_total + kQBM - 1) / kQBM - head_x;
+    const uint32_t ny = a.n_kv_heads, n_head = head_x * ny * ranges.z0[1];
+    uint32_t w = tail_spread(blockIdx.x, gridDim.x, n_head);
+    const int split = (int)(head_x * kQBM) >> lg;   // first token of the tail
+    tail_rows = w >= n_head;
+    if (tail_rows) w -= n_head;
+    const uint32_t nx = tail_rows ? tail_x : head_x;
+    wi.x = (int)(w % nx + (tail_rows ? head_x : 0));
+    wi.y = (int)((w / nx) % ny);
+    wi.z = (int)(w / (nx * ny));
+    direct = !tail_rows && ranges.z0[1] == 1;
+    if (tail_rows) {
+      tok0 = split;
+      slice = (ranges.z0[1] > 1 ? (int64_t)ranges.z0[1] * split : 0) +
+              (int64_t)wi.z * (a.n_q - split);
+    } else {
+      slice = (int64_t)wi.z * split;
+    }
+  }
+  const int g = wi.y;
   const int row0 = wi.x * kQBM;
   const int prow = row0 + w * 32 + l32;
   const bool row_ok = prow < rows_total;
@@ -256,8 +284,9 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a, DqR
   const int head = (g << lg) + (prow & ((1 << lg) - 1));
   const int tok_first = row0 >> lg;
   const int tok_last = min(a.n_q - 1, (row0 + kQBM - 1) >> lg);
-  const int ri = ranges.of(wi.z);
-  const int64_t kv_begin = ranges.begin[ri], chunk_keys = (int64_t)ranges.per[ri] * kQBN;
+  const int ri = tail_rows ? 0 : ranges.of(wi.z);
+  const int64_t kv_begin = ranges.begin[ri];
+  const int64_t chunk_keys = (int64_t)(tail_rows ? ranges.tail_per : ranges.per[ri]) * kQBN;
   const int64_t c_lo = (kv_begin & ~int64_t(kQBN - 1)) + (wi.z - ranges.z0[ri]) * chunk_keys;
   const int64_t kb = max(kv_begin, c_lo);
   const int64_t ke = min(ranges.end[ri], c_lo + chunk_keys);
@@ -267,9 +296,9 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a, DqR
   const int64_t k_lo = kb & ~int64_t(kQBN - 1);
   const int n_tiles = k_hi > kb ? (int)((k_hi - k_lo + kQBN - 1) / kQBN) : 0;
 
-  const bool add = !part && a.accumulate_dq;
-  float* dq = part ? part + (((int64_t)wi.z * a.n_q + tok) * a.n_q_heads + head) * kD
-                   : a.dq + ((int64_t)tok * a.n_q_heads + head) * kD;
+  const bool add = direct && a.accumulate_dq;
+  float* dq = direct ? a.dq + ((int64_t)tok * a.n_q_heads + head) * kD
+                     : part + ((slice + tok - tok0) * a.n_q_heads + head) * kD;
   if (n_tiles == 0) {
     if (row_ok && !add) {
       const f32x4 z = {0.f, 0.f, 0.f, 0.f};
@@ -382,7 +411,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a, DqR
   wait_fetch();   // no direct load is left in flight when the waves end
 
   if (row_ok) {
-    const float c = part ? 1.f : a.scale;
+    const float c = direct ? a.scale : 1.f;
 #pragma unroll
     for (int db = 0; db < 8; ++db) {
 #pragma unroll
@@ -667,6 +696,51 @@ int dq_chunks(const BwdArgs& a, int64_t items, int64_t tiles) {
   return best;
 }
 
+// Time of n workgroups of `t` tile times on 256 CUs.  The last round's CUs clock
+// higher where fewer are busy (214 of 256: 1.18 us a tile instead of 1.32; 164:
+// 0.92 of 1.19; 96: 0.90).
+double rounds(int64_t n, double t) {
+  const double f = (double)(n % 256) / 256;
+  return t * ((double)(n / 256) + (f > 0 ? std::max(0.75, 0.36 + 0.64 * f) : 0.));
+}
+
+// A tail for a range of `chunks` chunks, where that is faster: the row tiles that
+// fill whole rounds keep few chunks, and those left over share one round among
+// all CUs in many, so that no round is nearly empty, within the same room for
+// partial sums (chunks of every row would need more: 258 items have room for
+// one).  Measured, one range of 204,800 keys, 16 heads on 2: 1,111 tokens (140
+// items) 5.35 -> 4.70 ms, 1,536 (192) 7.21 -> 6.43, 2,064 (258) 15.3 -> 8.6, 3,000
+// (376) 14.5 -> 12.5: 1,190-1,210 TFLOP/s, as 2,048 and 4,096 tokens reach.
+void plan_tail(const BwdArgs& a, int64_t tiles, DqPlan& p) {
+  const int64_t nx = ((int64_t)a.n_q * a.group + kQBM - 1) / kQBM, H = a.n_kv_heads;
+  const int64_t room = dq_part_rows(a.n_q, a.group) / a.n_q_heads;   // tokens
+  const double per_tok = 4.7e-4 * a.n_q_heads;
+  auto chunk = [&](int64_t c) { return (tiles + c - 1) / c; };
+  double least = 0.98 * (rounds(nx * H * p.chunks, (double)p.per + 6) +
+                         (p.chunks > 1 ? 5 + per_tok * a.n_q * p.chunks : 0.));
+  for (int64_t c1 = 1; c1 <= 4; ++c1) {
+    const int64_t hx = nx * H * c1 / 256 * 256 / (c1 * H);
+    if (hx == 0 || hx >= nx) continue;
+    const int64_t tok = hx * kQBM / a.group, parts = c1 > 1 ? c1 * tok : 0;
+    for (int64_t f = 1; f <= 4; f *= 2) {
+      const int64_t c2 = std::min({256 / ((nx - hx) * H * f), tiles / 4,
+                                   (room - parts) / (a.n_q - tok)});
+      if (c2 < 2) break;
+      const int64_t sums = parts + c2 * (a.n_q - tok);
+      const double cost = rounds(hx * H * c1, (double)chunk(c1) + 6) +
+                          rounds((nx - hx) * H * c2, (double)chunk(c2) + 6) + 5 +
+                          (c1 > 1 ? 5 : 0) + per_tok * (double)sums;
+      if (cost >= least) continue;
+      least = cost;
+      p.per = (int32_t)chunk(c1);
+      p.chunks = (int32_t)((tiles + p.per - 1) / p.per);
+      p.tail_x = (int32_t)hx;
+      p.tail_per = (int32_t)chunk(c2);
+      p.tail_chunks = (int32_t)((tiles + p.tail_per - 1) / p.tail_per);
+    }
+  }
+}
+
 }  // namespace
 
 DqPlan plan_dq_bf16_d256(const BwdArgs& a, int64_t begin, int64_t end) {
@@ -682,13 +756,18 @@ DqPlan plan_dq_bf16_d256(const BwdArgs& a, int64_t begin, int64_t end) {
   // stay together (1,111 tokens, 8 ranges of 12,500: 2,731 us apart, 2,825 joined),
   // and one whose single chunk fills half the chip writes its result itself.
   const int64_t wgs = items * chunks;
-  return DqPlan{begin, end, chunks, per, 0, wgs <= 256 && (chunks > 1 || wgs < 128)};
+  DqPlan p{begin, end, chunks, per, 0, wgs <= 256 && (chunks > 1 || wgs < 128)};
+  if (!p.joins) plan_tail(a, tiles, p);
+  return p;
 }
 
 hipError_t launch_dq_bf16_d256(const BwdArgs& a, const DqRanges& r, float* part,
                                hipStream_t stream) {
-  const dim3 grid((unsigned)(((int64_t)a.n_q * a.group + kQBM - 1) / kQBM), a.n_kv_heads,
-                  r.z0[r.n]);
+  const unsigned nx = (unsigned)(((int64_t)a.n_q * a.group + kQBM - 1) / kQBM);
+  const dim3 grid = r.tail_chunks == 0
+                        ? dim3(nx, a.n_kv_heads, r.z0[r.n])
+                        : dim3(a.n_kv_heads * ((unsigned)r.tail_x * r.z0[1] +
+                                               (nx - r.tail_x) * r.tail_chunks));
   // (pages of 8 and 16 rows: 2,336 -> 1,962 us per shard with the lookup per wave
   // instead of per row, 2,048 rows x 50,000 keys, as with longer pages)
   switch (page_form(a.log2_page)) {

@@ -38,6 +38,9 @@ inline int f32_dkdv_chunks(int n_q, int group) {
   return (int)(c < 16 ? c : 16);
 }
 
+// Packed query rows of a workgroup of the bf16 dq kernel.
+constexpr int kDqRows = 128;
+
 // Most rows (of head_dim floats) of dq partial sums that one key range's chunks
 // take: 512 workgroups, two per CU, of up to 128 packed rows.  The workspace has
 // room for two such ranges (dq_part_bytes).  Both grow with n_q, so that a workspace made
@@ -51,10 +54,13 @@ inline size_t dq_part_bytes(int n_q, int group, int head_dim) {
 }
 
 // Key ranges of one dq launch: workgroups z0[i] .. z0[i + 1] - 1 (grid z) work on
-// range i, chunks of `per` 32-key tiles of it.
+// range i, chunks of `per` 32-key tiles of it.  With tail_chunks (one range, bf16)
+// these are the chunks of the row tiles before tail_x; the others have tail_chunks
+// chunks of tail_per tiles, and the grid is the list of both (tail last).
 constexpr int kMaxDqRanges = 16;
 struct DqRanges {
   int32_t n;
+  int32_t tail_x = 0, tail_per = 0, tail_chunks = 0;
   int32_t z0[kMaxDqRanges + 1];
   int32_t per[kMaxDqRanges];
   int64_t begin[kMaxDqRanges], end[kMaxDqRanges];
@@ -71,6 +77,7 @@ struct DqPlan {
   int64_t begin, end;
   int32_t chunks, per, form;
   bool joins;               // may share a launch with other ranges (through partial sums)
+  int32_t tail_x = 0, tail_per = 0, tail_chunks = 0;   // as in DqRanges
 };
 
 // Whether the fp32 matrix-core kernels take these shapes (the generic kernels

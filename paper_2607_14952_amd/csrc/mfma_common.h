@@ -404,26 +404,22 @@ __device__ __forceinline__ WorkItem xcd_work_item() {
 // q + (k < r) slots (q, r = n / 8, n % 8) and q_l + (k < r_l) long items
 // (q_l, r_l for the long count), so the difference, its short count, is never
 // negative and the short counts add up to the slice.  With one slice it is
-// xcd_work_item.
-__host__ __device__ inline WorkItem tail_spread_item(uint32_t id, uint32_t nx, uint32_t ny,
-                                                     uint32_t nz) {
-  const uint32_t n = nx * ny * nz, nl = nx * ny * (nz - 1);
+// xcd_work_item.  tail_spread is the dealing for any n items, the first nl long.
+__host__ __device__ inline uint32_t tail_spread(uint32_t id, uint32_t n, uint32_t nl) {
   const uint32_t xcd = id % 8, slot = id / 8;
   const uint32_t q = n / 8, r = n % 8, ql = nl / 8, rl = nl % 8;
   const uint32_t long_begin = xcd * ql + (xcd < rl ? xcd : rl);
   const uint32_t long_cnt = ql + (xcd < rl ? 1u : 0u);
+  if (slot < long_cnt) return long_begin + slot;
+  return nl + (xcd * q + (xcd < r ? xcd : r)) - long_begin + (slot - long_cnt);
+}
+__host__ __device__ inline WorkItem tail_spread_item(uint32_t id, uint32_t nx, uint32_t ny,
+                                                     uint32_t nz) {
+  const uint32_t w = tail_spread(id, nx * ny * nz, nx * ny * (nz - 1));
   WorkItem it;
-  if (slot < long_cnt) {
-    const uint32_t w = long_begin + slot;
-    it.x = (int)(w % nx);
-    it.y = (int)((w / nx) % ny);
-    it.z = (int)(w / (nx * ny));
-  } else {
-    const uint32_t w = (xcd * q + (xcd < r ? xcd : r)) - long_begin + (slot - long_cnt);
-    it.x = (int)(w % nx);
-    it.y = (int)(w / nx);
-    it.z = (int)(nz - 1);
-  }
+  it.x = (int)(w % nx);
+  it.y = (int)((w / nx) % ny);
+  it.z = (int)(w / (nx * ny));
   return it;
 }
 __device__ __forceinline__ WorkItem xcd_work_item_tail_spread() {

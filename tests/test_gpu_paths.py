@@ -293,6 +293,45 @@ def test_bwd_ranges_equal_calls(cfg, cuts):
             assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("cfg,begin", [
+    # whole rounds of row tiles in two chunks, one tile a KV head (the last 64 packed
+    # rows, or 16 tokens of 32 heads) in many
+    (_bf16("tail_r1036", 9_600, 1_036), 17),
+    (_bf16("tail_g16", 7_000, 514, hq=32), 3),
+    # in one chunk, which writes its result itself
+    (_bf16("tail_r2056", 1_500, 2_056), 17),
+    (_bf16("tail_g1", 1_000, 8_200, hq=4, hkv=4), 0),
+    (_bf16("tail_half", 1_200, 3_000, page=8), 5),
+], ids=lambda x: getattr(x, "name", ""))
+def test_dq_tail(cfg, begin):
+    """A range whose last row tiles are cut into more key chunks than the others,
+    against ranges of seven key tiles, which are never cut.  P and dS are formed key
+    by key, so that only the order of the fp32 additions differs: under 1,000 of
+    them per element, 2^-24 of the running sum each (6e-5; 1e-6 where they fall at
+    random)."""
+    import torch
+
+    from paper_2607_14952_amd import inputs
+    from paper_2607_14952_amd.replay import device_inputs
+    dev = device_inputs(inputs.dense_inputs(cfg))
+    kv = B.PagedKV(dev["k_pool"], dev["v_pool"], dev["page_table"])
+    P, n = cfg.prefix_len, cfg.kv_len
+    kw = dict(prefix_len=P, q_pos0=P, scale=cfg.scale)
+    op, lp = B.prefix_attn_fwd(dev["q"], kv, [(0, n)], **kw)
+    out, lse = B.lse_merge(op, lp, out_dtype=dev["q"].dtype)
+    print(f"[gpu] dq tail {cfg.name}", flush=True)
+    cuts = [begin, *range((begin // 32 + 7) * 32, n, 224), n]
+    for flags in (0, B.FLAG_ACCUMULATE_DQ):
+        start = torch.full((cfg.resp_len, cfg.n_q_heads, cfg.head_dim), 0.5, device="cuda")
+        want, _, _ = B.prefix_attn_bwd_ranges(dev["q"], kv, dev["d_out"], out, lse,
+                                              list(zip(cuts, cuts[1:])), dq=start.clone(),
+                                              flags=flags, **kw)
+        got, _, _ = B.prefix_attn_bwd(dev["q"], kv, dev["d_out"], out, lse, kv_begin=begin,
+                                      kv_end=n, dq=start.clone(), flags=flags, **kw)
+        torch.cuda.synchronize()
+        assert (got - want).abs().max().item() <= 2e-5 * want.abs().max().item()
+
+
 @pytest.mark.parametrize("page,prefix,backward", [(16, 16 * 61 + 5, True), (16, 16 * 64, False),
                                                   (64, 64 * 37 + 1, True), (32, 32 * 9, True)])
 def test_cyclic_replay_pages(page, prefix, backward):
