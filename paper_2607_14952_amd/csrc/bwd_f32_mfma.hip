@@ -23,6 +23,8 @@
 // keys, 8 heads of 128 on 2 KV heads 25.8 -> 0.55 ms (dq at 100 TFLOP/s of the
 // 154 an fp32 GEMM reaches: the matrix cores are busy 73% of the time, with two
 // waves per SIMD where four row groups share a tile; with one, 0.61 ms).
+#include <math.h>
+
 #include <algorithm>
 
 #include "f32_mfma.h"
@@ -331,12 +333,35 @@ DqPlan plan_dq_f32_mfma(const BwdArgs& a, int64_t begin, int64_t end) {
   const int64_t wide = (rows + 127) / 128 * a.n_kv_heads, narrow = (rows + 31) / 32 * a.n_kv_heads;
   // Chunks of at least 8 (4) key tiles, enough for two workgroups on each CU
   // and no more than the partial sums have room for.  Four row groups share
-  // a staged tile where that still gives every CU its two workgroups.
-  const int64_t room = dq_part_rows(a.n_q, a.group) / ((int64_t)a.n_q * a.n_q_heads);
-  const bool share = wide * std::min(std::max<int64_t>(room, 1), (n_tiles + 7) / 8) >= 512;
+  // a staged tile where that still gives nearly every CU its two workgroups: 32-row
+  // ones in more rounds are slower where the sums have room for 456 (600 tokens x 24
+  // heads on 3 over 30,000 keys: 4,390 us, shared 3,215) or 510 (516 x 8 on 2 over
+  // 16,001: 912 and 573; 260 x 24 on 3 over 30,000: 1,665 and 971).
+  const int64_t room = std::max<int64_t>(1, dq_part_rows(a.n_q, a.group) / ((int64_t)a.n_q * a.n_q_heads));
+  const int64_t most = std::min(room, (n_tiles + 7) / 8);
+  const bool share = wide * most >= 448;
+  int64_t want = 1;
+  if (share) {
+    // Of the counts that fill one to three rounds of two workgroups per CU, the
+    // least tiles a CU takes one after another (a last round of single workgroups
+    // takes 0.6 of the time; 3 tiles for a start and end).  One workgroup more than
+    // a round holds costs a round: 200 tokens x 16 heads on 2 over 20,000 keys, 520
+    // workgroups 304 us, 494 261; 600 x 3 on 3 over 10,000 135 and 119.
+    double least = INFINITY;
+    for (int64_t k = 0; k <= 3; ++k) {
+      const int64_t c = std::max<int64_t>(1, std::min(512 * k / wide, most));
+      const int64_t n = wide * c, last = n % 512;
+      const double cost = ((double)(n / 512) + (last == 0 ? 0. : last <= 256 ? 0.6 : 1.)) *
+                          ((double)((n_tiles + c - 1) / c) + 3);
+      if (cost < least) {
+        least = cost;
+        want = c;
+      }
+    }
+  } else {
+    want = std::max<int64_t>(1, std::min({(512 + narrow - 1) / narrow, (n_tiles + 3) / 4, room}));
+  }
   const int64_t items = share ? wide : narrow;
-  int64_t want = std::min((512 + items - 1) / items, (n_tiles + (share ? 7 : 3)) / (share ? 8 : 4));
-  want = std::max<int64_t>(1, std::min(want, room));
   const int64_t unit = share ? 1 : 4;                // whole iterations of the workgroup
   const int64_t per = ((n_tiles + want - 1) / want + unit - 1) / unit * unit;
   const int64_t chunks = (n_tiles + per - 1) / per;
