@@ -290,7 +290,7 @@ struct TopkShared {
     };
   };
   uint32_t wave_gt[kKWaves], wave_eq[kKWaves], wcount[kKWaves], wave_sum[kKWaves];
-  uint32_t bin, above, count;
+  uint32_t bin, above, in_bin, count;
 };
 
 static_assert(sizeof(TopkShared) <= 80 * 1024, "two top-k workgroups per CU");
@@ -300,10 +300,12 @@ __device__ __forceinline__ float key_float(uint32_t key) {
 }
 
 // The bin b of hist[0 .. nbins) holding the need-th largest (counting from the
-// top) and the number of keys in bins above it, by the whole workgroup: need >= 1
-// and the histogram holds at least need keys (else bin 0, 0 above).  A thread
-// sums kPer neighbouring bins, from its own start so that a wave's reads
-// spread over the banks.
+// top), the number of keys in it and in bins above it, by the whole workgroup:
+// need >= 1 and the histogram holds at least need keys (else bin 0 with 0 and 0).
+// hist itself is read by nobody after this (a wave may go on to clear it for the
+// next digit while others still have the results to read).  A thread sums kPer
+// neighbouring bins, from its own start so that a wave's reads spread over the
+// banks.
 template <int kPer>
 __device__ __forceinline__ void find_crossing(TopkShared& sh, uint32_t need, int tid) {
   const int lane = tid & 63, wv = tid >> 6;
@@ -317,7 +319,7 @@ __device__ __forceinline__ void find_crossing(TopkShared& sh, uint32_t need, int
     if (lane + d < 64) incl += o;
   }
   if (lane == 0) sh.wave_sum[wv] = incl;
-  if (tid == 0) sh.bin = sh.above = 0;
+  if (tid == 0) sh.bin = sh.above = sh.in_bin = 0;
   __syncthreads();
   for (int v = wv + 1; v < kKWaves; ++v) incl += sh.wave_sum[v];
   const uint32_t excl = incl - mine;
@@ -330,6 +332,7 @@ __device__ __forceinline__ void find_crossing(TopkShared& sh, uint32_t need, int
     }
     sh.bin = (uint32_t)b;
     sh.above = acc;
+    sh.in_bin = sh.hist[b];
   }
   __syncthreads();
 }
@@ -585,7 +588,7 @@ __global__ __launch_bounds__(kKThreads) void topk_kernel(TopkArgs a) {
   // first digit: key bits 31..20
   histogram(20, 12, 0, 0);
   crossing(4096, (uint32_t)a.k);
-  const uint32_t b1 = sh.bin, above1 = sh.above, in_bin = sh.hist[b1];
+  const uint32_t b1 = sh.bin, above1 = sh.above, in_bin = sh.in_bin;
   uint32_t T, gt_total;
   if (in_bin <= (uint32_t)kKCap) {
     // gather the bin's keys into LDS (with their columns) and count, per wave

@@ -1,0 +1,80 @@
+"""The top-k kernel's own source on the CPU (topk_host.cpp): the selection with each
+wave ahead of the others in turn, as far as the barriers let it."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2607_14952_amd", "csrc")
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ missing")
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("topk_host")
+    with open(os.path.join(CSRC, "dsa_select.hip")) as f:
+        src = f.read()
+    kernel = src[src.index("// ---------------------------------------------------------------- top-k"):]
+    launch = kernel[kernel.index("// Chunks of a row."):kernel.rindex("}  // namespace ls")]
+    (tmp / "topk_section.inc").write_text(kernel[:kernel.index("}  // namespace")])
+    (tmp / "topk_launch.inc").write_text(launch)
+    so = tmp / "topk_host.so"
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wno-unknown-pragmas", "-I",
+           os.path.join(HERE, "host_shim"), "-I", CSRC, "-I", str(tmp),
+           os.path.join(HERE, "topk_host.cpp"), "-o", str(so)]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout[-4000:]
+    return ctypes.CDLL(str(so))
+
+
+def order_key(x):
+    """The library's order of scores, as integers: -0 below +0."""
+    key = x.view(np.int32)
+    return np.where(key < 0, key ^ 0x7FFFFFFF, key).astype(np.int64)
+
+
+def check(lib, x, k, n_chunks=1, orders=(0, 1, 2)):
+    """The kernel's selection from the rows of x, against a stable sort's."""
+    rows, n = x.shape
+    flat = np.zeros(rows * n + 4, np.float32)
+    at = -flat.ctypes.data // 4 % 4     # 16-byte aligned
+    buf = flat[at:at + rows * n].reshape(rows, n)
+    buf[:] = x
+    c = ctypes
+    for order in orders:
+        pos, sc = np.full((rows, k), -7, np.int32), np.zeros((rows, k), np.float32)
+        parted = lib.topk_host(c.c_void_p(buf.ctypes.data), c.c_int64(n), None, rows, c.c_int64(n),
+                               c.c_int64(5), k, c.c_void_p(pos.ctypes.data),
+                               c.c_void_p(sc.ctypes.data), c.c_int64(k), n_chunks, order)
+        assert not parted, f"threads wait at different barriers (order {order})"
+        for r in range(rows):
+            want = np.sort(np.argsort(-order_key(x[r]), kind="stable")[:k])
+            assert np.array_equal(pos[r], want + 5), f"order {order}"
+            assert np.array_equal(sc[r].view(np.int32), x[r, want].view(np.int32))
+
+
+@pytest.mark.parametrize("value,n,k", [(-2.5, 5_000, 300), (-3.0e38, 4_500, 2_000), (1.5, 5_000, 9)])
+def test_many_keys_in_the_threshold_bin(lib, value, n, k):
+    """More keys share the threshold's first digit than the LDS list holds: the row is
+    passed over again.  At -2 and below, that digit's own count lies where the next
+    histogram begins, which no wave may clear before every wave has read it."""
+    x = np.full((1, n), value, np.float32)
+    check(lib, x, k)
+    x[0, ::7] *= np.float32(1 + 2.0 ** -20)   # two keys in one bin
+    check(lib, x, k)
+
+
+@pytest.mark.parametrize("kind", ["normal", "ties", "mostly_inf"])
+@pytest.mark.parametrize("n,k,n_chunks", [(3_001, 300, 1), (66_000, 700, 1), (140_001, 512, 2)])
+def test_selection(lib, kind, n, k, n_chunks):
+    rng = np.random.default_rng(n + k)
+    x = rng.standard_normal((1, n)).astype(np.float32)
+    if kind == "ties":
+        x = np.round(x * 4) / np.float32(4)
+    elif kind == "mostly_inf":
+        x[:, k // 2:] = -np.inf
+    check(lib, x, k, n_chunks, orders=(0, 1) if n < 10_000 else (1,))
