@@ -479,7 +479,8 @@ __global__ __launch_bounds__(kKThreads) void topk_kernel(TopkArgs a) {
       for (int u = 0; u < kFUnroll; ++u) {
         const int64_t i = i0 + 256 * u + 4 * lane;
         // (the float order puts -0 and the NaNs of the key order's low end in
-        // too; keys below the bound among the candidates do no harm)
+        // too: candidates below the bound, which the threshold found among them
+        // tells apart)
         bool in[4];
         uint64_t m[4];
 #pragma unroll
@@ -516,7 +517,8 @@ __global__ __launch_bounds__(kKThreads) void topk_kernel(TopkArgs a) {
       fits = fits && sh.wcount[v] <= (uint32_t)kFCap;
     }
     if (fits && total >= (uint32_t)a.k) {
-      // every key >= lkey is a candidate, so counts among them are exact
+      // every key >= lkey is a candidate, so the threshold found among them is
+      // the row's if it is no lower
       auto cand_hist = [&](int shift, int bits, int pbits, uint32_t prefix) {
         for (int b = tid; b < (1 << bits); b += kKThreads) sh.hist[b] = 0;
         __syncthreads();
@@ -540,47 +542,49 @@ __global__ __launch_bounds__(kKThreads) void topk_kernel(TopkArgs a) {
       crossing(1024, (uint32_t)a.k - ab1 - ab2);
       const uint32_t Tf = (c1 << 20) | (c2 << 10) | sh.bin;
       const uint32_t need_eq_f = (uint32_t)a.k - (ab1 + ab2 + sh.above);
-      // per wave region: keys above and equal to the threshold
-      uint32_t g = 0, e = 0;
-      for (uint32_t j = lane; j < wcount; j += 64) {
-        const uint32_t key = sh.wkey[wv][j];
-        g += key > Tf ? 1u : 0u;
-        e += key == Tf ? 1u : 0u;
-      }
-      g = __reduce_add_sync(~0ull, g);
-      e = __reduce_add_sync(~0ull, e);
-      if (lane == 0) {
-        sh.wave_gt[wv] = g;
-        sh.wave_eq[wv] = e;
-      }
-      __syncthreads();
-      uint32_t fbase = 0, feq_before = 0;
-      for (int v = 0; v < wv; ++v) {
-        const uint32_t take =
-            feq_before >= need_eq_f ? 0u : min(sh.wave_eq[v], need_eq_f - feq_before);
-        fbase += sh.wave_gt[v] + take;
-        feq_before += sh.wave_eq[v];
-      }
-      uint32_t run_sel = 0, run_eq = 0;
-      for (uint32_t j0 = 0; j0 < wcount; j0 += 64) {
-        const uint32_t j = j0 + lane;
-        const bool ok = j < wcount;
-        const uint32_t key = ok ? sh.wkey[wv][j] : 0u;
-        const bool gt = ok && key > Tf, eq = ok && key == Tf;
-        const uint64_t eqm = __ballot(eq);
-        const uint32_t eq_rank = feq_before + run_eq + (uint32_t)__popcll(eqm & below);
-        const bool sel = gt || (eq && eq_rank < need_eq_f);
-        const uint64_t selm = __ballot(sel);
-        const uint32_t o = fbase + run_sel + (uint32_t)__popcll(selm & below);
-        if (sel && o < (uint32_t)a.k) {
-          const int32_t i = sh.widx[wv][j];
-          op[o] = pos_of(i);
-          if (os) os[o] = key_float(key);
+      if (Tf >= lkey) {
+        // per wave region: keys above and equal to the threshold
+        uint32_t g = 0, e = 0;
+        for (uint32_t j = lane; j < wcount; j += 64) {
+          const uint32_t key = sh.wkey[wv][j];
+          g += key > Tf ? 1u : 0u;
+          e += key == Tf ? 1u : 0u;
         }
-        run_sel += (uint32_t)__popcll(selm);
-        run_eq += (uint32_t)__popcll(eqm);
+        g = __reduce_add_sync(~0ull, g);
+        e = __reduce_add_sync(~0ull, e);
+        if (lane == 0) {
+          sh.wave_gt[wv] = g;
+          sh.wave_eq[wv] = e;
+        }
+        __syncthreads();
+        uint32_t fbase = 0, feq_before = 0;
+        for (int v = 0; v < wv; ++v) {
+          const uint32_t take =
+              feq_before >= need_eq_f ? 0u : min(sh.wave_eq[v], need_eq_f - feq_before);
+          fbase += sh.wave_gt[v] + take;
+          feq_before += sh.wave_eq[v];
+        }
+        uint32_t run_sel = 0, run_eq = 0;
+        for (uint32_t j0 = 0; j0 < wcount; j0 += 64) {
+          const uint32_t j = j0 + lane;
+          const bool ok = j < wcount;
+          const uint32_t key = ok ? sh.wkey[wv][j] : 0u;
+          const bool gt = ok && key > Tf, eq = ok && key == Tf;
+          const uint64_t eqm = __ballot(eq);
+          const uint32_t eq_rank = feq_before + run_eq + (uint32_t)__popcll(eqm & below);
+          const bool sel = gt || (eq && eq_rank < need_eq_f);
+          const uint64_t selm = __ballot(sel);
+          const uint32_t o = fbase + run_sel + (uint32_t)__popcll(selm & below);
+          if (sel && o < (uint32_t)a.k) {
+            const int32_t i = sh.widx[wv][j];
+            op[o] = pos_of(i);
+            if (os) os[o] = key_float(key);
+          }
+          run_sel += (uint32_t)__popcll(selm);
+          run_eq += (uint32_t)__popcll(eqm);
+        }
+        return;
       }
-      return;
     }
     __syncthreads();   // (the full-row passes reuse the LDS)
   }

@@ -78,3 +78,18 @@ def test_selection(lib, kind, n, k, n_chunks):
     elif kind == "mostly_inf":
         x[:, k // 2:] = -np.inf
     check(lib, x, k, n_chunks, orders=(0, 1) if n < 10_000 else (1,))
+
+
+def test_nan_does_not_fill_up_a_bound_too_high(lib):
+    """The sampled blocks hold all the large keys, so that fewer than k of the row's keys
+    reach the bound; NaNs with the sign bit set (the lowest of the key order) pass the
+    bound's float comparison and bring the candidates to k or more.  The row's selection
+    is of its finite keys all the same."""
+    n, k = 66_000, 700
+    rng = np.random.default_rng(3)
+    x = rng.uniform(-1, 1, (1, n)).astype(np.float32)
+    sampled = np.concatenate([np.arange(256) + (j * n // 64 & ~3) for j in range(64)])
+    x[0, rng.choice(sampled, 400, replace=False)] = rng.uniform(5, 9, 400).astype(np.float32)
+    others = np.setdiff1d(np.arange(n), sampled)
+    x.view(np.uint32)[0, rng.choice(others, 600, replace=False)] = 0xFFC00000
+    check(lib, x, k)
