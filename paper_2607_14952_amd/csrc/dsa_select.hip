@@ -770,17 +770,25 @@ hipError_t launch_dsa_scores(const DsaArgs& args, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Keys of each of a row's chunks but the last, which has the rest: whole 1 KiB
+// pieces, so that every chunk begins as the row is aligned.
+static int64_t topk_chunk_len(int64_t n, int n_chunks) {
+  return ((n + n_chunks - 1) / n_chunks + 255) / 256 * 256;
+}
+
 // Chunks of a row.  A workgroup takes about 20 us and 0.17 us per 1,024 keys,
 // 512 run at a time (two per CU); a second launch selects from the chunks' k
-// candidates each, about 20 us and 0.3 us per 1,024 of these.  Chunks keep at
-// least kFMinN keys (and so more than k).  Measured, k = 2,048: 1 row x 1M 196
-// -> 93 us (16 chunks), 128 rows x 1M 238 -> 158 us (4), 32 rows x 524,288 132
-// -> 80 us (8); 131,072 columns stay whole.
+// candidates each, about 20 us and 0.3 us per 1,024 of these.  Every chunk keeps
+// at least kFMinN keys, and so more than k and the sampled path (a last one of
+// 65,273 would take the full-row passes while the others wait).  Measured, k =
+// 2,048: 1 row x 1M 196 -> 93 us (16 chunks), 128 rows x 1M 238 -> 158 us (4),
+// 32 rows x 524,288 132 -> 80 us (8); 131,072 columns stay whole.
 int topk_chunks(int64_t n_rows, int64_t n, int k) {
   if (k > kFMaxK || n_rows <= 0) return 1;
   int best = 1;
   double least = 20 + 1.7e-4 * (double)n;
-  for (int c = 2; c <= 16 && n_rows * c <= 512 && n / c >= kFMinN; ++c) {
+  for (int c = 2; c <= 16 && n_rows * c <= 512; ++c) {
+    if (n - (c - 1) * topk_chunk_len(n, c) < kFMinN) continue;
     const double cost = 40 + 1.7e-4 * (double)n / c + 3e-4 * (double)c * k;
     if (cost < least) {
       best = c;
@@ -797,7 +805,7 @@ hipError_t launch_topk(const TopkArgs& args, int n_chunks, int32_t* cand_pos, fl
   if (n_chunks > 1) {
     // each chunk's k largest, in ascending position order, chunk after chunk:
     // the row's selection is among them, ties still resolved by position
-    a.seg = ((a.n + n_chunks - 1) / n_chunks + 255) / 256 * 256;
+    a.seg = topk_chunk_len(a.n, n_chunks);
     a.out_pos = cand_pos;
     a.out_scores = cand_scores;
     a.out_ld = (int64_t)n_chunks * a.k;

@@ -19,7 +19,7 @@ def lib(tmp_path_factory):
     with open(os.path.join(CSRC, "dsa_select.hip")) as f:
         src = f.read()
     kernel = src[src.index("// ---------------------------------------------------------------- top-k"):]
-    launch = kernel[kernel.index("// Chunks of a row."):kernel.rindex("}  // namespace ls")]
+    launch = kernel[kernel.index("// Keys of each of a row's chunks"):kernel.rindex("}  // namespace ls")]
     (tmp / "topk_section.inc").write_text(kernel[:kernel.index("}  // namespace")])
     (tmp / "topk_launch.inc").write_text(launch)
     so = tmp / "topk_host.so"
@@ -93,3 +93,19 @@ def test_nan_does_not_fill_up_a_bound_too_high(lib):
     others = np.setdiff1d(np.arange(n), sampled)
     x.view(np.uint32)[0, rng.choice(others, 600, replace=False)] = 0xFFC00000
     check(lib, x, k)
+
+
+def test_chunks_keep_the_sampled_path(lib):
+    """Every chunk that the rule cuts, the last one too, has the 65,536 keys from which
+    on a row is sampled; the launch's chunks are the rule's."""
+    c = ctypes
+    cut = 0
+    for n in [1_029_369, *range(131_072, 1_048_577, 1_073)]:
+        for rows, k in ((1, 2048), (3, 700), (40, 64)):
+            m = lib.topk_chunk_count(c.c_int64(rows), c.c_int64(n), k)
+            assert 1 <= m <= 16
+            if m > 1:
+                seg = lib.topk_chunk_len(c.c_int64(n), m)
+                assert seg % 256 == 0 and (m - 1) * seg + 65_536 <= n <= m * seg, (n, m)
+                cut += 1
+    assert cut > 100

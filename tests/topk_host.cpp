@@ -166,6 +166,10 @@ extern "C" int topk_chunk_count(int64_t n_rows, int64_t n, int k) {
   return ls::topk_chunks(n_rows, n, k);
 }
 
+extern "C" int topk_chunk_len(int64_t n, int n_chunks) {
+  return (int)ls::topk_chunk_len(n, n_chunks);
+}
+
 // ls_topk_select_ws on host memory; n_chunks 0: as topk_chunks says.  Nonzero
 // when the waves of a workgroup waited at different barriers.
 extern "C" int topk_host(const float* scores, int64_t ld, const int32_t* positions, int32_t n_rows,
