@@ -266,11 +266,11 @@ __device__ __forceinline__ uint32_t okey(float x) {
 }
 
 // Sampled-bound path: rows of at least kFMinN keys and k <= kFMaxK, 16-byte
-// aligned.  64 sample blocks of up to 1,024 keys bound the threshold from
-// below; one pass then gathers every key at or above the bound into a
-// per-wave LDS region (in position order), and the selection is resolved
-// there.  A region overflow, or fewer than k keys at or above the bound,
-// falls back to the full-row passes.  One workgroup looks through about 5 keys
+// aligned.  A sample of 16,384 to 65,536 keys bounds the threshold from below;
+// one pass then gathers every key at or above the bound into a per-wave LDS
+// region (in position order), and the selection is resolved there.  A region
+// overflow, or fewer than k keys at or above the bound, falls back to the
+// full-row passes.  One workgroup looks through about 5 keys
 // per ns, however many CUs are idle, so few long rows are cut (topk_chunks).
 constexpr int64_t kFMinN = 65536;
 constexpr int kFMaxK = 2048;
@@ -390,27 +390,31 @@ __global__ __launch_bounds__(kKThreads) void topk_kernel(TopkArgs a) {
   };
 
   if (n >= kFMinN && a.k <= kFMaxK && (reinterpret_cast<uintptr_t>(x) & 15) == 0) {
-    // --- sample: 64 blocks spread over the row; digit histograms of their keys
-    const int blk = (int)min<int64_t>(1024, max<int64_t>(256, (n / 2048) / 256 * 256));
+    // --- sample: n_s keys in blocks of 32 (128 bytes) spread evenly over the row, in
+    // digit histograms.  Neighbouring scores may resemble each other, and a longer
+    // block then says little more than a short one: of rows smoothed over 16 to 256
+    // positions (k = 512 and 2,048, 65,536 to 1M keys) 12% left this path with 64
+    // blocks of 256 keys and a margin of six deviations, 6% with these.  500 rows
+    // smoothed over 64, k = 2,048, the whole selection: 65,536 keys 106 -> 57 us,
+    // 524,288 777 -> 631; in random order 57.7 -> 56.6 and 231 -> 229.
+    const int n_s = 64 * (int)min<int64_t>(1024, max<int64_t>(256, (n / 2048) / 256 * 256));
+    const int64_t apart = n / (n_s / 32);   // (>= 32: n >= kFMinN)
     auto sample_hist = [&](int shift, int bits, int pbits, uint32_t prefix) {
       for (int b = tid; b < (1 << bits); b += kKThreads) sh.hist[b] = 0;
       __syncthreads();
-      // the wave's blocks in 256-key pieces, eight loads in flight
-      const int per_blk = blk / 256, pieces = 64 / kKWaves * per_blk;
+      // 8 blocks a wave and load, eight loads in flight
+      const int pieces = n_s / 256 / kKWaves;
       for (int p0 = 0; p0 < pieces; p0 += kFUnroll) {
         f32x4 v[kFUnroll];
-        bool in[kFUnroll];
 #pragma unroll
         for (int u = 0; u < kFUnroll; ++u) {
-          const int p = p0 + u, j = wv + kKWaves * (p / per_blk);
-          const int64_t start = ((int64_t)j * n / 64) & ~int64_t(3);
-          const int64_t i = start + 256 * (p % per_blk) + 4 * lane;
-          in[u] = p < pieces && i + 3 < n;
-          v[u] = *reinterpret_cast<const f32x4*>(x + (in[u] ? i : 0));
+          const int j = 8 * (wv + kKWaves * min(p0 + u, pieces - 1)) + (lane >> 3);
+          const int64_t i = (((int64_t)j * apart) & ~int64_t(31)) + 4 * (lane & 7);
+          v[u] = *reinterpret_cast<const f32x4*>(x + i);
         }
 #pragma unroll
         for (int u = 0; u < kFUnroll; ++u) {
-          if (!in[u]) continue;
+          if (p0 + u >= pieces) continue;
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             const uint32_t key = okey(v[u][c]);
@@ -422,29 +426,17 @@ __global__ __launch_bounds__(kKThreads) void topk_kernel(TopkArgs a) {
       __syncthreads();
     };
     sample_hist(20, 12, 0, 0);
-    // samples actually read: blocks whose 4-key groups lie inside the row
-    uint32_t n_s = 0;
-    for (int b = tid; b < 4096; b += kKThreads) n_s += sh.hist[b];
-    n_s = __reduce_add_sync(~0ull, n_s);
-    if (lane == 0) sh.wave_gt[wv] = n_s;
-    __syncthreads();
-    n_s = 0;
-    for (int v = 0; v < kKWaves; ++v) n_s += sh.wave_gt[v];
-    // bound: the sample key, to 22 bits, at which the sample count from the
-    // top reaches the count expected above the k-th key and six of its standard
-    // deviations more (a row in random order then falls short of k about once
-    // in 10^8)
+    // bound: the sample key, to 22 bits, at which the sample count from the top
+    // reaches the count expected above the k-th key and half of it more, or six of
+    // its standard deviations (for keys in random order) where these are more
     const double expect = (double)a.k * (double)n_s / (double)n;
-    const double want = ceil(expect + 6.0 * sqrt(expect) + 8.0);
+    const double want = ceil(expect + max<double>(0.5 * expect, 6.0 * sqrt(expect) + 8.0));
     const uint32_t need_s = (uint32_t)min<double>((double)n_s, want);
-    uint32_t lkey = 0;
-    if (need_s >= 1) {
-      crossing(4096, need_s);
-      const uint32_t s1 = sh.bin, sa1 = sh.above;
-      sample_hist(10, 10, 12, s1);
-      crossing(1024, need_s - sa1);
-      lkey = (s1 << 20) | (sh.bin << 10);
-    }
+    crossing(4096, need_s);
+    const uint32_t s1 = sh.bin, sa1 = sh.above;
+    sample_hist(10, 10, 12, s1);
+    crossing(1024, need_s - sa1);
+    const uint32_t lkey = (s1 << 20) | (sh.bin << 10);
     // --- one pass: wave v gathers its segment's keys >= lkey, in position order
     const int64_t fseg = ((n + kKWaves - 1) / kKWaves + 255) / 256 * 256;
     const int64_t flo = (int64_t)wv * fseg, fhi = min(n, flo + fseg);

@@ -88,8 +88,8 @@ def test_nan_does_not_fill_up_a_bound_too_high(lib):
     n, k = 66_000, 700
     rng = np.random.default_rng(3)
     x = rng.uniform(-1, 1, (1, n)).astype(np.float32)
-    sampled = np.concatenate([np.arange(256) + (j * n // 64 & ~3) for j in range(64)])
-    x[0, rng.choice(sampled, 400, replace=False)] = rng.uniform(5, 9, 400).astype(np.float32)
+    sampled = np.concatenate([np.arange(32) + (j * (n // 512) & ~31) for j in range(512)])
+    x[0, rng.choice(sampled, 450, replace=False)] = rng.uniform(5, 9, 450).astype(np.float32)
     others = np.setdiff1d(np.arange(n), sampled)
     x.view(np.uint32)[0, rng.choice(others, 600, replace=False)] = 0xFFC00000
     check(lib, x, k)
@@ -109,3 +109,21 @@ def test_chunks_keep_the_sampled_path(lib):
                 assert seg % 256 == 0 and (m - 1) * seg + 65_536 <= n <= m * seg, (n, m)
                 cut += 1
     assert cut > 100
+
+
+@pytest.mark.parametrize("width", [64, 256])
+def test_smooth_rows_stay_on_the_sampled_path(lib, width):
+    """Neighbouring scores of an index resemble each other.  Rows smoothed over so many
+    positions select as those in random order do, without the passes over the whole
+    row that follow a bound too high (told by the barriers passed)."""
+    n, k = 65_536, 2_048
+    window = np.zeros(n)
+    window[:width] = np.hanning(width + 2)[1:-1]
+
+    def barriers(x):
+        check(lib, x[None], k, orders=(0,))
+        return lib.topk_barriers()
+    rows = [np.random.default_rng(s).standard_normal(n) for s in range(24)]
+    usual = barriers(rows[0].astype(np.float32))
+    smooth = [np.fft.irfft(np.fft.rfft(r) * np.fft.rfft(window), n).astype(np.float32) for r in rows]
+    assert sum(barriers(r / r.std()) != usual for r in smooth) == 0

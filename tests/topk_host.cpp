@@ -34,6 +34,7 @@ struct Group {
   void (*body)(const ls::TopkArgs&) = nullptr;
   const ls::TopkArgs* args = nullptr;
   bool diverged = false;
+  int barriers = 0;
 };
 Group g;
 int order = 0;           // 0: waves ascending, 1: descending, 2: odd waves first
@@ -157,6 +158,7 @@ static void emu_launch(void (*)(ls::TopkArgs), dim3 grid, dim3 block, const ls::
           return;
         }
         done = g.t[0].state == kDone;
+        g.barriers += !done;
         for (int i = 0; i < g.n && !done; ++i) g.t[i].state = kRun;
       }
     }
@@ -165,6 +167,9 @@ static void emu_launch(void (*)(ls::TopkArgs), dim3 grid, dim3 block, const ls::
 extern "C" int topk_chunk_count(int64_t n_rows, int64_t n, int k) {
   return ls::topk_chunks(n_rows, n, k);
 }
+
+// Barriers that the workgroups of the last call passed.
+extern "C" int topk_barriers() { return emu::g.barriers; }
 
 extern "C" int topk_chunk_len(int64_t n, int n_chunks) {
   return (int)ls::topk_chunk_len(n, n_chunks);
@@ -188,6 +193,7 @@ extern "C" int topk_host(const float* scores, int64_t ld, const int32_t* positio
   a.k = k;
   emu::order = order;
   emu::g.diverged = false;
+  emu::g.barriers = 0;
   if (n_chunks == 0) n_chunks = ls::topk_chunks(n_rows, n, k);
   std::vector<int32_t> cand((size_t)n_rows * n_chunks * k);
   std::vector<float> cand_scores(cand.size());
