@@ -137,7 +137,13 @@ def fine_splits(cfg, splits, n_rows=None):
 
 
 class ReplayStep:
-    """Buffers and call sequence of one fwd(+bwd) replay over a config's shards."""
+    """Buffers and call sequence of one fwd(+bwd) replay over a config's shards.
+
+    shards[s] is shard s's key range and splits[i] that of part i (out_part[i],
+    lse_part[i]; shard s has parts groups[s] and the ranges shard_splits[s]), as
+    shard_kv[s] names positions: a cyclic shard's store has its owned pages first,
+    so that its keys are 0 .. shard_len - 1.  Forward-only and fp32 steps have more
+    parts than configured splits (fine_splits)."""
 
     def __init__(self, cfg, dev: dict, *, backward: bool | None = None, stream=None):
         import torch
@@ -146,33 +152,31 @@ class ReplayStep:
         self.kv = B.PagedKV(dev["k_pool"], dev["v_pool"], dev["page_table"])
         self.backward_enabled = cfg.backward if backward is None else backward
         self.stream = stream
+        self._shard_kv = None
         q = dev["q"]
         R, Hq, D, Dv = cfg.resp_len, cfg.n_q_heads, cfg.head_dim, cfg.head_dim_v
         own = (cfg.prefix_len, cfg.kv_len)
-        if cfg.ownership == "cyclic":
-            table = dev["page_table"].cpu().numpy()
+        self.cyclic = cfg.ownership == "cyclic"
+        if self.cyclic:
+            self._table = dev["page_table"].cpu().numpy()
             owners = [c for c in range(cfg.n_shards) if cfg.shard_len(c)]
             splits = [cfg.virtual_splits(c) for c in owners] + [[own]]
-
-            def store(pages):
-                t = table.copy()
-                t[:len(pages)] = table[pages]
-                return B.PagedKV(dev["k_pool"], dev["v_pool"], torch.from_numpy(t).to(q.device))
-
+            self.shards = [(0, cfg.shard_len(c)) for c in owners] + [own]
             if cfg.page_size >= 32:
-                self.shards, order = cyclic_shards(cfg)
-                self.stores = [store(order)]
-                splits = [[(b + i, b + j) for i, j in sp]
-                          for sp, (b, _) in zip(splits, self.shards[:-1])] + [[own]]
+                self._ranges, order = cyclic_shards(cfg)
+                self.stores = [self._store(order)]
             else:
-                self.shards = [(0, cfg.shard_len(c)) for c in owners] + [own]
-                self.stores = [store(cfg.shard_pages(c)) for c in owners] + [self.kv]
+                self._ranges = self.shards
+                self._shard_kv = self.stores = self._shard_stores()
         else:
-            self.shards = [r for r in cfg.shard_ranges() if r[0] < r[1]]
+            self.shards = self._ranges = [r for r in cfg.shard_ranges() if r[0] < r[1]]
             self.stores = [self.kv]
             every = [r for r in cfg.splits() if r[0] < r[1]]
             splits = [[r for r in every if b <= r[0] and r[1] <= e] for b, e in self.shards]
             assert sum(map(len, splits)) == len(every)
+        # where each shard's own coordinates begin in its store
+        base = [r[0] - o[0] for r, o in zip(self._ranges, self.shards)]
+        splits = [[(x + i, x + j) for i, j in sp] for x, sp in zip(base, splits)]
         # With a bf16 backward the splits stay as configured: other ones round P, and
         # with it the bf16 output inside Delta, in other places, which moves the dq of
         # a few rows with concentrated probabilities by up to 1.3e-2 (10 rows x 33,374
@@ -181,13 +185,14 @@ class ReplayStep:
             splits = fine_splits(cfg, splits)
         # The parts in launch order (key order of one store, else shard by shard);
         # shard s has the parts groups[s] and is launched from store_of(s).
-        order = splits if len(self.stores) > 1 else sorted(splits)
-        self.splits = [r for sp in order for r in sp]
-        start, at = 0, {}
-        for sp in order:
-            at[id(sp)] = start
-            start += len(sp)
-        self.groups = [(at[id(sp)], at[id(sp)] + len(sp)) for sp in splits]
+        order = sorted(range(len(splits)), key=lambda s: splits[s]) \
+            if len(self.stores) == 1 else range(len(splits))
+        self._launch, self.splits, self.groups = [], [], [None] * len(splits)
+        for s in order:
+            self.groups[s] = (len(self.splits), len(self.splits) + len(splits[s]))
+            self._launch += splits[s]
+            self.splits += [(i - base[s], j - base[s]) for i, j in splits[s]]
+        self.shard_splits = [self.splits[i:j] for i, j in self.groups]
         kw = dict(dtype=torch.float32, device=q.device)
         self.out_part = torch.empty((len(self.splits), R, Hq, Dv), **kw)
         self.lse_part = torch.empty((len(self.splits), Hq, R), **kw)
@@ -201,8 +206,29 @@ class ReplayStep:
             self.dv = torch.zeros((cfg.kv_len - cfg.prefix_len, cfg.n_kv_heads, Dv), **kw)
             self.ws = B.bwd_workspace(q, self.kv, prefix_len=cfg.prefix_len, q_pos0=cfg.q_pos0)
 
+    def _store(self, pages):
+        """A store whose first pages are these (logical pages of the step's table)."""
+        import torch
+        t = self._table.copy()
+        t[:len(pages)] = self._table[pages]
+        return B.PagedKV(self.dev["k_pool"], self.dev["v_pool"],
+                         torch.from_numpy(t).to(self.dev["page_table"].device))
+
+    def _shard_stores(self):
+        cfg = self.cfg
+        return [self._store(cfg.shard_pages(c)) for c in range(cfg.n_shards)
+                if cfg.shard_len(c)] + [self.kv]
+
+    @property
+    def shard_kv(self):
+        """Each shard's own store (made when first asked for where the step itself
+        reads all cyclic shards through one)."""
+        if self._shard_kv is None:
+            self._shard_kv = self._shard_stores() if self.cyclic else [self.kv] * len(self.shards)
+        return self._shard_kv
+
     def store_of(self, s: int):
-        """The store that shard s's ranges refer to."""
+        """The store that the step launches shard s from."""
         return self.stores[s if len(self.stores) > 1 else 0]
 
     def forward_splits(self):
@@ -210,11 +236,11 @@ class ReplayStep:
         c = self.cfg
         kw = dict(prefix_len=c.prefix_len, q_pos0=c.q_pos0, scale=c.scale, stream=self.stream)
         if len(self.stores) == 1:
-            B.prefix_attn_fwd(self.dev["q"], self.stores[0], self.splits, out_part=self.out_part,
+            B.prefix_attn_fwd(self.dev["q"], self.stores[0], self._launch, out_part=self.out_part,
                               lse_part=self.lse_part, **kw)
             return
         for s, (i, j) in enumerate(self.groups):
-            B.prefix_attn_fwd(self.dev["q"], self.stores[s], self.splits[i:j],
+            B.prefix_attn_fwd(self.dev["q"], self.stores[s], self._launch[i:j],
                               out_part=self.out_part[i:j], lse_part=self.lse_part[i:j], **kw)
 
     def merge(self):
@@ -242,7 +268,7 @@ class ReplayStep:
         first reuse the Delta and lse * log2(e) the first one left in the
         workspace, so ranges must run in order, starting at 0."""
         c = self.cfg
-        b, e = self.shards[r]
+        b, e = self._ranges[r]
         B.prefix_attn_bwd(self.dev["q"], self.store_of(r), self.dev["d_out"], self.out, self.lse,
                           prefix_len=c.prefix_len, q_pos0=c.q_pos0, scale=c.scale,
                           kv_begin=b, kv_end=e,
@@ -259,7 +285,7 @@ class ReplayStep:
                 self.backward_range(r)
             return self.dq, self.dk, self.dv
         B.prefix_attn_bwd_ranges(self.dev["q"], self.stores[0], self.dev["d_out"], self.out, self.lse,
-                                 self.shards, prefix_len=c.prefix_len, q_pos0=c.q_pos0,
+                                 self._ranges, prefix_len=c.prefix_len, q_pos0=c.q_pos0,
                                  scale=c.scale, dq=self.dq, dk_resp=self.dk, dv_resp=self.dv,
                                  workspace=self.ws, stream=self.stream)
         return self.dq, self.dk, self.dv

@@ -364,3 +364,31 @@ def test_cyclic_replay_pages(page, prefix, backward):
                           prefix_len=prefix, out=o, lse=l, **kw)
         for got, ref in zip((step.dq, step.dk, step.dv), refs):
             assert rel_l2(host(got), ref) <= TOL_BF16["grad"]
+
+
+@pytest.mark.parametrize("page", [16, 64])
+def test_cyclic_shards_by_hand(page):
+    """The shards of a cyclic step, called one by one through the stores and ranges that
+    it names, leave its parts and its gradients, to the bit."""
+    import torch
+
+    from paper_2607_14952_amd import inputs
+    from paper_2607_14952_amd.replay import ReplayStep, device_inputs
+    cfg = _bf16(f"cyclic_hand_p{page}", page * 37 + 1, 21, page=page, shards=5, ownership="cyclic")
+    dev = device_inputs(inputs.dense_inputs(cfg))
+    step = ReplayStep(cfg, dev)
+    print(f"[gpu] {cfg.name}", flush=True)
+    step.step()
+    kw = dict(prefix_len=cfg.prefix_len, q_pos0=cfg.q_pos0, scale=cfg.scale)
+    dq = dk = dv = None
+    for s, (b, e) in enumerate(step.shards):
+        i, j = step.groups[s]
+        o, l = B.prefix_attn_fwd(dev["q"], step.shard_kv[s], step.shard_splits[s], **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(o, step.out_part[i:j]) and torch.equal(l, step.lse_part[i:j])
+        dq, dk, dv = B.prefix_attn_bwd(dev["q"], step.shard_kv[s], dev["d_out"], step.out, step.lse,
+                                       kv_begin=b, kv_end=e, dq=dq, dk_resp=dk, dv_resp=dv,
+                                       flags=B.FLAG_ACCUMULATE_DQ if s else 0, **kw)
+    torch.cuda.synchronize()
+    for x, y in zip((dq, dk, dv), (step.dq, step.dk, step.dv)):
+        assert torch.equal(x, y)

@@ -57,6 +57,36 @@ def test_cyclic_table(prefix, page, shards):
         assert order[-1] == cfg.n_prefix_pages - 1
 
 
+@pytest.mark.parametrize("kw", [dict(prefix_len=256 * 61 + 100), dict(prefix_len=64 * 37 + 1, page_size=64),
+                                dict(prefix_len=16 * 61 + 5, page_size=16),
+                                dict(prefix_len=256 * 3)], ids=str)
+def test_cyclic_step_names_each_shards_own_store(kw):
+    """A cyclic step's shards, shard_splits and splits are ranges of the shards' own
+    stores, whose tables begin with the owned pages, whatever store the step itself
+    reads them through."""
+    import torch
+
+    from paper_2607_14952_amd.replay import ReplayStep
+    cfg = BASE.scaled(resp_len=21, splits_per_shard=2, ownership="cyclic", **kw)
+    n_pages = cfg.n_logical_pages
+    table = np.random.default_rng(1).permutation(n_pages).astype(np.int32)
+    pool = torch.zeros((n_pages, 1, 1, 1), dtype=torch.bfloat16)
+    step = ReplayStep(cfg, dict(q=torch.zeros((21, 16, 256), dtype=torch.bfloat16), k_pool=pool,
+                                v_pool=pool, page_table=torch.from_numpy(table)), backward=False)
+    assert step.cyclic
+    owners = [c for c in range(cfg.n_shards) if cfg.shard_len(c)]
+    assert step.shards == [(0, cfg.shard_len(c)) for c in owners] + [(cfg.prefix_len, cfg.kv_len)]
+    assert len(step.shard_kv) == len(step.shards) and step.shard_kv[-1] is step.kv
+    for s, c in enumerate(owners):
+        pages = cfg.shard_pages(c)
+        assert np.array_equal(step.shard_kv[s].page_table.numpy()[:len(pages)], table[pages])
+    for (b, e), parts, (i, j) in zip(step.shards, step.shard_splits, step.groups):
+        assert parts == step.splits[i:j]
+        assert parts[0][0] == b and parts[-1][1] == e
+        assert all(x[1] == y[0] for x, y in zip(parts, parts[1:]))
+    assert sorted(x for g in step.groups for x in range(*g)) == list(range(len(step.splits)))
+
+
 def test_merge_groups_rejects():
     import ctypes
 
