@@ -214,8 +214,11 @@ size_t ls_prefix_attn_bwd_workspace_size(const ls_attn_params* p);
  * workspace: device memory of ls_prefix_attn_bwd_workspace_size(p) bytes for
  *   the same p (it grows with the response length q_pos0 + n_q - prefix_len:
  *   it holds the partial dK/dV sums of row chunks and the partial dq sums of
- *   key chunks, and a workspace made for p serves any smaller n_q and q_pos0).  Every call
- *   first writes Delta_i = d_out_i . out_i and lse_i * log2(e) ([n_q_heads,
+ *   key chunks, and a workspace made for p serves any smaller n_q and q_pos0).
+ *   An fp32 call also accepts less, down to the two arrays named next (each
+ *   padded to 256 bytes), and then runs on the scalar kernels, which need no
+ *   partial sums: slower, and with another rounding order.  Every call first
+ *   writes Delta_i = d_out_i . out_i and lse_i * log2(e) ([n_q_heads,
  *   n_q] fp32 each) at the start of the workspace.  LS_FLAG_PREP_READY skips
  *   that step: the caller asserts that an earlier call on the same stream, with
  *   the same workspace, n_q, n_q_heads, d_out, out and lse, already wrote them

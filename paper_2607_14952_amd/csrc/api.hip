@@ -415,9 +415,11 @@ namespace {
 // path and the fp32 matrix-core path) the dk/dv partials of the row chunks and
 // the dq partials of the key chunks; each padded to 256 bytes.  Every part
 // grows with n_q and q_pos0, so a workspace serves any call with smaller ones.
+// An fp32 call with room for the first two alone takes the generic kernels.
 struct BwdWorkspace {
   size_t stat_bytes, part_bytes, dq_bytes;
   size_t total() const { return 2 * stat_bytes + part_bytes + dq_bytes; }
+  size_t least(int32_t dtype) const { return dtype == LS_F32 ? 2 * stat_bytes : total(); }
 };
 
 BwdWorkspace bwd_workspace_layout(const ls_attn_params* p) {
@@ -450,11 +452,11 @@ namespace {
 // whose plan says so share dq launches, as many at a time as the partial sums
 // have room for.  A range keeps the chunks it would have alone
 // and the sums keep their order, so the result is that of a call per range.
-hipError_t launch_backward(ls::BwdArgs& a, bool bf16, const std::vector<ls_split>& ranges,
-                           size_t part_bytes, hipStream_t s) {
+hipError_t launch_backward(ls::BwdArgs& a, bool bf16, bool generic,
+                           const std::vector<ls_split>& ranges, size_t part_bytes, hipStream_t s) {
   hipError_t e = hipSuccess;
   auto key0 = [&](const ls_split& r) { return std::max(r.kv_begin, a.prefix_len); };
-  if (!bf16 && !ls::f32_mfma_fits(a.head_dim, a.head_dim_v, a.n_kv_heads)) {
+  if (generic) {
     for (const ls_split& r : ranges) {
       a.kv_begin = r.kv_begin;
       a.kv_end = r.kv_end;
@@ -558,10 +560,13 @@ LS_API ls_status ls_prefix_attn_bwd_ranges(const ls_attn_params* p, const ls_spl
                           (const void*)dv_resp, (const void*)workspace})
     if (ptr && !aligned16(ptr))
       return fail(LS_ERR_INVALID_ARG, "device pointers must be 16-byte aligned");
-  size_t need = ls_prefix_attn_bwd_workspace_size(p);
-  if (!workspace || workspace_bytes < need)
-    return fail(LS_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,
+  const BwdWorkspace wl = bwd_workspace_layout(p);
+  if (!workspace || workspace_bytes < wl.least(p->dtype))
+    return fail(LS_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", wl.least(p->dtype),
                 workspace ? workspace_bytes : (size_t)0);
+  const bool generic = p->dtype == LS_F32 &&
+                       (workspace_bytes < wl.total() ||
+                        !ls::f32_mfma_fits(p->head_dim, p->head_dim_v, p->n_kv_heads));
   const size_t es = esize(p->dtype);
   const size_t rows = (size_t)p->n_q * p->n_q_heads;
   const size_t n_resp = (size_t)(kv_len - p->prefix_len);
@@ -575,12 +580,11 @@ LS_API ls_status ls_prefix_attn_bwd_ranges(const ls_attn_params* p, const ls_spl
     outs.push_back(rng("dk_resp", dk_resp, n_resp * p->n_kv_heads * p->head_dim * 4));
     outs.push_back(rng("dv_resp", dv_resp, n_resp * p->n_kv_heads * p->head_dim_v * 4));
   }
-  outs.push_back(rng("workspace", workspace, need));
+  outs.push_back(rng("workspace", workspace, generic ? wl.least(p->dtype) : wl.total()));
   if ((st = check_alias(outs, ins)) != LS_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   if ((st = check_pages(p, kv_end, s)) != LS_OK) return st;
 
-  const BwdWorkspace wl = bwd_workspace_layout(p);
   float* delta = (float*)workspace;
   float* lse2 = (float*)((char*)workspace + wl.stat_bytes);
   hipError_t e = hipSuccess;
@@ -601,8 +605,11 @@ LS_API ls_status ls_prefix_attn_bwd_ranges(const ls_attn_params* p, const ls_spl
   a.dq = dq;
   a.dk_resp = dk_resp;
   a.dv_resp = dv_resp;
-  a.dkdv_part = wl.part_bytes ? (float*)((char*)workspace + 2 * wl.stat_bytes) : nullptr;
-  a.dq_part = wl.dq_bytes ? (float*)((char*)workspace + 2 * wl.stat_bytes + wl.part_bytes) : nullptr;
+  a.dkdv_part = a.dq_part = nullptr;
+  if (!generic) {
+    a.dkdv_part = (float*)((char*)workspace + 2 * wl.stat_bytes);
+    a.dq_part = (float*)((char*)workspace + 2 * wl.stat_bytes + wl.part_bytes);
+  }
   a.q_pos0 = p->q_pos0;
   a.prefix_len = p->prefix_len;
   a.k_pos_stride = (int64_t)p->n_kv_heads * p->head_dim;
@@ -620,7 +627,7 @@ LS_API ls_status ls_prefix_attn_bwd_ranges(const ls_attn_params* p, const ls_spl
   a.accumulate_dq = (p->flags & LS_FLAG_ACCUMULATE_DQ) ? 1 : 0;
   a.accumulate_dkv = (p->flags & LS_FLAG_ACCUMULATE_DKV) ? 1 : 0;
   a.dkdv_rows = 0;
-  e = launch_backward(a, p->dtype == LS_BF16, todo, wl.dq_bytes, s);
+  e = launch_backward(a, p->dtype == LS_BF16, generic, todo, wl.dq_bytes, s);
   return e == hipSuccess ? LS_OK : hip_fail(e, "backward launch");
 }
 

@@ -392,3 +392,34 @@ def test_cyclic_shards_by_hand(page):
     torch.cuda.synchronize()
     for x, y in zip((dq, dk, dv), (step.dq, step.dk, step.dv)):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("d", [64, 160], ids=["matrix_cores", "generic"])
+def test_f32_backward_in_less_workspace(d):
+    """An fp32 backward also runs in the workspace of a block with fewer response keys,
+    and in one that holds no more than Delta and the log-normalizers."""
+    import torch
+
+    from paper_2607_14952_amd import inputs
+    from paper_2607_14952_amd.replay import device_inputs
+    from tests._gpu import TOL_F32, host, rel_l2
+    cfg = _f32(f"workspace_d{d}", 6, 2, d, d, 300, 40)
+    dev = device_inputs(inputs.dense_inputs(cfg))
+    kv = B.PagedKV(dev["k_pool"], dev["v_pool"], dev["page_table"])
+    P, q0, n = cfg.prefix_len, cfg.prefix_len + 21, 19
+    q, d_out = dev["q"][21:], dev["d_out"][21:]
+    kw = dict(prefix_len=P, q_pos0=q0, scale=cfg.scale)
+    op, lp = B.prefix_attn_fwd(q, kv, [(0, q0 + n)], **kw)
+    out, lse = B.lse_merge(op, lp)
+    want = B.prefix_attn_bwd(q, kv, d_out, out, lse, **kw)
+    stat = -(-n * cfg.n_q_heads * 4 // 256) * 256
+    for ws in (B.bwd_workspace(q, kv, prefix_len=P, q_pos0=P),
+               torch.empty(2 * stat, dtype=torch.uint8, device="cuda")):
+        print(f"[gpu] f32 backward d={d} in {ws.numel()} bytes", flush=True)
+        got = B.prefix_attn_bwd(q, kv, d_out, out, lse, workspace=ws, **kw)
+        torch.cuda.synchronize()
+        for x, y in zip(got, want):
+            assert rel_l2(host(x), host(y)) <= TOL_F32["grad"]
+    with pytest.raises(B.LongStrawError) as ei:
+        B.prefix_attn_bwd(q, kv, d_out, out, lse, workspace=ws[:2 * stat - 256], **kw)
+    assert ei.value.name == "LS_ERR_WORKSPACE"
