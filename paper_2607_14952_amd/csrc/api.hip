@@ -431,8 +431,8 @@ BwdWorkspace bwd_workspace_layout(const ls_attn_params* p) {
   if (n_resp <= 0 || p->n_q_heads % p->n_kv_heads != 0) return w;
   const int group = p->n_q_heads / p->n_kv_heads;
   if (p->dtype == LS_BF16) {
-    w.part_bytes = (size_t)ls::dkdv_row_chunks(p->n_q, group) * 2 * p->n_kv_heads *
-                   (size_t)n_resp * p->head_dim * 4;
+    w.part_bytes = (size_t)ls::dkdv_part_keys(p->n_q, group, p->n_kv_heads, n_resp) * 2 *
+                   p->n_kv_heads * p->head_dim * 4;
     w.dq_bytes = ls::dq_part_bytes(p->n_q, group, p->head_dim);
   } else if (ls::f32_mfma_fits(p->head_dim, p->head_dim_v, p->n_kv_heads)) {
     w.part_bytes = pad((size_t)ls::f32_dkdv_chunks(p->n_q, group) * p->n_kv_heads *

@@ -445,7 +445,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dq_bf16_d256_kernel(BwdArgs a, DqR
 //   dv^T += dO^T P, dk^T += Q^T dS (transposed reads of the row tiles).
 // The chunk's partial sums go to the workspace; dkdv_reduce_kernel adds the
 // active chunks in order (deterministic), scales dk and writes or accumulates.
-constexpr int kKeysPerWG = 128;
+constexpr int kKeysPerWG = kDkdvKeys;
 constexpr int kRStat = 256;                                // per wave: 32 lse2 + 32 Delta floats
 constexpr int kRStage = 2 * kTileBytes + 4 * kRStat;       // Q tile, dO tile, stats
 constexpr int kRAhead = 2;
@@ -602,10 +602,10 @@ __global__ __launch_bounds__(256, 1) void bwd_dkdv_bf16_d256_kernel(BwdArgs a, i
   }
   wait_fetch();
 
-  // partial sums of this chunk: part[chunk][0 = dk, 1 = dv][g][key - prefix_len][256]
+  // partial sums of this chunk: part[chunk][0 = dk, 1 = dv][g][key - key0][256]
   if (j_mine < key_end) {
-    const int64_t n_part = a.kv_end - a.prefix_len;
-    const int64_t kidx = j_mine - a.prefix_len;
+    const int64_t n_part = key_end - key0;
+    const int64_t kidx = j_mine - key0;
     float* pk = a.dkdv_part + (((int64_t)chunk * 2 * a.n_kv_heads + g) * n_part + kidx) * kD;
     float* pv = pk + (int64_t)a.n_kv_heads * n_part * kD;
 #pragma unroll
@@ -638,17 +638,15 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(BwdArgs a, int64_t key
   const int g = (int)((item / (kD / 4)) % a.n_kv_heads);
   const int64_t j = key0 + item / ((kD / 4) * a.n_kv_heads);
   const int64_t j0 = key0 + (j - key0) / kKeysPerWG * kKeysPerWG;
-  const int64_t n_part = a.kv_end - a.prefix_len;
-  const int64_t kidx = j - a.prefix_len;
   f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = sk;
   for (int c = 0; c < n_chunks; ++c) {
     if (dkdv_row_lo(a, j0, c) >= dkdv_row_hi(a, c)) continue;
-    const float* pk = a.dkdv_part + (((int64_t)c * 2 * a.n_kv_heads + g) * n_part + kidx) * kD + d0;
+    const float* pk = a.dkdv_part + (((int64_t)c * 2 * a.n_kv_heads + g) * n_keys + j - key0) * kD + d0;
     sk += *reinterpret_cast<const f32x4*>(pk);
-    sv += *reinterpret_cast<const f32x4*>(pk + (int64_t)a.n_kv_heads * n_part * kD);
+    sv += *reinterpret_cast<const f32x4*>(pk + (int64_t)a.n_kv_heads * n_keys * kD);
   }
   sk *= a.scale;
-  const int64_t r = (kidx * a.n_kv_heads + g) * kD + d0;
+  const int64_t r = ((j - a.prefix_len) * a.n_kv_heads + g) * kD + d0;
   f32x4* dkr = reinterpret_cast<f32x4*>(a.dk_resp + r);
   f32x4* dvr = reinterpret_cast<f32x4*>(a.dv_resp + r);
   if (a.accumulate_dkv) {
@@ -788,11 +786,7 @@ hipError_t launch_dkdv_bf16_d256(const BwdArgs& args, int64_t key0, hipStream_t 
   BwdArgs a = args;
   const int64_t n_keys = a.kv_end - key0, packed = (int64_t)a.n_q * a.group;
   const unsigned blocks = (unsigned)((n_keys + kKeysPerWG - 1) / kKeysPerWG);
-  // Row chunks (dkdv_row_chunks: the most, which the workspace has room for): two
-  // workgroups per CU, or chunks of 2,048 rows where there are more of these.
-  const int64_t fill = (512 + (int64_t)blocks * a.n_kv_heads - 1) / ((int64_t)blocks * a.n_kv_heads);
-  const int64_t want = std::min<int64_t>(dkdv_row_chunks(a.n_q, a.group),
-                                         std::max((packed + 2047) / 2048, fill));
+  const int64_t want = dkdv_launch_chunks(a.n_q, a.group, a.n_kv_heads, n_keys);
   a.dkdv_rows = (int32_t)(((packed + want - 1) / want + 31) / 32 * 32);
   const int n_chunks = (int)((packed + a.dkdv_rows - 1) / a.dkdv_rows);
   hipLaunchKernelGGL(bwd_dkdv_bf16_d256_kernel, dim3(blocks, a.n_kv_heads, n_chunks), dim3(256), 0,

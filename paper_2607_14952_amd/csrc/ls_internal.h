@@ -30,6 +30,25 @@ inline int dkdv_row_chunks(int n_q, int group) {
   const int64_t few = (rows + 127) / 128, many = (rows + 2047) / 2048;
   return (int)(few < 16 ? few : many > 16 ? many : 16);
 }
+// Response keys of a workgroup of that kernel.
+constexpr int kDkdvKeys = 128;
+// Row chunks of a launch over n_keys keys: two workgroups per CU, or chunks of
+// 2,048 rows where there are more of these.
+inline int64_t dkdv_launch_chunks(int n_q, int group, int n_kv_heads, int64_t n_keys) {
+  const int64_t blocks = (n_keys + kDkdvKeys - 1) / kDkdvKeys * n_kv_heads;
+  const int64_t fill = (512 + blocks - 1) / blocks, many = ((int64_t)n_q * group + 2047) / 2048;
+  const int64_t most = dkdv_row_chunks(n_q, group), want = fill > many ? fill : many;
+  return most < want ? most : want;
+}
+// Most keys times chunks of any launch over up to n_resp keys: a launch of fill
+// chunks has at most 512 workgroups of kDkdvKeys keys and one chunk of its keys more.
+// Grows with n_q and n_resp.
+inline int64_t dkdv_part_keys(int n_q, int group, int n_kv_heads, int64_t n_resp) {
+  const int64_t many = ((int64_t)n_q * group + 2047) / 2048 * n_resp;
+  const int64_t fill = 512 * kDkdvKeys / n_kv_heads + n_resp;
+  const int64_t most = dkdv_row_chunks(n_q, group) * n_resp, want = fill > many ? fill : many;
+  return most < want ? most : want;
+}
 
 // Row chunks of the fp32 matrix-core dk/dv kernel: 128 packed rows (one 32-row
 // tile per wave of its workgroups), at most 16 chunks.
@@ -120,8 +139,8 @@ struct BwdArgs {
   float* dq;                // [n_q, Hq, D]
   float* dk_resp;           // [kv_len - prefix_len, Hkv, D]
   float* dv_resp;           // [kv_len - prefix_len, Hkv, Dv]
-  float* dkdv_part;         // partial dk/dv sums of row chunks (bf16: [row chunks, 2, Hkv,
-                            // kv_end - prefix_len, D]; fp32: [row chunks, keys, Hkv, D + Dv])
+  float* dkdv_part;         // partial dk/dv sums of row chunks over the launch's keys (bf16:
+                            // [row chunks, 2, Hkv, keys, D]; fp32: [row chunks, keys, Hkv, D + Dv])
   float* dq_part;           // partial dq sums of key chunks [chunks, n_q, Hq, D], unscaled
                             // (dq_part_bytes in all)
   int64_t q_pos0;

@@ -1,6 +1,7 @@
 // What the host headers of csrc/ need of the HIP runtime, for compiling device
-// code with a host compiler (tests/topk_host.cpp).
+// code with a host compiler (tests/topk_host.cpp, tests/plan_host.cpp).
 #pragma once
+#include <stddef.h>
 #include <stdint.h>
 #define __device__
 #define __host__
