@@ -466,11 +466,22 @@ def dsa_index_scores(q_index, w_index, k_index_pool, page_table, *, pos_begin: i
     return scores[:, :n]
 
 
+def topk_workspace(rows: int, n: int, k: int, device):
+    """Workspace through which topk_select shares few long rows of n columns among
+    workgroups (empty where these rows gain nothing by it)."""
+    torch = _torch()
+    need = load_library().ls_topk_workspace_size(rows, n, k)
+    return torch.empty(need, dtype=torch.uint8, device=device)
+
+
 def topk_select(scores, k: int, *, n: int | None = None, positions=None, pos_offset: int = 0,
-                out_pos=None, out_scores=None, stream=None):
-    """ls_topk_select over the rows of ``scores`` [rows, >= n] (row stride ld):
+                out_pos=None, out_scores=None, workspace=None, stream=None):
+    """ls_topk_select_ws over the rows of ``scores`` [rows, >= n] (row stride ld):
     positions [rows, k] int32 ascending and their scores [rows, k] (outputs may
-    be column slices of wider arrays: their row stride is passed on)."""
+    be column slices of wider arrays: their row stride is passed on).  What is not
+    given is allocated: the outputs, and the workspace (topk_workspace) of few long
+    rows.  A given workspace that is too small leaves each row to one workgroup;
+    the selection is the same."""
     torch = _torch()
     rows = scores.shape[0]
     n = scores.shape[1] if n is None else n
@@ -485,19 +496,17 @@ def topk_select(scores, k: int, *, n: int | None = None, positions=None, pos_off
                          "have unit column stride")
     if positions is not None and positions.stride(0) != scores.stride(0):
         raise ValueError("topk_select: positions must have the row stride of scores")
-    # few long rows are shared among workgroups, through candidates kept here (memory
-    # of the stream the call runs on, so that it is not handed out again before)
-    need = load_library().ls_topk_workspace_size(rows, n, k)
-    ws = None
-    if need:
+    if workspace is None:
+        # (memory of the stream the call runs on, so that it is not handed out again before)
         with torch.cuda.stream(stream):
-            ws = torch.empty(need, dtype=torch.uint8, device=scores.device)
+            workspace = topk_workspace(rows, n, k, scores.device)
     check(load_library().ls_topk_select_ws(
         _ptr(scores, torch.float32, "scores", dense=False), scores.stride(0),
         _ptr(positions, torch.int32, "positions", dense=False), rows, n, pos_offset, k,
         _ptr(out_pos, torch.int32, "out_pos", dense=False),
         _ptr(out_scores, torch.float32, "out_scores", dense=False), out_pos.stride(0),
-        _ptr(ws, None, "workspace"), need, _stream(stream)))
+        _ptr(workspace, None, "workspace"), workspace.numel() * workspace.element_size(),
+        _stream(stream)))
     return out_pos, out_scores
 
 

@@ -32,6 +32,12 @@ class DsaSelect:
             self.cand_pos = torch.empty((R, k * len(self.shards)), dtype=torch.int32,
                                         device=self.scores.device)
             self.cand_sc = torch.empty_like(self.cand_pos, dtype=torch.float32)
+            lengths = [e - b for b, e in self.shards] + [self.cand_sc.shape[1]]
+        else:
+            lengths = [P]
+        # (one for every selection: they run one after another)
+        self.topk_ws = max((B.topk_workspace(R, n, k, self.scores.device) for n in set(lengths)),
+                           key=torch.numel)
 
     def score(self):
         d = self.dev
@@ -43,7 +49,7 @@ class DsaSelect:
         P, k = self.cfg.prefix_len, self.cfg.topk
         if self.mode == "global":
             B.topk_select(self.scores, k, n=P, out_pos=self.idx, out_scores=self.sel_scores,
-                          stream=self.stream)
+                          workspace=self.topk_ws, stream=self.stream)
             return self.idx
         # per-shard candidates (positions ascending across shards), then the merge
         for s, (b, e) in enumerate(self.shards):
@@ -52,9 +58,10 @@ class DsaSelect:
                                  f"k = {k} positions")
             B.topk_select(self.scores[:, b:], k, n=e - b, pos_offset=b,
                           out_pos=self.cand_pos[:, s * k:(s + 1) * k],
-                          out_scores=self.cand_sc[:, s * k:(s + 1) * k], stream=self.stream)
+                          out_scores=self.cand_sc[:, s * k:(s + 1) * k], workspace=self.topk_ws,
+                          stream=self.stream)
         B.topk_select(self.cand_sc, k, positions=self.cand_pos, out_pos=self.idx,
-                      out_scores=self.sel_scores, stream=self.stream)
+                      out_scores=self.sel_scores, workspace=self.topk_ws, stream=self.stream)
         return self.idx
 
     def run(self):

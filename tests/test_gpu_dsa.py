@@ -16,7 +16,7 @@ import pytest
 
 import oracle as O
 from paper_2607_14952_amd import binding as B
-from paper_2607_14952_amd import inputs
+from paper_2607_14952_amd import configs, inputs
 from paper_2607_14952_amd.replay import to_device
 from tests._gpu import announce, host
 
@@ -291,3 +291,26 @@ def test_dsa_c5_full_size_sampled():
         mask = np.zeros(P, bool)
         mask[want[j]] = True
         assert ref[j][mask].min() >= ref[j][~mask].max() - 2 * tol[j], f"row {rows[j]}"
+
+
+@pytest.mark.parametrize("mode", ["global", "candidates"])
+def test_selection_allocates_nothing(mode):
+    """A selection's buffers, the one through which few long rows are shared among
+    workgroups too, are DsaSelect's own."""
+    import torch
+
+    from paper_2607_14952_amd.dsa import DsaSelect
+    cfg = configs.C5.scaled(name="dsa_noalloc", prefix_len=500_006, resp_len=3, topk=256)
+    dev = {k: to_device(v) for k, v in inputs.dsa_index_inputs(3, 3, 32, 500_006, 64).items()}
+    sel = DsaSelect(cfg, dev, mode=mode, n_shards=2)
+    assert sel.topk_ws.numel() > 0
+    sel.run()
+    torch.cuda.synchronize()
+    before = torch.cuda.memory_stats()["allocation.all.allocated"]
+    announce(f"selection {mode} without allocations")
+    idx = sel.run().clone()
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == before + 1   # (the clone)
+    want, _ = B.topk_select(sel.scores, cfg.topk, n=cfg.prefix_len,
+                            workspace=torch.empty(0, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert torch.equal(idx, want)
