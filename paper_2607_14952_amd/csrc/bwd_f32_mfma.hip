@@ -121,11 +121,14 @@ __global__ __launch_bounds__(256, kRW == 4 ? 2 : 1) void bwd_dq_f32_mfma_kernel(
 #pragma unroll
     for (int k = 1; k < kKW; ++k) acc_add_lds<kDB>(acc, smem + (k - 1) * kAcc, 1.f, lane);
   }
-  if (row_ok) {
-    // a chunk's partial sum (unscaled), or the result when there is one chunk
-    float* dst = part ? part + ((int64_t)z * a.n_q * a.n_q_heads + rh) * D : a.dq + rh * D;
-    const float c = part ? 1.f : a.scale;
-    const bool add = !part && a.accumulate_dq;
+  // a chunk's partial sum (unscaled), or the result when there is one chunk
+  float* const out = part ? part + (int64_t)z * a.n_q * a.n_q_heads * D : a.dq;
+  const float c = part ? 1.f : a.scale;
+  const bool add = !part && a.accumulate_dq;
+  // rows to form again key by key (f32_rows.h); the rows past the end are none
+  uint32_t again = not_finite<kDB>(acc) & (uint32_t)__ballot(row_ok);
+  if (row_ok && !(add && (again >> j & 1))) {
+    float* dst = out + rh * D;
 #pragma unroll
     for (int b = 0; b < kDB; ++b) {
 #pragma unroll
@@ -136,6 +139,26 @@ __global__ __launch_bounds__(256, kRW == 4 ? 2 : 1) void bwd_dq_f32_mfma_kernel(
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = fmaf(c, acc[b][4 * q4 + e], v[e]);
         if (d < D) *reinterpret_cast<f32x4*>(dst + d) = v;
+      }
+    }
+  }
+  if (__builtin_expect(again != 0, 0)) {
+    __threadfence();   // (the values stored so far come first)
+    for (; again; again &= again - 1) {
+      const int64_t r = of_lane(rh, __builtin_ctz(again));
+      const int t = (int)(r / a.n_q_heads), hd = (int)(r - (int64_t)t * a.n_q_heads);
+      const int zz = opaque(blockIdx.z), i = ranges.of(zz), ln = lane_id();
+      const int64_t begin = ranges.begin[i];
+      const int64_t from = (begin & ~int64_t(31)) + (int64_t)(zz - ranges.z0[i]) * ranges.per[i] * 32;
+      float x[2];
+      f32r::dq_row<2>(a, max(begin, from),
+                      min(min(ranges.end[i], a.q_pos0 + t + 1), from + ranges.per[i] * 32), t, hd,
+                      ln, x);
+      float* dst = out + r * D;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int d = ln + 64 * k;
+        if (d < D) dst[d] = fmaf(c, x[k], add ? dst[d] : 0.f);
       }
     }
   }
@@ -242,28 +265,50 @@ __global__ __launch_bounds__(256) void bwd_dkdv_f32_mfma_kernel(BwdArgs a, int64
     acc_to_lds<kDB>(smem + (2 * (w - 1) + 1) * kAcc, dv, lane);
   }
   __syncthreads();
-  if (w > 0 || !key_ok) return;
+  if (w > 0) return;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     acc_add_lds<kDB>(dk, smem + 2 * k * kAcc, 1.f, lane);
     acc_add_lds<kDB>(dv, smem + (2 * k + 1) * kAcc, 1.f, lane);
   }
   // part[chunk][key - key0][g][D + Dv]
-  float* dst = part + (((int64_t)chunk * (a.kv_end - key0) + (key - key0)) * a.n_kv_heads + g) *
-                          (D + Dv);
+  auto part_of = [&](int64_t k) {
+    return part + (((int64_t)chunk * (a.kv_end - key0) + (k - key0)) * a.n_kv_heads + g) * (D + Dv);
+  };
+  if (key_ok) {
+    float* dst = part_of(key);
 #pragma unroll
-  for (int b = 0; b < kDB; ++b) {
+    for (int b = 0; b < kDB; ++b) {
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const int d = 32 * b + 8 * q4 + 4 * h;
-      f32x4 x, y;
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int d = 32 * b + 8 * q4 + 4 * h;
+        f32x4 x, y;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        x[e] = dk[b][4 * q4 + e];
-        y[e] = dv[b][4 * q4 + e];
+        for (int e = 0; e < 4; ++e) {
+          x[e] = dk[b][4 * q4 + e];
+          y[e] = dv[b][4 * q4 + e];
+        }
+        if (d < D) *reinterpret_cast<f32x4*>(dst + d) = x;
+        if (d < Dv) *reinterpret_cast<f32x4*>(dst + D + d) = y;
       }
-      if (d < D) *reinterpret_cast<f32x4*>(dst + d) = x;
-      if (d < Dv) *reinterpret_cast<f32x4*>(dst + D + d) = y;
+    }
+  }
+  // keys to form again row by row (f32_rows.h); the keys past the end are none
+  uint32_t again = (not_finite<kDB>(dk) | not_finite<kDB>(dv)) & (uint32_t)__ballot(key_ok);
+  if (__builtin_expect(again != 0, 0)) {
+    __threadfence();   // (the values stored so far come first)
+    for (; again; again &= again - 1) {
+      const int64_t k = of_lane(key, __builtin_ctz(again));
+      const int ln = lane_id();
+      float x[2], y[2];
+      f32r::dkdv_key<2>(a, k, g, row_lo, row_hi, ln, x, y);
+      float* dst = part_of(k);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int d = ln + 64 * i;
+        if (d < D) dst[d] = x[i];
+        if (d < Dv) dst[D + d] = y[i];
+      }
     }
   }
 }

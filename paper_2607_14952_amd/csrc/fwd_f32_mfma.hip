@@ -147,6 +147,16 @@ __global__ __launch_bounds__(256, kRW == 4 ? 2 : 1) void fwd_f32_mfma_kernel(Fwd
       a.lse_part[((int64_t)sp * a.n_q_heads + head) * a.n_q + tok] =
           l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
   }
+  // rows to form again key by key (f32_rows.h); the rows past the end are none
+  uint32_t again = not_finite<kDB>(oacc) & (uint32_t)__ballot(row_ok);
+  if (__builtin_expect(again != 0, 0)) {
+    __threadfence();   // (the values stored so far come first)
+    for (; again; again &= again - 1) {
+      const int i = __builtin_ctz(again);
+      f32r::fwd_row<2>(a, opaque(blockIdx.z), __builtin_amdgcn_readlane(tok, i),
+                       __builtin_amdgcn_readlane(head, i), lane_id());
+    }
+  }
 }
 
 template <int kDP>

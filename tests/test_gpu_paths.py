@@ -423,3 +423,56 @@ def test_f32_backward_in_less_workspace(d):
     with pytest.raises(B.LongStrawError) as ei:
         B.prefix_attn_bwd(q, kv, d_out, out, lse, workspace=ws[:2 * stat - 256], **kw)
     assert ei.value.name == "LS_ERR_WORKSPACE"
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")], ids=["nan", "inf"])
+@pytest.mark.parametrize("hq,d,dv,resp", [(4, 64, 64, 40), (6, 128, 96, 150), (6, 40, 72, 40)],
+                         ids=["d64", "four_groups", "d40"])
+def test_f32_rows_before_a_bad_position(hq, d, dv, resp, bad):
+    """A response position whose key and value are not finite reaches the rows that see
+    it, not those before it in the same tiles; a row whose query and d_out are not
+    reaches the keys that it sees, not those after it."""
+    import numpy as np
+    import torch
+
+    from paper_2607_14952_amd import inputs
+    from paper_2607_14952_amd.replay import device_inputs
+    from tests._gpu import TOL_F32, host, rel_l2
+    cfg = _f32(f"bad_d{d}", hq, 2, d, dv, 4_103 if resp > 100 else 70, resp)
+    dev = device_inputs(inputs.dense_inputs(cfg))
+    P, R = cfg.prefix_len, cfg.resp_len
+    kw = dict(prefix_len=P, q_pos0=P, scale=cfg.scale)
+
+    def run(t):
+        kv = B.PagedKV(t["k_pool"], t["v_pool"], t["page_table"])
+        op, lp = B.prefix_attn_fwd(t["q"], kv, [(0, P // 2), (P // 2, P + R)], **kw)
+        out, lse = B.lse_merge(op, lp)
+        dq = torch.full((R, hq, d), 0.5, device="cuda")
+        _, dk, dv = B.prefix_attn_bwd(t["q"], kv, t["d_out"], out, lse, dq=dq,
+                                      flags=B.FLAG_ACCUMULATE_DQ, **kw)
+        torch.cuda.synchronize()
+        return [host(x) for x in (out, lse.t(), dq, dk, dv)]
+
+    good = run(dev)
+    at = R - 15
+    page, slot = int(dev["page_table"][(P + at) // cfg.page_size]), (P + at) % cfg.page_size
+    t = {k: v.clone() for k, v in dev.items()}
+    t["k_pool"][page, slot] = bad
+    t["v_pool"][page, slot] = bad
+    print(f"[gpu] {cfg.name}: key and value {bad}", flush=True)
+    got = run(t)
+    for x, y in zip(got[:3], good):
+        assert np.isfinite(x[:at]).all() and rel_l2(x[:at], y[:at]) <= TOL_F32["grad"]
+    for x in (got[0], got[2]):
+        assert not np.isfinite(x[at:]).all(axis=(1, 2)).any()
+    t = {k: v.clone() for k, v in dev.items()}
+    t["q"][at] = bad
+    t["d_out"][at] = bad
+    print(f"[gpu] {cfg.name}: query and d_out {bad}", flush=True)
+    got = run(t)
+    for x, y in zip(got[:3], good):
+        rest = np.arange(R) != at
+        assert np.isfinite(x[rest]).all() and rel_l2(x[rest], y[rest]) <= TOL_F32["grad"]
+    for x, y in zip(got[3:], good[3:]):
+        assert np.isfinite(x[at + 1:]).all() and rel_l2(x[at + 1:], y[at + 1:]) <= TOL_F32["grad"]
+        assert not np.isfinite(x[:at + 1]).all(axis=(1, 2)).any()
