@@ -302,23 +302,7 @@ LS_API ls_status ls_prefix_attn_fwd(const ls_attn_params* p, const ls_split* spl
   ls::FwdArgs a;
   fill_common(p, a);
   for (int i0 = 0; i0 < n_splits; i0 += a.n_splits) {
-    // as many splits as the arguments hold and 32-bit offsets reach; a longer
-    // split goes alone
-    a.split_base = splits[i0].kv_begin;
-    int n = 0;
-    while (n < ls::kMaxSplitsPerLaunch && i0 + n < n_splits &&
-           splits[i0 + n].kv_end - a.split_base <= (int64_t)UINT32_MAX) {
-      a.split_lo[n] = (uint32_t)(splits[i0 + n].kv_begin - a.split_base);
-      a.split_hi[n] = (uint32_t)(splits[i0 + n].kv_end - a.split_base);
-      ++n;
-    }
-    a.split_more = 0;
-    if (n == 0) {
-      n = 1;
-      a.split_lo[0] = a.split_hi[0] = 0;
-      a.split_more = splits[i0].kv_end - a.split_base;
-    }
-    a.n_splits = n;
+    ls::pack_splits(a, splits + i0, n_splits - i0);
     a.out_part = out_part + part_out * i0;
     a.lse_part = lse_part + part_lse * i0;
     hipError_t e = p->dtype == LS_BF16 ? ls::launch_fwd_bf16_d256(a, s) : ls::launch_fwd_f32(a, s);

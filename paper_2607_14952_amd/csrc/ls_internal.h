@@ -126,6 +126,28 @@ struct FwdArgs {
 };
 static_assert(sizeof(FwdArgs) <= 4096, "kernel arguments");
 
+// Puts the first of n sorted splits (with kv_begin and kv_end) into a's arguments: as
+// many as these hold and 32-bit offsets reach, or one longer split alone.  Returns
+// how many.
+template <typename Split>
+inline int pack_splits(FwdArgs& a, const Split* splits, int n) {
+  a.split_base = splits[0].kv_begin;
+  a.split_more = 0;
+  a.n_splits = 0;
+  while (a.n_splits < kMaxSplitsPerLaunch && a.n_splits < n &&
+         splits[a.n_splits].kv_end - a.split_base <= (int64_t)UINT32_MAX) {
+    a.split_lo[a.n_splits] = (uint32_t)(splits[a.n_splits].kv_begin - a.split_base);
+    a.split_hi[a.n_splits] = (uint32_t)(splits[a.n_splits].kv_end - a.split_base);
+    ++a.n_splits;
+  }
+  if (a.n_splits == 0) {
+    a.split_lo[0] = a.split_hi[0] = 0;
+    a.split_more = splits[0].kv_end - a.split_base;
+    a.n_splits = 1;
+  }
+  return a.n_splits;
+}
+
 // Backward.  The dq launches take their key ranges from DqRanges, the dk/dv ones
 // from kv_begin / kv_end.
 struct BwdArgs {
@@ -222,8 +244,8 @@ hipError_t launch_merge(const float* out_part, const float* lse_part, const int3
                         bool out_bf16, bool bf16_numerator, float* group_out, float* group_lse,
                         void* out, float* lse, hipStream_t stream);
 hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t stream);
-// fp32 on the matrix cores, for the shapes f32_mfma_fits accepts (launch_fwd_f32
-// and launch_bwd_f32 take them for those and the generic kernels for the others)
+// fp32 on the matrix cores, for the shapes f32_mfma_fits accepts (launch_fwd_f32 and
+// the backward entry point take them for those, the generic kernels for the others)
 hipError_t launch_fwd_f32_mfma(const FwdArgs& a, hipStream_t stream);
 DqPlan plan_dq_f32_mfma(const BwdArgs& a, int64_t begin, int64_t end);
 hipError_t launch_dq_f32_mfma(const BwdArgs& a, const DqRanges& r, int form, float* part,

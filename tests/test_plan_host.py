@@ -49,3 +49,26 @@ def test_block_of_2048_reserves_the_chunks_it_takes(lib):
     chunks, where sixteen would be the most for fewer keys."""
     assert lib.dkdv_launch_chunks(2_048, 8, 2, I64(8_192)) == 8
     assert lib.dkdv_part_keys(2_048, 8, 2, I64(8_192)) == 8 * 8_192
+
+
+BIG = 1 << 32
+
+
+@pytest.mark.parametrize("splits", [
+    [(0, 1)], [(7 * i, 7 * i + 5) for i in range(1_000)],
+    # one that no 32-bit offset reaches, first, last and between others
+    [(5, BIG + 5)], [(3, 9), (9, 2 * BIG), (2 * BIG, 2 * BIG + 1)],
+    # ends at and one past the offsets' reach from the launch's first key
+    [(11, 20), (20, 11 + BIG - 1)], [(11, 20), (20, 11 + BIG)],
+    [(i << 30, (i + 1) << 30) for i in range(1, 40)],
+], ids=["one", "many", "long", "long_between", "reach", "past", "gibi"])
+def test_split_bounds_survive_packing(lib, splits):
+    arr = (I64 * (2 * len(splits)))(*[x for s in splits for x in s])
+    begin, end = (I64 * 448)(), (I64 * 448)()
+    got, i = [], 0
+    while i < len(splits):
+        m = lib.pack_splits(arr, len(splits), i, begin, end)
+        assert 1 <= m <= 448 and i + m <= len(splits)
+        got += list(zip(begin[:m], end[:m]))
+        i += m
+    assert got == splits
