@@ -24,9 +24,9 @@ STATUS = {0: "LS_OK", -1: "LS_ERR_INVALID_ARG", -2: "LS_ERR_UNSUPPORTED", -3: "L
           -4: "LS_ERR_ALIAS", -5: "LS_ERR_STALE", -6: "LS_ERR_PAGE_OOB", -7: "LS_ERR_HIP"}
 EXPORTS = ["ls_abi_version", "ls_status_string", "ls_last_error", "ls_gather_kv", "ls_scatter_kv",
            "ls_prefix_attn_fwd", "ls_lse_merge", "ls_lse_merge_groups",
-           "ls_prefix_attn_bwd_workspace_size", "ls_prefix_attn_bwd", "ls_prefix_attn_bwd_ranges", "ls_sparse_attn_workspace_size",
-           "ls_sparse_attn_fwd", "ls_sparse_attn_bwd", "ls_dsa_index_scores", "ls_topk_select",
-           "ls_topk_select_ws", "ls_topk_workspace_size",
+           "ls_prefix_attn_bwd_workspace_size", "ls_prefix_attn_bwd", "ls_prefix_attn_bwd_ranges",
+           "ls_sparse_attn_workspace_size", "ls_sparse_attn_fwd", "ls_sparse_attn_bwd",
+           "ls_dsa_index_scores", "ls_topk_select", "ls_topk_select_ws", "ls_topk_workspace_size",
            "ls_hbm_read_probe", "ls_sparse_attn_fwd_noalloc"]
 
 

@@ -7,8 +7,8 @@ its own pages of the pool (ls_scatter_kv through the page table: right-sized
 pages that belong to the store, not views of a chunk tensor), then its queries
 attend to every earlier position and causally within the chunk
 (ls_prefix_attn_fwd over the chunk's splits, cut finer where they leave CUs
-idle, with q_pos0 = b, then ls_lse_merge).  Chunking does not change the result: row t's output is causal
-attention over positions 0 .. t.
+idle, with q_pos0 = b, then ls_lse_merge).  Chunking does not change the
+result: row t's output is causal attention over positions 0 .. t.
 """
 from __future__ import annotations
 

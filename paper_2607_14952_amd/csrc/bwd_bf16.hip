@@ -185,8 +185,8 @@ __device__ __forceinline__ void dq_step(const BwdArgs& a, char* __restrict__ nex
                                         const char* __restrict__ prev_k, const TileFetch& kf,
                                         const TileFetch& vf, const PageLookup& pl, int32_t& pe,
                                         int64_t t0_next, int64_t t0_after, int64_t k_hi,
-                                        int64_t t0, int64_t kb, int64_t k_all, int64_t my_lim, int w,
-                                        const bf16x8* qreg, const bf16x8* dreg,
+                                        int64_t t0, int64_t kb, int64_t k_all, int64_t my_lim,
+                                        int w, const bf16x8* qreg, const bf16x8* dreg,
                                         const TileOffsets& to, int hh, float lse2, float delta,
                                         f32x16* acc, f32x16& s_prev, f32x16& dp_prev,
                                         f32x16& s, f32x16& dp, DqTail& tail) {
@@ -226,8 +226,8 @@ __device__ __forceinline__ void dq_step(const BwdArgs& a, char* __restrict__ nex
   }
   if (t0 < kb || t0 + kQBN > k_all) mask_keys(s, t0, kb, my_lim, hh);
   if (!kFirst)
-    dq_update<kForm == kRowPage ? 0 : kDqDefer>(prev_k, ds.d0, ds.d1, acc, to, kEarly ? kt0 : nullptr,
-                                      &tail);
+    dq_update<kForm == kRowPage ? 0 : kDqDefer>(prev_k, ds.d0, ds.d1, acc, to,
+                                                kEarly ? kt0 : nullptr, &tail);
 }
 
 // Workgroup z works on a chunk of one of the key ranges.  With `part` each writes
@@ -641,7 +641,8 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(BwdArgs a, int64_t key
   f32x4 sk = {0.f, 0.f, 0.f, 0.f}, sv = sk;
   for (int c = 0; c < n_chunks; ++c) {
     if (dkdv_row_lo(a, j0, c) >= dkdv_row_hi(a, c)) continue;
-    const float* pk = a.dkdv_part + (((int64_t)c * 2 * a.n_kv_heads + g) * n_keys + j - key0) * kD + d0;
+    const float* pk =
+        a.dkdv_part + (((int64_t)c * 2 * a.n_kv_heads + g) * n_keys + j - key0) * kD + d0;
     sk += *reinterpret_cast<const f32x4*>(pk);
     sv += *reinterpret_cast<const f32x4*>(pk + (int64_t)a.n_kv_heads * n_keys * kD);
   }

@@ -35,8 +35,8 @@ using namespace f32m;
 
 // ============================================================== dq
 template <int kDP, int kRW>
-__global__ __launch_bounds__(256, kRW == 4 ? 2 : 1) void bwd_dq_f32_mfma_kernel(BwdArgs a, DqRanges ranges,
-                                                              float* __restrict__ part) {
+__global__ __launch_bounds__(256, kRW == 4 ? 2 : 1) void bwd_dq_f32_mfma_kernel(
+    BwdArgs a, DqRanges ranges, float* __restrict__ part) {
   constexpr int kKW = 4 / kRW;
   constexpr int kS = kRowS<kDP>;
   constexpr int kDB = kDP / 32;

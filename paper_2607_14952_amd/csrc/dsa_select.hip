@@ -19,9 +19,10 @@
 // ring and the exchange.
 //
 // Top-k kernel.  One workgroup per row, or per chunk of a row where rows are few
-// and long (topk_chunks), with a second launch over the candidates.  A histogram of the top 12 bits of an
-// order-preserving 32-bit key of the fp32 scores finds the bin holding the
-// k-th largest key.  When that bin holds at most 4,096 keys (the usual case),
+// and long (topk_chunks), with a second launch over the candidates.  Long rows
+// take the sampled-bound path below; for the others a histogram of the top 12
+// bits of an order-preserving 32-bit key of the fp32 scores finds the bin holding
+// the k-th largest key.  When that bin holds at most 4,096 keys (the usual case),
 // one more pass over the row gathers them into LDS and counts the keys above
 // the bin, and the exact k-th largest key T is found among the gathered keys
 // (two 10-bit digits in LDS); otherwise two more histogram passes over the row

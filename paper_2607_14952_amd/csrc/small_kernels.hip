@@ -534,8 +534,8 @@ hipError_t launch_merge(const float* out_part, const float* lse_part, const int3
   // The narrow kernel: where one thread per item leaves under two waves per
   // SIMD and the parts are more than one batch of loads (16 rows x 16 heads,
   // 257 parts in 9 groups: 79 us in ten launches of one thread per item, 17 us
-  // here; 1 row, 65 parts: 37 us in ten launches, 7 us here with 129 parts).  A single group's bf16 numerator is added in
-  // part order, which one thread does.
+  // here; 1 row, 65 parts: 37 us in ten launches, 7 us here with 129 parts).  A
+  // single group's bf16 numerator is added in part order, which one thread does.
   const bool narrow = items <= 512 * 64 && (most > kMU || n_groups > 1) &&
                       !(bf16_numerator && n_groups == 1);
   if (narrow) {
