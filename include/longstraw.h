@@ -212,14 +212,16 @@ size_t ls_prefix_attn_bwd_workspace_size(const ls_attn_params* p);
  * dk_resp/dv_resp may both be NULL when the range holds no response key.
  * LS_FLAG_ACCUMULATE_DQ / LS_FLAG_ACCUMULATE_DKV select += over =.
  * workspace: device memory of ls_prefix_attn_bwd_workspace_size(p) bytes for
- *   the same p (it grows with the response length q_pos0 + n_q - prefix_len:
- *   it holds the partial dK/dV sums of row chunks and the partial dq sums of
- *   key chunks, and a workspace made for p serves any smaller n_q and q_pos0).
- *   An fp32 call also accepts less, down to the two arrays named next (each
+ *   the same p; one made for p serves any smaller n_q and q_pos0.  Beside the two
+ *   arrays named next it holds the partial dK/dV sums of row chunks, which grow
+ *   with the response length q_pos0 + n_q - prefix_len, and the partial dq sums of
+ *   key chunks: 4 KiB x head_dim for each packed row (query row of one KV head's
+ *   group), at most 512 KiB x head_dim (128 MiB at head_dim 256, from 128 packed
+ *   rows on).  An fp32 call also accepts less, down to the two arrays alone (each
  *   padded to 256 bytes), and then runs on the scalar kernels, which need no
  *   partial sums: slower, and with another rounding order.  Every call first
- *   writes Delta_i = d_out_i . out_i and lse_i * log2(e) ([n_q_heads,
- *   n_q] fp32 each) at the start of the workspace.  LS_FLAG_PREP_READY skips
+ *   writes Delta_i = d_out_i . out_i and lse_i * log2(e) ([n_q_heads, n_q] fp32
+ *   each) at the start of the workspace.  LS_FLAG_PREP_READY skips
  *   that step: the caller asserts that an earlier call on the same stream, with
  *   the same workspace, n_q, n_q_heads, d_out, out and lse, already wrote them
  *   and nothing has overwritten them since (the key ranges of one backward

@@ -734,7 +734,7 @@ int score_tiles(int64_t blocks, int64_t tiles, int64_t slots) {
   const int64_t most_chunks = std::max(least_chunks, std::min(tiles, 4 * slots / blocks));
   for (int64_t c = least_chunks; c <= most_chunks; ++c) {
     const int64_t per = (tiles + c - 1) / c;
-    const int64_t chunks = (tiles + per - 1) / per;   // (65,535: a grid dimension)
+    const int64_t chunks = (tiles + per - 1) / per;
     const int64_t cost = (blocks * chunks + slots - 1) / slots * (per + 4);
     if (cost < least) {
       least = cost;

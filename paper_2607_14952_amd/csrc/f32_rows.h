@@ -136,9 +136,10 @@ __device__ __forceinline__ void dkdv_key(const BwdArgs& a, int64_t j, int g, int
 #pragma unroll
   for (int k = 0; k < kPer; ++k) dk[k] = dv[k] = 0.f;
   const int64_t first = j > a.q_pos0 ? (j - a.q_pos0) * a.group : 0;
-  for (int64_t r = max(row_lo, first); r < row_hi; ++r) {
-    const int64_t row = r / a.group;
-    const int head = (int)(r - row * a.group) + g * a.group;
+  int64_t r = max(row_lo, first), row = r / a.group;
+  int hh = (int)(r - row * a.group);
+  for (; r < row_hi; ++r) {
+    const int head = g * a.group + hh;
     const int64_t pair = row * a.n_q_heads + head;
     float qv[kPer], dov[kPer];
     load_channels<kPer>(qv, static_cast<const float*>(a.q) + pair * a.head_dim, a.head_dim, lane);
@@ -157,6 +158,10 @@ __device__ __forceinline__ void dkdv_key(const BwdArgs& a, int64_t j, int g, int
     for (int k = 0; k < kPer; ++k) {
       dk[k] = fmaf(ds, qv[k], dk[k]);
       dv[k] = fmaf(p, dov[k], dv[k]);
+    }
+    if (++hh == a.group) {
+      hh = 0;
+      ++row;
     }
   }
 }
