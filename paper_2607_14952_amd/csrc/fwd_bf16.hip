@@ -28,6 +28,8 @@
 // natural-log normalizer.
 #include <math.h>
 
+#include <algorithm>
+
 #include "ls_internal.h"
 #include "mfma_common.h"
 
@@ -474,20 +476,48 @@ hipError_t launch_waves(const FwdArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Whether 256-row workgroups of eight waves finish sooner than 128-row ones of four,
+// one per CU each: the rounds of 256 workgroups that the long splits take (those of
+// half the longest one's time or more), or all workgroups' time shared among the CUs
+// where that is more.  A tile takes 0.93 us and start and end 12 with four waves,
+// 1.7 and 28 with eight.  Measured with pages of 16, four and eight waves: 2 and 4
+// workgroups of 128 tiles 121 and 191 us, 504 and 256 of 32 tiles 82 and 83, 504 and
+// 256 of 128 264 and 244, 8,064 and 4,096 of 2 337 and 563 (243 points of equal
+// splits: within 4% of the better one in all but 4).
+bool eight_waves(const FwdArgs& a) {
+  auto time = [&](int rows_per, double tile, double ends) {
+    const int64_t wgs = ((int64_t)a.n_q * a.group + rows_per - 1) / rows_per * a.n_kv_heads;
+    auto one = [&](int i) {
+      return tile * (double)((a.split_end(i) - a.split_begin(i) + kBN - 1) / kBN) + ends;
+    };
+    double most = 0, sum = 0;
+    for (int i = 0; i < a.n_splits; ++i) most = std::max(most, one(i));
+    int64_t longs = 0;
+    for (int i = 0; i < a.n_splits; ++i) {
+      longs += 2 * one(i) >= most;
+      sum += one(i);
+    }
+    return std::max((double)((longs * wgs + 255) / 256) * most, sum * (double)wgs / 256);
+  };
+  return time(256, 1.7, 28) < time(128, 0.93, 12);
+}
+
 }  // namespace
 
 // Calls with more than 128 packed rows take the two-waves-per-SIMD kernel; with
 // fewer, half of its 256-row workgroup would be empty, and four waves do.
 // Pages of 4 rows or fewer (one lookup per key row, more registers) always take
-// four.  Pages of 8 and 16 rows measured 2,421 -> 1,949 us with the lookup per wave
-// instead of per row (1,111 rows x 100,000 keys; 1,844 with pages of 64).
+// four.  Pages of 8 and 16 rows take eight where eight_waves says so.  With a lookup
+// per row and four waves, with one per wave and always eight, and so: 40 rows x
+// 62,987 keys in 2 splits 1,088, 1,500 and 879 us; 1,239 x 1,266 in 32 1,269, 1,428
+// and 1,153; 1,111 x 100,000 in 32 2,139, 1,755 and 1,752.
 hipError_t launch_fwd_bf16_d256(const FwdArgs& a, hipStream_t stream) {
   const PageForm form = page_form(a.log2_page);
   if (form == kRowPage) return launch_waves<kRowPage, 4>(a, stream);
   const bool few = (int64_t)a.n_q * a.group <= 128;
   if (form == kWavePage)
-    return few ? launch_waves<kWavePage, 4>(a, stream)
-               : launch_waves<kWavePage, LS_FWD_WAVES>(a, stream);
+    return few || !eight_waves(a) ? launch_waves<kWavePage, 4>(a, stream)
+                                  : launch_waves<kWavePage, LS_FWD_WAVES>(a, stream);
   return few ? launch_waves<kTilePage, 4>(a, stream)
              : launch_waves<kTilePage, LS_FWD_WAVES>(a, stream);
 }

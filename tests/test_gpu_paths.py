@@ -246,7 +246,7 @@ def test_dsa_scores_chunks(R, P, heads):
 
 
 @pytest.mark.parametrize("page", [4, 8, 16])
-@pytest.mark.parametrize("R", [15, 77], ids=["four_waves", "eight_waves"])
+@pytest.mark.parametrize("R", [15, 77], ids=["few_rows", "more_rows"])
 def test_bf16_short_pages(page, R):
     """Pages shorter than a key tile: a wave's rows in one page (8 and 16), or a
     lookup per row (4).  Splits and ranges begin and end inside pages, tiles and
@@ -502,3 +502,30 @@ def test_more_splits_than_one_launch_takes(cfg):
     splits = [(b, min(b + 4, P)) for b in range(0, P, 4)] + [(P, P + cfg.resp_len)]
     assert len(splits) > 2 * 448
     check_forward(cfg, h, device_inputs(h), splits, P=P, q_pos0=P)
+
+
+@pytest.mark.parametrize("page", [8, 16])
+@pytest.mark.parametrize("R,P,n", [(77, 4_096, 3), (512, 8_192, 8), (300, 3, 1)],
+                         ids=["four_waves", "eight_waves", "own_keys"])
+def test_short_pages_leave_the_bits_of_long_ones(page, R, P, n):
+    """Pages of 8 and 16 take workgroups of four or eight waves by the splits' lengths and
+    number; either way each row's partial results are those of the same positions in
+    pages of 64."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(page + R)
+    total = -(-(P + R) // 64) * 64
+    k, v = (torch.randn((total, 2, 256), device="cuda", generator=g).to(torch.bfloat16)
+            for _ in range(2))
+    q = torch.randn((R, 16, 256), device="cuda", generator=g).to(torch.bfloat16)
+    splits = [(P * i // n, P * (i + 1) // n) for i in range(n)] + [(P, P + R)]
+    print(f"[gpu] pages of {page}, R={R}", flush=True)
+    got = []
+    for S in (page, 64):
+        table = torch.randperm(total // S, device="cuda", generator=g)
+        pools = [torch.empty_like(x).view(-1, S, 2, 256) for x in (k, v)]
+        for pool, x in zip(pools, (k, v)):
+            pool[table] = x.view(-1, S, 2, 256)
+        got.append(B.prefix_attn_fwd(q, B.PagedKV(*pools, table.to(torch.int32)), splits,
+                                     prefix_len=P, q_pos0=P, scale=1 / 16))
+    torch.cuda.synchronize()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
