@@ -440,23 +440,26 @@ hipError_t launch_backward(ls::BwdArgs& a, bool bf16, bool generic,
                            const std::vector<ls_split>& ranges, size_t part_bytes, hipStream_t s) {
   hipError_t e = hipSuccess;
   auto key0 = [&](const ls_split& r) { return std::max(r.kv_begin, a.prefix_len); };
-  if (generic) {
-    for (const ls_split& r : ranges) {
-      a.kv_begin = r.kv_begin;
-      a.kv_end = r.kv_end;
-      if ((e = ls::launch_bwd_f32_generic(a, key0(r), s)) != hipSuccess) return e;
-      a.accumulate_dq = 1;
-    }
-    return e;
-  }
+  auto by_key = [&](const ls_split& r) {
+    return generic || (!bf16 && ls::f32_range_small(a.head_dim, a.head_dim_v,
+                                                    (int64_t)a.n_q * a.group, r.kv_end - r.kv_begin));
+  };
   const int64_t n = (int64_t)a.n_q * a.n_q_heads * a.head_dim;   // values of one partial dq
   const int64_t room = (int64_t)(part_bytes / 4) / n;
   for (size_t i = 0; i < ranges.size();) {
+    if (by_key(ranges[i])) {
+      a.kv_begin = ranges[i].kv_begin;
+      a.kv_end = ranges[i].kv_end;
+      if ((e = ls::launch_dq_f32_generic(a, s)) != hipSuccess) return e;
+      a.accumulate_dq = 1;
+      ++i;
+      continue;
+    }
     ls::DqRanges r;
     r.n = 0;
     r.z0[0] = 0;
     int form = 0;
-    for (; i < ranges.size() && r.n < ls::kMaxDqRanges; ++i) {
+    for (; i < ranges.size() && r.n < ls::kMaxDqRanges && !by_key(ranges[i]); ++i) {
       const int64_t begin = ranges[i].kv_begin, end = ranges[i].kv_end;
       const ls::DqPlan p = bf16 ? ls::plan_dq_bf16_d256(a, begin, end)
                                 : ls::plan_dq_f32_mfma(a, begin, end);
@@ -495,7 +498,9 @@ hipError_t launch_backward(ls::BwdArgs& a, bool bf16, bool generic,
     if (r.kv_end <= a.prefix_len) continue;
     a.kv_begin = r.kv_begin;
     a.kv_end = r.kv_end;
-    e = bf16 ? ls::launch_dkdv_bf16_d256(a, key0(r), s) : ls::launch_dkdv_f32_mfma(a, key0(r), s);
+    e = bf16        ? ls::launch_dkdv_bf16_d256(a, key0(r), s)
+        : by_key(r) ? ls::launch_dkdv_f32_generic(a, key0(r), s)
+                    : ls::launch_dkdv_f32_mfma(a, key0(r), s);
     if (e != hipSuccess) return e;
   }
   return e;

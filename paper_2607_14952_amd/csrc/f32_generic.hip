@@ -1,6 +1,7 @@
 // fp32 replay kernels for any head_dim <= 256 and any GQA group; head dimensions
 // that are multiples of 4 up to 128 run on the matrix cores instead
-// (fwd_f32_mfma.hip, bwd_f32_mfma.hip).  One wave owns one (query row, head) --
+// (fwd_f32_mfma.hip, bwd_f32_mfma.hip), but for the backward of a few keys
+// (f32_range_small).  One wave owns one (query row, head) --
 // or, for the response-key gradients, one (key, KV head) -- and walks its keys
 // one at a time with an online softmax; lane l holds channels l, l+64, l+128,
 // l+192.
@@ -68,13 +69,15 @@ hipError_t launch_fwd_f32(const FwdArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_f32_generic(const BwdArgs& a, int64_t key0, hipStream_t stream) {
-  unsigned blocks = (unsigned)(((int64_t)a.n_q * a.n_q_heads + 3) / 4);
+hipError_t launch_dq_f32_generic(const BwdArgs& a, hipStream_t stream) {
+  const unsigned blocks = (unsigned)(((int64_t)a.n_q * a.n_q_heads + 3) / 4);
   hipLaunchKernelGGL(bwd_dq_f32_kernel, dim3(blocks), dim3(256), 0, stream, a);
-  hipError_t e = hipGetLastError();
+  return hipGetLastError();
+}
+
+hipError_t launch_dkdv_f32_generic(const BwdArgs& a, int64_t key0, hipStream_t stream) {
   const int64_t n_keys = a.kv_end - key0;
-  if (e != hipSuccess || n_keys <= 0) return e;
-  blocks = (unsigned)((n_keys * a.n_kv_heads + 3) / 4);
+  const unsigned blocks = (unsigned)((n_keys * a.n_kv_heads + 3) / 4);
   hipLaunchKernelGGL(bwd_dkdv_f32_kernel, dim3(blocks), dim3(256), 0, stream, a, key0, n_keys);
   return hipGetLastError();
 }

@@ -103,6 +103,20 @@ struct DqPlan {
 // take the others).
 bool f32_mfma_fits(int head_dim, int head_dim_v, int n_kv_heads);
 
+// Whether a backward's key range is so small that the generic kernels finish it first:
+// they walk its keys (for dk/dv its rows) one by one, 0.6 us each at widths up to 64
+// and 0.8 at 128 (0.45), where dk/dv and its reduce take 12 and 21 us on the matrix
+// cores, and dq 8 and 17 in a launch of its own; in one joined with other ranges the
+// key costs nothing more, so the line lies where dk/dv alone pays for a further dq
+// launch.  Measured, generic and matrix cores: the response's range alone, 2 tokens x 2
+// heads of 128 on 1 10 and 40 us, 4 x 2 of 64 13 and 24; steps of 3 ranges, 2 x 4 of 128
+// on 1 68 and 79, 4 x 12 of 96 on 4 66 and 70; past the line 8 x 2 of 64 51 and 47.
+inline bool f32_range_small(int head_dim, int head_dim_v, int64_t rows, int64_t keys) {
+  const int d = head_dim > head_dim_v ? head_dim : head_dim_v;
+  const int64_t width = d <= 64 ? 64 : d <= 96 ? 96 : 128;
+  return 48 * keys + 32 * rows <= 9 * width;
+}
+
 // Everything a forward-split kernel needs; passed by value as a kernel argument.
 struct FwdArgs {
   const void* q;
@@ -266,8 +280,9 @@ hipError_t launch_fwd_bf16_d256(const FwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd_prep(const void* d_out, const void* out, bool dout_bf16, bool out_bf16,
                            const float* lse, int n_q, int n_heads, int dv, float* delta,
                            float* lse2, hipStream_t stream);
-// the generic fp32 kernels over [a.kv_begin, a.kv_end); dk/dv of its keys from key0 on
-hipError_t launch_bwd_f32_generic(const BwdArgs& a, int64_t key0, hipStream_t stream);
+// the generic fp32 kernels: dq over [a.kv_begin, a.kv_end), dk/dv of its keys from key0 on
+hipError_t launch_dq_f32_generic(const BwdArgs& a, hipStream_t stream);
+hipError_t launch_dkdv_f32_generic(const BwdArgs& a, int64_t key0, hipStream_t stream);
 DqPlan plan_dq_bf16_d256(const BwdArgs& a, int64_t begin, int64_t end);
 hipError_t launch_dq_bf16_d256(const BwdArgs& a, const DqRanges& r, float* part,
                                hipStream_t stream);

@@ -37,6 +37,8 @@ def _f32(name, hq, hkv, d, dv, prefix, resp, page=64, shards=1, splits=2):
     _f32("shared_tiles", 8, 4, 96, 96, 4_103, 260),
     # response keys in several blocks and row chunks (five, the last ragged)
     _f32("dkdv_chunks", 8, 2, 128, 128, 100, 300),
+    # a response of a few keys, whose backward runs on the generic kernels
+    _f32("few_keys", 8, 4, 128, 128, 300, 6),
     # the generic kernels: a width that is no multiple of 4, and one past 128
     _f32("generic_d66", 4, 2, 66, 64, 200, 33),
     _f32("generic_d160", 2, 1, 160, 160, 200, 33),
@@ -271,6 +273,8 @@ def test_bf16_short_pages(page, R):
     (_bf16("ranges_whole", 600, 2_100), [0, 300, 600, 2_700]),
     (_f32("ranges", 4, 2, 64, 64, 6_000, 40), [0, 2_000, 2_100, 6_000, 6_040]),
     (_f32("ranges_generic", 2, 1, 160, 160, 300, 9), [0, 100, 300, 309]),
+    # ranges of a few keys, which run on the generic kernels between others
+    (_f32("ranges_small", 4, 2, 64, 64, 600, 4), [0, 5, 300, 306, 600, 604]),
 ], ids=lambda x: getattr(x, "name", ""))
 def test_bwd_ranges_equal_calls(cfg, cuts):
     """Ranges that share launches leave the bits of one call per range: several
