@@ -322,17 +322,45 @@ def bwd_workspace(q, kv: PagedKV, *, prefix_len: int, q_pos0: int):
     return torch.empty(max(n, 16), dtype=torch.uint8, device=q.device)
 
 
+def _bwd_args(q, kv, d_out, out, lse, has_resp, prefix_len, q_pos0, scale, flags, dq, dk_resp,
+              dv_resp, workspace, expected_epoch, stream):
+    """The gradients, the params and the arguments after the key range of a backward call
+    (has_resp: the range holds response keys); what is not given is allocated."""
+    torch = _torch()
+    R, Hq, D = q.shape
+    f32 = torch.float32
+    if dq is None:
+        dq = torch.empty((R, Hq, D), dtype=f32, device=q.device)
+    if has_resp:
+        n_resp, Hkv = q_pos0 + R - prefix_len, kv.k_pool.shape[2]
+        if dk_resp is None:
+            dk_resp = torch.zeros((n_resp, Hkv, D), dtype=f32, device=q.device)
+        if dv_resp is None:
+            dv_resp = torch.zeros((n_resp, Hkv, kv.v_pool.shape[3]), dtype=f32, device=q.device)
+    if workspace is None:
+        workspace = bwd_workspace(q, kv, prefix_len=prefix_len, q_pos0=q_pos0)
+    p = make_params(q, kv, prefix_len=prefix_len, q_pos0=q_pos0, scale=scale, flags=flags,
+                    expected_epoch=expected_epoch)
+    return (dq, dk_resp, dv_resp), p, (
+        _ptr(d_out, q.dtype, "d_out"), _ptr(out, None, "out"), _dtype_code(out),
+        _ptr(lse, f32, "lse"), _ptr(dq, f32, "dq"), _ptr(dk_resp, f32, "dk_resp"),
+        _ptr(dv_resp, f32, "dv_resp"), _ptr(workspace, None, "workspace"),
+        workspace.numel() * workspace.element_size(), _stream(stream))
+
+
 def prefix_attn_bwd(q, kv: PagedKV, d_out, out, lse, *, prefix_len: int, q_pos0: int,
                     scale: float, kv_begin: int = 0, kv_end=None, flags: int = 0, dq=None,
                     dk_resp=None, dv_resp=None, workspace=None, expected_epoch=None,
                     stream=None):
     """ls_prefix_attn_bwd: dq over keys [kv_begin, kv_end) and dK/dV of the
     response keys in that range (rows j - prefix_len of dk_resp / dv_resp)."""
-    kv_end = q_pos0 + q.shape[0] if kv_end is None else kv_end
-    return prefix_attn_bwd_ranges(q, kv, d_out, out, lse, [(kv_begin, kv_end)],
-                                  prefix_len=prefix_len, q_pos0=q_pos0, scale=scale, flags=flags,
-                                  dq=dq, dk_resp=dk_resp, dv_resp=dv_resp, workspace=workspace,
-                                  expected_epoch=expected_epoch, stream=stream)
+    if kv_end is None:
+        kv_end = q_pos0 + q.shape[0]
+    grads, p, args = _bwd_args(q, kv, d_out, out, lse, kv_end > prefix_len, prefix_len, q_pos0,
+                               scale, flags, dq, dk_resp, dv_resp, workspace, expected_epoch,
+                               stream)
+    check(load_library().ls_prefix_attn_bwd(ctypes.byref(p), kv_begin, kv_end, *args))
+    return grads
 
 
 def prefix_attn_bwd_ranges(q, kv: PagedKV, d_out, out, lse, ranges, *, prefix_len: int,
@@ -340,32 +368,13 @@ def prefix_attn_bwd_ranges(q, kv: PagedKV, d_out, out, lse, ranges, *, prefix_le
                            dv_resp=None, workspace=None, expected_epoch=None, stream=None):
     """ls_prefix_attn_bwd_ranges: dq over the key ranges, accumulated in the order
     given, and dK/dV of the response keys in them."""
-    torch = _torch()
-    R, Hq, D = q.shape
-    Hkv, Dv = kv.k_pool.shape[2], kv.v_pool.shape[3]
-    kv_len = q_pos0 + R
-    if dq is None:
-        dq = torch.empty((R, Hq, D), dtype=torch.float32, device=q.device)
-    if any(e > prefix_len for _, e in ranges):
-        n_resp = kv_len - prefix_len
-        if dk_resp is None:
-            dk_resp = torch.zeros((n_resp, Hkv, D), dtype=torch.float32, device=q.device)
-        if dv_resp is None:
-            dv_resp = torch.zeros((n_resp, Hkv, Dv), dtype=torch.float32, device=q.device)
-    if workspace is None:
-        workspace = bwd_workspace(q, kv, prefix_len=prefix_len, q_pos0=q_pos0)
-    p = make_params(q, kv, prefix_len=prefix_len, q_pos0=q_pos0, scale=scale, flags=flags,
-                    expected_epoch=expected_epoch)
+    grads, p, args = _bwd_args(q, kv, d_out, out, lse, any(e > prefix_len for _, e in ranges),
+                               prefix_len, q_pos0, scale, flags, dq, dk_resp, dv_resp, workspace,
+                               expected_epoch, stream)
     n = len(ranges)
     arr = (Split * n)(*[Split(int(b), int(e)) for b, e in ranges])
-    f32 = torch.float32
-    check(load_library().ls_prefix_attn_bwd_ranges(
-        ctypes.byref(p), arr, n, _ptr(d_out, q.dtype, "d_out"), _ptr(out, None, "out"),
-        _dtype_code(out), _ptr(lse, f32, "lse"), _ptr(dq, f32, "dq"),
-        _ptr(dk_resp, f32, "dk_resp"), _ptr(dv_resp, f32, "dv_resp"),
-        _ptr(workspace, None, "workspace"), workspace.numel() * workspace.element_size(),
-        _stream(stream)))
-    return dq, dk_resp, dv_resp
+    check(load_library().ls_prefix_attn_bwd_ranges(ctypes.byref(p), arr, n, *args))
+    return grads
 
 
 # ----------------------------------------------------------------- sparse latent replay
