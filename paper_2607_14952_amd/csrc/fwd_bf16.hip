@@ -476,31 +476,13 @@ hipError_t launch_waves(const FwdArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Whether 256-row workgroups of eight waves finish sooner than 128-row ones of four,
-// one per CU each: the rounds of 256 workgroups that the long splits take (those of
-// half the longest one's time or more), or all workgroups' time shared among the CUs
-// where that is more.  A tile takes 0.93 us and start and end 12 with four waves,
-// 1.7 and 28 with eight.  Measured with pages of 16, four and eight waves: 2 and 4
-// workgroups of 128 tiles 121 and 191 us, 504 and 256 of 32 tiles 82 and 83, 504 and
-// 256 of 128 264 and 244, 8,064 and 4,096 of 2 337 and 563 (243 points of equal
-// splits: within 4% of the better one in all but 4).
-bool eight_waves(const FwdArgs& a) {
-  auto time = [&](int rows_per, double tile, double ends) {
-    const int64_t wgs = ((int64_t)a.n_q * a.group + rows_per - 1) / rows_per * a.n_kv_heads;
-    auto one = [&](int i) {
-      return tile * (double)((a.split_end(i) - a.split_begin(i) + kBN - 1) / kBN) + ends;
-    };
-    double most = 0, sum = 0;
-    for (int i = 0; i < a.n_splits; ++i) most = std::max(most, one(i));
-    int64_t longs = 0;
-    for (int i = 0; i < a.n_splits; ++i) {
-      longs += 2 * one(i) >= most;
-      sum += one(i);
-    }
-    return std::max((double)((longs * wgs + 255) / 256) * most, sum * (double)wgs / 256);
-  };
-  return time(256, 1.7, 28) < time(128, 0.93, 12);
-}
+// Whether 256-row workgroups of eight waves finish sooner than 128-row ones of four
+// (fwd_time): a tile takes 0.93 us and start and end 12 with four waves, 1.7 and 28
+// with eight.  Measured with pages of 16, four and eight waves: 2 and 4 workgroups
+// of 128 tiles 121 and 191 us, 504 and 256 of 32 tiles 82 and 83, 504 and 256 of 128
+// 264 and 244, 8,064 and 4,096 of 2 337 and 563 (243 points of equal splits: within
+// 4% of the better one in all but 4).
+bool eight_waves(const FwdArgs& a) { return fwd_time(a, 256, 1.7, 28) < fwd_time(a, 128, 0.93, 12); }
 
 }  // namespace
 

@@ -13,9 +13,8 @@
 //
 // The MFMA bounds it (64 cycles each; one 16-byte LDS read per 4 of them), so
 // what matters is that every SIMD has a wave: calls whose 128-row workgroups
-// would not give each CU one take kRW = 1, four times as many workgroups with a
-// quarter of the keys per wave (128 rows x 2 heads, 3 splits: 198 -> 58 us; at
-// 288 workgroups of 128 rows kRW = 1 measured 536 us against 422).
+// leave CUs idle take kRW = 1, four times as many workgroups with a quarter of the
+// keys per wave, where these finish sooner (f32_fwd_wide).
 #include "f32_mfma.h"
 
 namespace ls {
@@ -162,9 +161,7 @@ __global__ __launch_bounds__(256, kRW == 4 ? 2 : 1) void fwd_f32_mfma_kernel(Fwd
 template <int kDP>
 void launch(const FwdArgs& a, hipStream_t stream) {
   const int64_t rows = (int64_t)a.n_q * a.group;
-  const int64_t wide = (rows + 127) / 128 * a.n_kv_heads * a.n_splits;
-  // a 128-row workgroup for each CU, or quarter-size ones
-  if (wide >= 256) {
+  if (f32_fwd_wide(a)) {
     const dim3 grid((unsigned)((rows + 127) / 128), a.n_kv_heads, a.n_splits);
     hipLaunchKernelGGL((fwd_f32_mfma_kernel<kDP, 4>), grid, dim3(256), 0, stream, a);
   } else {

@@ -162,6 +162,35 @@ inline int pack_splits(FwdArgs& a, const Split* splits, int n) {
   return a.n_splits;
 }
 
+// An estimate of a forward launch's time in workgroups of rows_per packed rows, one
+// per CU each, that take `tile` for 32 keys and `ends` to start and end: the rounds of
+// 256 workgroups that the long splits take (those of half the longest one's time or
+// more), or all workgroups' time shared among the CUs where that is more.
+inline double fwd_time(const FwdArgs& a, int rows_per, double tile, double ends) {
+  const int64_t wgs = ((int64_t)a.n_q * a.group + rows_per - 1) / rows_per * a.n_kv_heads;
+  auto one = [&](int i) { return tile * (double)((a.split_end(i) - a.split_begin(i) + 31) / 32) + ends; };
+  double most = 0, sum = 0;
+  for (int i = 0; i < a.n_splits; ++i) most = one(i) > most ? one(i) : most;
+  int64_t longs = 0;
+  for (int i = 0; i < a.n_splits; ++i) {
+    longs += 2 * one(i) >= most;
+    sum += one(i);
+  }
+  const double rounds = (double)((longs * wgs + 255) / 256) * most, shared = sum * (double)wgs / 256;
+  return rounds > shared ? rounds : shared;
+}
+
+// Whether the fp32 matrix-core forward takes 128-row workgroups, or 32-row ones whose
+// four waves share the keys.  A tile and the ends (start, merge of the waves) take 4.5
+// and 4 us with 128 rows, 1.77 and 5 with 32, at width 128 (at 64 0.55 of that).
+// Measured at width 128, workgroups of 128 and of 32 rows: 6 and 24 with 256 keys each
+// 44 and 21 us; 120 and 460 46 and 43, with 64 keys 18 and 27, with 4,096 keys 622 and
+// 467; 216 and 828 48 and 81, 20 and 51, 627 and 912; 288 and 1,104 81 and 100, 31 and
+// 64, 1,125 and 1,141 (168 points: within 3% of the better one in all but 3, at most
+// 6% off; 32 rows wherever 128-row workgroups were fewer than the CUs: in all but 52,
+// up to 2.7 times).
+inline bool f32_fwd_wide(const FwdArgs& a) { return fwd_time(a, 128, 4.5, 4) < fwd_time(a, 32, 1.77, 5); }
+
 // Backward.  The dq launches take their key ranges from DqRanges, the dk/dv ones
 // from kv_begin / kv_end.
 struct BwdArgs {

@@ -19,3 +19,16 @@ extern "C" int pack_splits(const ls_split* splits, int n, int i0, int64_t* begin
   }
   return m;
 }
+// Whether a launch of n splits of `keys` keys takes the fp32 forward's 128-row workgroups.
+extern "C" int f32_fwd_wide(int n_q, int group, int n_kv_heads, int n, int keys) {
+  static ls::FwdArgs a;
+  a.n_q = n_q;
+  a.group = group;
+  a.n_kv_heads = n_kv_heads;
+  a.n_splits = n;
+  for (int i = 0; i < n; ++i) {
+    a.split_lo[i] = i * keys;
+    a.split_hi[i] = (i + 1) * keys;
+  }
+  return ls::f32_fwd_wide(a);
+}

@@ -39,6 +39,8 @@ def _f32(name, hq, hkv, d, dv, prefix, resp, page=64, shards=1, splits=2):
     _f32("dkdv_chunks", 8, 2, 128, 128, 100, 300),
     # a response of a few keys, whose backward runs on the generic kernels
     _f32("few_keys", 8, 4, 128, 128, 300, 6),
+    # short splits: 128-row workgroups though they are fewer than the CUs
+    _f32("short_splits", 32, 4, 64, 64, 1_000, 91, splits=10),
     # the generic kernels: a width that is no multiple of 4, and one past 128
     _f32("generic_d66", 4, 2, 66, 64, 200, 33),
     _f32("generic_d160", 2, 1, 160, 160, 200, 33),

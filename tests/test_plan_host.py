@@ -72,3 +72,14 @@ def test_split_bounds_survive_packing(lib, splits):
         got += list(zip(begin[:m], end[:m]))
         i += m
     assert got == splits
+
+
+@pytest.mark.parametrize("n_q,hkv,splits,keys,wide", [
+    # rows of 32 heads on 4 (8 on 2): few workgroups, one round or two of them, more
+    (64, 1, 3, 256, 0), (48, 4, 8, 64, 1), (48, 4, 8, 256, 0), (91, 4, 5, 64, 1),
+    (91, 4, 5, 1_024, 0), (91, 4, 9, 64, 1), (91, 4, 9, 256, 1), (91, 4, 9, 4_096, 1),
+    (91, 4, 20, 256, 1),
+])
+def test_f32_forward_workgroups(lib, n_q, hkv, splits, keys, wide):
+    """The measured better of the two workgroup sizes."""
+    assert lib.f32_fwd_wide(n_q, 8, hkv, splits, keys) == wide
