@@ -440,9 +440,12 @@ hipError_t launch_backward(ls::BwdArgs& a, bool bf16, bool generic,
                            const std::vector<ls_split>& ranges, size_t part_bytes, hipStream_t s) {
   hipError_t e = hipSuccess;
   auto key0 = [&](const ls_split& r) { return std::max(r.kv_begin, a.prefix_len); };
+  const int64_t rows = (int64_t)a.n_q * a.group, width = ls::f32_width(a.head_dim, a.head_dim_v);
   auto by_key = [&](const ls_split& r) {
-    return generic || (!bf16 && ls::f32_range_small(a.head_dim, a.head_dim_v,
-                                                    (int64_t)a.n_q * a.group, r.kv_end - r.kv_begin));
+    return generic || (!bf16 && ls::f32_dq_small(width, rows, r.kv_end - r.kv_begin));
+  };
+  auto by_row = [&](const ls_split& r) {
+    return generic || (!bf16 && ls::f32_dkdv_small(width, rows, r.kv_end - key0(r), a.n_kv_heads));
   };
   const int64_t n = (int64_t)a.n_q * a.n_q_heads * a.head_dim;   // values of one partial dq
   const int64_t room = (int64_t)(part_bytes / 4) / n;
@@ -499,7 +502,7 @@ hipError_t launch_backward(ls::BwdArgs& a, bool bf16, bool generic,
     a.kv_begin = r.kv_begin;
     a.kv_end = r.kv_end;
     e = bf16        ? ls::launch_dkdv_bf16_d256(a, key0(r), s)
-        : by_key(r) ? ls::launch_dkdv_f32_generic(a, key0(r), s)
+        : by_row(r) ? ls::launch_dkdv_f32_generic(a, key0(r), s)
                     : ls::launch_dkdv_f32_mfma(a, key0(r), s);
     if (e != hipSuccess) return e;
   }

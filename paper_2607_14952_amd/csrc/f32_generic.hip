@@ -1,7 +1,7 @@
 // fp32 replay kernels for any head_dim <= 256 and any GQA group; head dimensions
 // that are multiples of 4 up to 128 run on the matrix cores instead
 // (fwd_f32_mfma.hip, bwd_f32_mfma.hip), but for the backward of a few keys
-// (f32_range_small).  One wave owns one (query row, head) --
+// or rows (f32_dq_small, f32_dkdv_small).  One wave owns one (query row, head) --
 // or, for the response-key gradients, one (key, KV head) -- and walks its keys
 // one at a time with an online softmax; lane l holds channels l, l+64, l+128,
 // l+192.

@@ -103,18 +103,26 @@ struct DqPlan {
 // take the others).
 bool f32_mfma_fits(int head_dim, int head_dim_v, int n_kv_heads);
 
-// Whether a backward's key range is so small that the generic kernels finish it first:
-// they walk its keys (for dk/dv its rows) one by one, 0.6 us each at widths up to 64
-// and 0.8 at 128 (0.45), where dk/dv and its reduce take 12 and 21 us on the matrix
-// cores, and dq 8 and 17 in a launch of its own; in one joined with other ranges the
-// key costs nothing more, so the line lies where dk/dv alone pays for a further dq
-// launch.  Measured, generic and matrix cores: the response's range alone, 2 tokens x 2
-// heads of 128 on 1 10 and 40 us, 4 x 2 of 64 13 and 24; steps of 3 ranges, 2 x 4 of 128
-// on 1 68 and 79, 4 x 12 of 96 on 4 66 and 70; past the line 8 x 2 of 64 51 and 47.
-inline bool f32_range_small(int head_dim, int head_dim_v, int64_t rows, int64_t keys) {
+// Whether the generic kernels finish a small part of an fp32 backward first.  They walk
+// the keys of dq and the rows of dk/dv one by one, 0.6 and 0.4 us each, where the
+// matrix cores and the reduce after them take 8 and 12 us, 17 and 21 at width 128.
+// Measured, generic and matrix cores, in calls of the response's keys alone: dk/dv of
+// 16 rows of 64 21 and 25 us, of 24 of 16 25 and 25, of 32 of 64 29 and 26, of 48 of 128
+// 46 and 44; dq of 4 keys of 64 21 and 25, of 4 of 128 30 and 42.  The generic dk/dv has
+// a wave per key and KV head: 2,048 of 20 rows of 64 28 and 30 us, 4,096 32 and 30,
+// 16,384 64 and 44.
+inline int64_t f32_width(int head_dim, int head_dim_v) {
   const int d = head_dim > head_dim_v ? head_dim : head_dim_v;
-  const int64_t width = d <= 64 ? 64 : d <= 96 ? 96 : 128;
-  return 48 * keys + 32 * rows <= 9 * width;
+  return d <= 64 ? 64 : d <= 96 ? 96 : 128;
+}
+inline bool f32_dkdv_small(int64_t width, int64_t rows, int64_t keys, int n_kv_heads) {
+  return 3 * rows <= width && keys * n_kv_heads <= 2048;
+}
+// A dq range that shares its launch with others costs little more, and which they are
+// must not change its bits: the line lies below the one for a range alone.  4 keys with
+// two ranges of 1,000 and 3,096: width 64 25 us for 23, 128 35 for 29, 8 keys 40 for 32.
+inline bool f32_dq_small(int64_t width, int64_t rows, int64_t keys) {
+  return 32 * keys <= width || 48 * keys + 32 * rows <= 9 * width;
 }
 
 // Everything a forward-split kernel needs; passed by value as a kernel argument.

@@ -41,6 +41,9 @@ def _f32(name, hq, hkv, d, dv, prefix, resp, page=64, shards=1, splits=2):
     _f32("few_keys", 8, 4, 128, 128, 300, 6),
     # short splits: 128-row workgroups though they are fewer than the CUs
     _f32("short_splits", 32, 4, 64, 64, 1_000, 91, splits=10),
+    # dk/dv of few rows on the generic kernel, dq on the matrix cores; the reverse
+    _f32("few_rows", 2, 1, 64, 64, 300, 10),
+    _f32("few_dq_keys", 32, 2, 128, 128, 300, 4),
     # the generic kernels: a width that is no multiple of 4, and one past 128
     _f32("generic_d66", 4, 2, 66, 64, 200, 33),
     _f32("generic_d160", 2, 1, 160, 160, 200, 33),
